@@ -69,21 +69,27 @@ extern "C" {
 
 /* flags */
 #define FCM_F_KAHAN_ONLY  (1u << 0)  /* cross-block reduction in compensated FP32
-                                        instead of FP64 */
+                                        instead of FP64 (per-voxel passes; a solve over
+                                        the grey levels sums in FP64 throughout) */
 #define FCM_F_TIMING      (1u << 1)  /* time every fused pass with HIP events */
 
 /* iteration drivers */
 #define FCM_DRIVER_LOOP   0     /* one launch per pass from the host */
 #define FCM_DRIVER_GRAPH  1     /* a hipGraph of graph_k passes, replayed */
-#define FCM_DRIVER_PERSISTENT 2 /* one persistent launch runs the data-range pass
-                                   and every pass of a solve (default where
-                                   supported) */
-#define FCM_DRIVER_HISTOGRAM  3 /* histogram domain: one pass counts the grey levels,
-                                   then Algorithm 1 runs over the (at most 256)
-                                   levels present in FP64 in one block; every voxel
-                                   sum regroups exactly by level, so the result is the
-                                   same iteration (up to rounding order), and the data
-                                   are read once per solve */
+#define FCM_DRIVER_PERSISTENT 2 /* one launch runs a whole solve (default where
+                                   supported).  With a grid, an exchange or the
+                                   cooperative launch chosen by the caller: the
+                                   data-range pass and every pass over the voxels.
+                                   With all three left to the library (grid 0,
+                                   FCM_EXCHANGE_AUTO, FCM_LAUNCH_RESIDENT), and fewer
+                                   than 2^32 voxels: over the grey levels, as
+                                   FCM_DRIVER_HISTOGRAM (any start; with
+                                   FCM_INIT_RANDOM_U from pass 2 on) */
+#define FCM_DRIVER_HISTOGRAM  3 /* histogram domain: the voxels are read once, into
+                                   counts per grey level, and Algorithm 1 runs over the
+                                   (at most 256) levels present in FP64 in one block;
+                                   every voxel sum regroups exactly by level, so the
+                                   result is the same iteration (up to rounding) */
 
 /* how the blocks of a persistent launch combine their partial sums each pass */
 #define FCM_EXCHANGE_AUTO      0  /* all-gather on small grids, else leader */
@@ -124,9 +130,11 @@ typedef struct fcm_params {
 
 typedef struct fcm_tuning {
     int32_t block;      /* threads per block of the fused pass: 256 (the only size built) */
-    int32_t grid;       /* blocks of the fused pass; 0 picks from the device and n.
-                           The persistent driver caps it at the number of blocks
-                           that fit on the device at once. */
+    int32_t grid;       /* blocks of the fused pass; 0 picks from the device and n
+                           (persistent driver: see FCM_DRIVER_PERSISTENT).  The
+                           persistent driver caps it at the number of blocks that
+                           fit on the device at once.  fcm_get_tuning reports the
+                           grid that a per-voxel pass would take. */
     int32_t unroll;     /* 16-voxel chunks in flight per thread: 1 or 2 */
     int32_t driver;     /* FCM_DRIVER_* */
     int32_t graph_k;    /* loop/graph drivers: passes per host synchronisation
@@ -182,12 +190,12 @@ int fcm_solve(fcm_handle* h, fcm_result* out);
 int fcm_labels(fcm_handle* h, uint8_t* d_labels);
 
 /* Enqueue a whole solve (reset, start, Algorithm 1 to its end) on the
- * handle's stream and return without waiting: with the persistent driver this
- * is one kernel launch and no host synchronisation, so that solves and other
- * work can follow back to back (serving loops, pipelines).  d_labels (device,
- * n bytes, may be NULL): the labels of the result (as fcm_labels writes
- * them), computed by the same launch once the solve ends.  With the other
- * drivers, or the random-membership start, whose passes are driven from the
+ * handle's stream and return without waiting: with the persistent and the
+ * histogram driver this is one kernel launch (and one more for the labels of a
+ * solve over the grey levels) and no host synchronisation, so that solves and
+ * other work can follow back to back (serving loops, pipelines).  d_labels
+ * (device, n bytes, may be NULL): the labels of the result (as fcm_labels
+ * writes them).  With the other drivers, or the random-membership start, whose passes are driven from the
  * host, it runs the synchronous solve (and fcm_labels).  The result is read
  * with fcm_solve_wait; trajectories may be requested meanwhile (they are
  * ordered on the same stream).  A wait that hits its time limit in any
@@ -305,7 +313,8 @@ void fcm_batch_destroy(fcm_batch* b);
  * appended.  Choices are also cached per process.  The data must not change
  * during the call. */
 
-/* Single instance: persistent driver (ordinary launch) over grids from half
+/* Single instance: the configuration at entry, the persistent driver's
+ * per-voxel pass (ordinary launch) over grids from half
  * the CU count up to one 16-voxel chunk per thread, leader, all-gather and two-level
  * exchange, unroll 1 and 2; graph driver with 4 and 16 passes per graph.
  * Key: C, the m class (2, 1.5, other), the precision flag and floor(log2 n).

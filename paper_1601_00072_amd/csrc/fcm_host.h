@@ -16,6 +16,7 @@ namespace fcm {
 struct HandleShape {
     int64_t n, nbody;   // voxels, aligned 16-voxel chunks
     int C, mclass, kahan, device, ncu, coop;
+    int grid_asked;     // the grid as set by the caller (0: the library's choice)
 };
 struct BatchShape {
     int64_t voxels;     // all instances

@@ -1,17 +1,12 @@
-// Histogram-domain FCM: Algorithm 1 run over the grey levels of an 8-bit
-// input instead of its voxels.
+// Solve of one instance over its grey levels: one launch counts the levels of
+// the whole input and runs Algorithm 1 on the counts (fcm_level_dev.h).
 //
-// Every sum of Eq.1 and Eq.3 over the voxels regroups exactly by grey level,
-// sum_i f(x_i) = sum_g h_g f(g), and the memberships of Eq.4 depend on a
-// voxel only through its grey level, so the largest membership change of
-// Algorithm 1 is the largest change over the levels present.  After one
-// histogram pass the whole iteration therefore runs on at most 256 levels
-// (the binning idea the paper cites in Sec. 3, made exact here because the
-// data are 8-bit).  One block does it: thread g owns grey level g; the
-// per-level memberships, the weighted sums, the objective and the change
-// are FP64; the sums over the levels use fixed-order wave reductions.  The
-// history and the state are written in the same layout as the per-voxel
-// drivers, so results, trajectories and labels read the same way.
+// The blocks count their share of the voxels into LDS and add the 256 counts
+// to global counters; the last block to arrive (atomic ticket) takes the
+// totals and iterates, the others are gone by then.  Nobody waits for another
+// block, so the grid need not be resident at once.  The history and the state
+// are written in the same layout as the per-voxel drivers', so results,
+// trajectories and labels read the same way and the drivers can be mixed.
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -19,186 +14,154 @@
 #include "fcm.h"
 #include "fcm_device.h"
 #include "fcm_internal.h"
+#include "fcm_level.h"
+#include "fcm_level_dev.h"
 
 namespace fcm {
 
 namespace {
 
-// Eq.4 at grey level g for centroids v, in the normalised form
-// u_k = w_k / sum_j w_j with w_k = (d_min / d_k)^(2/(m-1)) <= 1, and the
-// zero-distance rule (equal split over the clusters at distance 0).
+// The result fields of a state record (one thread).
 template <int C>
-__device__ __forceinline__ void level_memberships(double g, const double (&v)[C], double m, double (&u)[C]) {
-    double d[C];
-    double dmin = 1.0e308;
-    int nz = 0;
-#pragma unroll
-    for (int k = 0; k < C; ++k) {
-        d[k] = fabs(g - v[k]);
-        dmin = fmin(dmin, d[k]);
-        nz += d[k] == 0.0;
-    }
-    if (nz) {
-#pragma unroll
-        for (int k = 0; k < C; ++k) u[k] = d[k] == 0.0 ? 1.0 / nz : 0.0;
-        return;
-    }
-    double s = 0.0;
-#pragma unroll
-    for (int k = 0; k < C; ++k) {
-        const double r = dmin / d[k];
-        u[k] = m == 2.0 ? r * r : pow(r, 2.0 / (m - 1.0));
-        s += u[k];
-    }
-#pragma unroll
-    for (int k = 0; k < C; ++k) u[k] /= s;
-}
-
-__device__ __forceinline__ double wave_max_f64(double v) {
-    v = fmax(v, dpp_mov_f64<0xB1>(v));
-    v = fmax(v, dpp_mov_f64<0x4E>(v));
-    v = fmax(v, dpp_mov_f64<0x141>(v));
-    v = fmax(v, dpp_mov_f64<0x140>(v));
-    return fmax(fmax(readlane_d(v, 0), readlane_d(v, 16)), fmax(readlane_d(v, 32), readlane_d(v, 48)));
-}
-
-template <int C>
-__global__ __launch_bounds__(256) void fcm_levels_kernel(LevelArgs a) {
-    constexpr int NQ = 2 * C + 1;
-    const int g = threadIdx.x, lane = g & 63, wid = g >> 6;
-    DevState* st = a.st;
-    const uint32_t cnt = a.counts[g];
-    const double c = (double)cnt, x = (double)g;
-    __shared__ double s_v[C], s_vp[C];
-    __shared__ double s_sum[4][NQ + 1];
-    __shared__ int s_p, s_done;
+__device__ __forceinline__ void level_commit(DevState* st, const LevelArgs& a, const LevelOutcome& o,
+                                             const LevelScratch& sh, int64_t total) {
     if (a.do_init) {
-        __shared__ uint32_t s_lo[4], s_hi[4];
-        uint32_t lo = cnt ? g : 255u, hi = cnt ? g : 0u;
-        lo = wave_min_u32(lo);
-        hi = wave_max_u32(hi);
-        if (lane == 0) {
-            s_lo[wid] = lo;
-            s_hi[wid] = hi;
-        }
-        __syncthreads();
-        if (g == 0) {
-            for (int w = 1; w < 4; ++w) {
-                lo = min(lo, s_lo[w]);
-                hi = max(hi, s_hi[w]);
-            }
-            double v[C];
-            start_centroids(C, lo, hi, a.given, a.v0, a.dv0, v);
-            commit_start(st, a.hist_v, C, lo, hi, v);
-            for (int k = 0; k < C; ++k) s_v[k] = v[k];
-            s_p = 0;
-            s_done = 0;
-        }
-    } else if (g == 0) {
-        s_p = st->pass;
-        s_done = st->done;
+        st->lo = o.lo;
+        st->hi = o.hi;
+    }
+    if (o.iters >= 0 || a.do_init) {
+        st->pass = o.pass;
+        st->iters = o.iters;
+        st->passes = o.iters + 1;
+        st->status = o.status;
+        st->done = o.done;
+        st->delta = o.delta;
+        st->J = o.J;
         for (int k = 0; k < C; ++k) {
-            s_v[k] = a.hist_v[(int64_t)s_p * C + k];
-            s_vp[k] = s_p > 0 ? a.hist_v[(int64_t)(s_p - 1) * C + k] : s_v[k];
+            st->vres[k] = sh.vp[k];
+            st->v32[o.pass & 1][k] = (float)sh.v[k];
+            st->v32[(o.pass + 1) & 1][k] = (float)sh.vp[k];
         }
     }
+    st->sync.passes_total = (uint64_t)total;
+}
+
+template <int C, int MK, bool LEARNED>
+__global__ __launch_bounds__(kLvBlock, LEARNED ? 2 : 4) void fcm_level_kernel(LevelArgs a) {
+    __shared__ __align__(16) uint32_t tab[256 * 64];
+    __shared__ int s_last;
+    const int tid = threadIdx.x, G = gridDim.x;
+    DevState* st = a.st;
+    if (!a.do_init && st->done) return;
+    level_clear(tab);
     __syncthreads();
-    for (int budget = a.max_passes; budget > 0 && !s_done; --budget) {
-        const int p = s_p;
-        double v[C], u[C];
-#pragma unroll
-        for (int k = 0; k < C; ++k) v[k] = s_v[k];
-        level_memberships<C>(x, v, a.m, u);
-        double dm = 0.0;
-        if (p > 0 && cnt) {
-            double vp[C], up[C];
-#pragma unroll
-            for (int k = 0; k < C; ++k) vp[k] = s_vp[k];
-            level_memberships<C>(x, vp, a.m, up);
-#pragma unroll
-            for (int k = 0; k < C; ++k) dm = fmax(dm, fabs(u[k] - up[k]));
-        }
-        double q[NQ];
-        double J = 0.0;
-#pragma unroll
-        for (int k = 0; k < C; ++k) {
-            const double w = c * (a.m == 2.0 ? u[k] * u[k] : pow(u[k], a.m));
-            q[k] = w * x;                       // sum of u^m x (Eq.3 numerator)
-            q[C + k] = w;                       // sum of u^m (Eq.3 denominator)
-            J += w * (x - v[k]) * (x - v[k]);   // Eq.1
-        }
-        q[2 * C] = J;
-#pragma unroll
-        for (int i = 0; i < NQ; ++i) {
-            const double r = wave_sum_f64(q[i]);
-            if (lane == 0) s_sum[wid][i] = r;
-        }
-        const double mx = wave_max_f64(dm);
-        if (lane == 0) s_sum[wid][NQ] = mx;
-        __syncthreads();
-        if (g == 0) {
-            double r[NQ];
-            for (int i = 0; i < NQ; ++i) r[i] = ((s_sum[0][i] + s_sum[1][i]) + s_sum[2][i]) + s_sum[3][i];
-            const double delta =
-                p > 0 ? fmax(fmax(s_sum[0][NQ], s_sum[1][NQ]), fmax(s_sum[2][NQ], s_sum[3][NQ])) : __builtin_nan("");
-            double vnext[C];
-            bool bad = false;
-            for (int k = 0; k < C; ++k) {
-                vnext[k] = r[C + k] > 0.0 ? r[k] / r[C + k] : v[k];
-                bad = bad || !isfinite(vnext[k]);
-            }
-            bad = bad || !isfinite(r[2 * C]);
-            int status = FCM_RUNNING, done = 0;
-            if (bad) {
-                status = FCM_ENUMERIC;
-                done = 1;
-            } else if (p >= 1 && delta < a.eps) {
-                status = FCM_OK;
-                done = 1;
-            } else if (p >= a.max_iter) {
-                status = FCM_NOT_CONVERGED;
-                done = 1;
-            }
-            a.hist_J[p] = r[2 * C];
-            a.hist_d[p] = delta;
-            for (int k = 0; k < C; ++k) st->vres[k] = v[k];
-            st->iters = p;
-            st->J = r[2 * C];
-            st->delta = delta;
-            st->passes = p + 1;
-            st->sync.passes_total += 1;
-            if (!done) {
-                for (int k = 0; k < C; ++k) {
-                    a.hist_v[(int64_t)(p + 1) * C + k] = vnext[k];
-                    st->v32[(p + 1) & 1][k] = (float)vnext[k];
-                    s_vp[k] = v[k];
-                    s_v[k] = vnext[k];
-                }
-                st->pass = p + 1;
-                s_p = p + 1;
-            }
-            st->status = status;
-            st->done = done;
-            s_done = done;
+    char* t8 = reinterpret_cast<char*>(tab);
+    level_count(t8, reinterpret_cast<const uint4*>(a.x + a.head), (int64_t)blockIdx.x * kLvBlock + tid, a.nbody,
+                (int64_t)G * kLvBlock);
+    if (blockIdx.x == 0) level_ragged(t8, a.x, a.n, a.head, a.nbody);
+    __syncthreads();
+    uint32_t cnt = level_total(tab);
+    if (G > 1) {
+        const int copies = G < kLvCopies ? G : kLvCopies;
+        if (cnt) {
+            // the returned value is consumed, so the wave goes on only when
+            // its add has been performed
+            const uint32_t old = __hip_atomic_fetch_add(a.counts + (blockIdx.x % copies) * 256 + tid, cnt,
+                                                        __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            asm volatile("" ::"v"(old));
         }
         __syncthreads();
+        if (tid == 0) {
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+            const uint32_t prev = __hip_atomic_fetch_add(&st->ticket, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+            s_last = prev == (uint32_t)G - 1u;
+        }
+        __syncthreads();
+        if (!s_last) return;
+        if (tid < 256) {
+            // atomic loads are served where the adds were performed
+            uint32_t part[kLvCopies];
+#pragma unroll
+            for (int c = 0; c < kLvCopies; ++c) part[c] = load_coherent(a.counts + c * 256 + tid);
+            cnt = 0u;
+#pragma unroll
+            for (int c = 0; c < kLvCopies; ++c) {
+                cnt += part[c];
+                store_coherent(a.counts + c * 256 + tid, 0u);
+            }
+        }
+        if (tid == 0) st->ticket = 0;
     }
+    __syncthreads();  // the table is read out: its memory becomes the iteration's scratch
+    if (tid >= 64 * kLvIterWaves) return;
+    LevelScratch& sh = *reinterpret_cast<LevelScratch*>(tab);
+    LevelProblem pb{};
+    pb.eps = a.eps;
+    pb.m = a.m;
+    pb.alpha = 1.0 / (a.m - 1.0);
+    pb.max_iter = a.max_iter;
+    pb.max_passes = a.max_passes;
+    pb.do_init = a.do_init;
+    pb.given = a.given;
+    pb.pass = a.do_init ? 0 : st->pass;
+    pb.fp32_range = a.fp32_range;
+    pb.n = a.n;
+    pb.v0 = a.v0;
+    pb.dv0 = a.dv0;
+    pb.mlp_w = a.mlp_w;
+    pb.hist_v = a.hist_v;
+    pb.hist_d = a.hist_d;
+    pb.hist_J = a.hist_J;
+    pb.times = nullptr;
+    LevelOutcome o{};
+    level_iterate<C, MK, LEARNED>(pb, cnt, sh, o);
+    if (tid >= 256) {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        if (tid == 256) {
+            const int64_t total = (int64_t)st->sync.passes_total + o.passes;
+            if (!a.do_init) {
+                o.lo = st->lo;
+                o.hi = st->hi;
+            }
+            level_commit<C>(st, a, o, sh, total);
+            level_commit<C>(a.host, a, o, sh, total);
+            a.host->lo = o.lo;
+            a.host->hi = o.hi;
+        }
+    }
+}
+
+template <int C, bool LEARNED>
+hipError_t launch_c(const LevelArgs& a, int mclass, int grid, hipStream_t s) {
+    if (mclass == kM2)
+        hipLaunchKernelGGL((fcm_level_kernel<C, kM2, LEARNED>), dim3(grid), dim3(kLvBlock), 0, s, a);
+    else if (mclass == kM15)
+        hipLaunchKernelGGL((fcm_level_kernel<C, kM15, LEARNED>), dim3(grid), dim3(kLvBlock), 0, s, a);
+    else
+        hipLaunchKernelGGL((fcm_level_kernel<C, kMGeneric, LEARNED>), dim3(grid), dim3(kLvBlock), 0, s, a);
+    return hipGetLastError();
+}
+
+template <int C>
+hipError_t launch_c(const LevelArgs& a, int mclass, int grid, hipStream_t s) {
+    return a.do_init && a.given == 3 ? launch_c<C, true>(a, mclass, grid, s) : launch_c<C, false>(a, mclass, grid, s);
 }
 
 }  // namespace
 
-hipError_t launch_levels(const LevelArgs& a, int C, hipStream_t s) {
+hipError_t launch_levels(const LevelArgs& a, int C, int mclass, int grid, hipStream_t s) {
     switch (C) {
-        case 2: hipLaunchKernelGGL(fcm_levels_kernel<2>, dim3(1), dim3(256), 0, s, a); break;
-        case 3: hipLaunchKernelGGL(fcm_levels_kernel<3>, dim3(1), dim3(256), 0, s, a); break;
-        case 4: hipLaunchKernelGGL(fcm_levels_kernel<4>, dim3(1), dim3(256), 0, s, a); break;
-        case 5: hipLaunchKernelGGL(fcm_levels_kernel<5>, dim3(1), dim3(256), 0, s, a); break;
-        case 6: hipLaunchKernelGGL(fcm_levels_kernel<6>, dim3(1), dim3(256), 0, s, a); break;
-        case 7: hipLaunchKernelGGL(fcm_levels_kernel<7>, dim3(1), dim3(256), 0, s, a); break;
-        case 8: hipLaunchKernelGGL(fcm_levels_kernel<8>, dim3(1), dim3(256), 0, s, a); break;
+        case 2: return launch_c<2>(a, mclass, grid, s);
+        case 3: return launch_c<3>(a, mclass, grid, s);
+        case 4: return launch_c<4>(a, mclass, grid, s);
+        case 5: return launch_c<5>(a, mclass, grid, s);
+        case 6: return launch_c<6>(a, mclass, grid, s);
+        case 7: return launch_c<7>(a, mclass, grid, s);
+        case 8: return launch_c<8>(a, mclass, grid, s);
         default: return hipErrorInvalidValue;
     }
-    return hipGetLastError();
 }
 
 }  // namespace fcm

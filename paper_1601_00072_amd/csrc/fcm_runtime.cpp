@@ -24,6 +24,7 @@
 #include "fcm_random.h"
 #include "fcm_internal.h"
 #include "fcm_learn.h"
+#include "fcm_level.h"
 
 using namespace fcm;
 
@@ -102,14 +103,18 @@ struct fcm_handle {
     int mclass = kM2;
     float alpha = 1.f, mexp = 2.f;
 
+    void* d_arena = nullptr;       // one allocation: d_state, d_lcounts, d_minmax, d_hist
     DevState* d_state = nullptr;
+    uint32_t* d_lcounts = nullptr; // [kLvCopies][256] grey-level counters of the level solve, zero between launches
+    // per-voxel drivers and the random start (ensure_voxel_ws)
     float* d_partials = nullptr;   // [rows][grid] partial rows of the per-pass launches
     uint32_t* d_minmax = nullptr;  // [2][grid]
     uint64_t* d_rows = nullptr;    // [2][kMaxPersistGrid][rows] tagged partial rows (cooperative driver)
     uint64_t* d_mmrows = nullptr;  // [2][kMaxPersistGrid][2] tagged grey-level ranges (cooperative driver)
     bool aborted = false;          // a cooperative wait timed out; the next reset clears everything
     double* d_hist = nullptr;      // v: (max_iter + 2) * C, then delta, then J: (max_iter + 2) each
-    DevState* h_state = nullptr;
+    DevState* h_state = nullptr;   // pinned: [0] the host's view, [1] written by the level solve itself
+    bool mirrored = false;         // h_state[1] holds the state that the last launch left
 
     fcm_tuning tun{};
     int grid = 1;               // resolved grid of the current driver
@@ -146,6 +151,19 @@ namespace {
 
 int64_t chunk_blocks(const fcm_handle* h) { return (h->nbody + kBlock - 1) / kBlock; }
 
+// Blocks of a level solve: one per 16,384 voxels, at most one per CU.  Fewer,
+// larger shares leave the count of a small input to too few CUs (256x256
+// pixels, solve and labels: 35.9 us with 65,536 voxels per block, 33.6 with
+// 16,384; 128x128x64 voxels: 23.3 and 20.1); smaller ones pay for more blocks
+// at the global counters (8,192: 20.9).  Two blocks per CU do not read faster
+// and contend there (512x512x256 voxels: 93 us with 512 blocks, 75 with 256,
+// 85 with 128).
+constexpr int64_t kLevelVoxelsPerBlock = 16384;
+int level_grid(const fcm_handle* h) {
+    return (int)std::max<int64_t>(
+        1, std::min<int64_t>((h->n + kLevelVoxelsPerBlock - 1) / kLevelVoxelsPerBlock, h->ncu));
+}
+
 // Internal start mode of a warm solve on the persistent driver: histogram and
 // network inference inside the solve kernel.
 constexpr int32_t kInitLearnedFused = 0x100;
@@ -153,6 +171,24 @@ constexpr int32_t kInitLearnedFused = 0x100;
 int start_mode(int init) {
     return init == FCM_INIT_GIVEN ? 1 : (init == FCM_INIT_DEVICE ? 2 : (init == kInitLearnedFused ? 3 : 0));
 }
+
+// Whether a solve runs over the grey levels (one read of the voxels, then
+// Algorithm 1 on 256 counts) instead of over the voxels in every pass.  The
+// persistent driver does so wherever the caller left the launch to the
+// library: an explicit grid, exchange or cooperative launch asks for the
+// per-voxel pass in that shape, as do the loop and graph drivers.  Measured
+// (C = 4, m = 2, solve and labels, per voxel and over the levels): 256x256
+// pixels 99.7 and 33.6 us, 128x128x64 voxels 108 and 20 us (enqueued),
+// 512x512x256 voxels 1,547 and 75 us; there is no size at which the
+// per-voxel pass is the faster one.  The 32-bit counters bound n.
+bool level_tuning(const fcm_handle* h, const fcm_tuning& t) {
+    if (h->n > (int64_t)UINT32_MAX) return false;
+    return t.driver == FCM_DRIVER_HISTOGRAM ||
+           (t.driver == FCM_DRIVER_PERSISTENT && t.grid == 0 && t.exchange == FCM_EXCHANGE_AUTO &&
+            t.launch == FCM_LAUNCH_RESIDENT);
+}
+
+bool use_levels(const fcm_handle* h) { return level_tuning(h, h->tun); }
 
 int resolve_grid(fcm_handle* h, int* out) {
     int64_t want = h->tun.grid > 0 ? h->tun.grid : std::min<int64_t>(chunk_blocks(h), 4LL * h->ncu);
@@ -233,6 +269,13 @@ int build_graph(fcm_handle* h) {
 }
 
 int read_state(fcm_handle* h) {
+    if (h->mirrored) {  // the launch itself left its result in host memory
+        FCM_HIP(hipStreamSynchronize(h->stream));
+        const DevState& m = h->h_state[1];
+        std::memcpy(h->h_state, &m, offsetof(DevState, sync));
+        h->h_state->sync.passes_total = m.sync.passes_total;
+        return FCM_OK;
+    }
     FCM_HIP(hipMemcpyAsync(h->h_state, h->d_state, sizeof(DevState), hipMemcpyDeviceToHost, h->stream));
     FCM_HIP(hipStreamSynchronize(h->stream));
     if (h->h_state->sync.abort) {
@@ -285,9 +328,41 @@ int flush_init(fcm_handle* h) {
     ia.dv0 = h->dv0;
     const int igrid = (int)std::max<int64_t>(1, std::min<int64_t>(chunk_blocks(h), std::min<int64_t>(4LL * h->ncu,
                                                                                                       kMaxGrid)));
+    h->mirrored = false;
     hipError_t e = launch_init(ia, igrid, h->stream);
     if (e != hipSuccess) return dev_err(e, "launch_init");
     h->pending_init = false;
+    return FCM_OK;
+}
+
+// Enqueue a level solve of up to max_passes passes (from v^0 if the
+// data-range pass is pending).
+int enqueue_levels(fcm_handle* h, int max_passes) {
+    LevelArgs a{};
+    a.x = h->d_x;
+    a.n = h->n;
+    a.head = h->head;
+    a.nbody = h->nbody;
+    a.st = h->d_state;
+    a.host = h->h_state + 1;
+    a.counts = h->d_lcounts;
+    a.hist_v = h->hist_v();
+    a.hist_d = h->hist_d();
+    a.hist_J = h->hist_J();
+    a.eps = h->p.eps;
+    a.m = h->p.m;
+    a.max_iter = h->p.max_iter;
+    a.do_init = h->pending_init ? 1 : 0;
+    a.given = start_mode(h->p.init);
+    a.max_passes = max_passes;
+    a.fp32_range = h->tun.driver == FCM_DRIVER_PERSISTENT ? 1 : 0;
+    for (int k = 0; k < kMaxC; ++k) a.v0[k] = h->given[k];
+    a.dv0 = h->dv0;
+    a.mlp_w = h->mlp_w;
+    hipError_t e = launch_levels(a, h->p.n_clusters, h->mclass, level_grid(h), h->stream);
+    if (e != hipSuccess) return dev_err(e, "launch_levels");
+    h->pending_init = false;
+    h->mirrored = true;
     return FCM_OK;
 }
 
@@ -309,6 +384,7 @@ int run_random_start(fcm_handle* h, int& batch) {
     }
     const int grid = (int)std::max<int64_t>(1, std::min<int64_t>(chunk_blocks(h), std::min<int64_t>(4LL * h->ncu,
                                                                                                      kMaxGrid)));
+    h->mirrored = false;
     const PassArgs a = pass_args(h);
     for (int phase = first; phase < last; ++phase) {
         hipError_t e = launch_random_pass(a, h->p.n_clusters, phase, h->p.seed, grid, h->stream);
@@ -346,36 +422,18 @@ int run_batch(fcm_handle* h, int batch) {
         int rc = fold_async(h);
         if (rc != FCM_OK) return rc;
     }
-    if (h->p.init == FCM_INIT_RANDOM_U && h->tun.driver != FCM_DRIVER_HISTOGRAM) {
+    if (h->p.init == FCM_INIT_RANDOM_U) {
         int rc = run_random_start(h, batch);
         if (rc != FCM_OK) return rc;
         if (batch < 1 || h->h_state->done) return FCM_OK;
     }
-    if (h->tun.driver == FCM_DRIVER_HISTOGRAM) {
-        int rc = ensure_level_ws(h);
-        if (rc != FCM_OK) return rc;
-        LevelArgs la{};
-        la.counts = h->d_wcounts;  // copy 0: the totals
-        la.st = h->d_state;
-        la.hist_v = h->hist_v();
-        la.hist_d = h->hist_d();
-        la.hist_J = h->hist_J();
-        la.eps = h->p.eps;
-        la.m = h->p.m;
-        la.max_iter = h->p.max_iter;
-        la.do_init = h->pending_init ? 1 : 0;
-        la.given = start_mode(h->p.init);
-        for (int k = 0; k < kMaxC; ++k) la.v0[k] = h->given[k];
-        la.dv0 = h->dv0;
-        la.max_passes = batch;
+    if (use_levels(h)) {
+        int rc = FCM_OK;
         if (timing) {
             if ((rc = ensure_events(h, 2)) != FCM_OK) return rc;
             FCM_HIP(hipEventRecord(h->ev[0], h->stream));
         }
-        if (h->pending_init)
-            FCM_HIP(launch_histogram(h->d_x, h->d_woff, 1, h->n, h->d_wcounts, h->d_whist, h->stream));
-        FCM_HIP(launch_levels(la, h->p.n_clusters, h->stream));
-        h->pending_init = false;
+        if ((rc = enqueue_levels(h, batch)) != FCM_OK) return rc;
         if (timing) FCM_HIP(hipEventRecord(h->ev[1], h->stream));
         if ((rc = read_state(h)) != FCM_OK) return rc;
         if (timing) {
@@ -385,6 +443,7 @@ int run_batch(fcm_handle* h, int batch) {
         }
         return FCM_OK;
     }
+    h->mirrored = false;
     if (h->tun.driver == FCM_DRIVER_PERSISTENT) {
         PassArgs a = pass_args(h);
         a.max_passes = batch;
@@ -443,8 +502,28 @@ int run_batch(fcm_handle* h, int batch) {
     return FCM_OK;
 }
 
+// Workspace of the per-voxel drivers and of the random start: partial rows
+// and the exchange's tagged words (cleared: no stale tag may match).
+int ensure_voxel_ws(fcm_handle* h) {
+    if (h->d_mmrows) return FCM_OK;
+    if (!h->d_partials && hipMalloc(&h->d_partials, sizeof(float) * partial_rows(kMaxC) * kMaxGrid) != hipSuccess)
+        return FCM_ENOMEM;
+    if (!h->d_rows && hipMalloc(&h->d_rows, sizeof(uint64_t) * 2 * kMaxPersistGrid * kTaggedStrideMax) != hipSuccess)
+        return FCM_ENOMEM;
+    uint64_t* mm = nullptr;
+    if (hipMalloc(&mm, sizeof(uint64_t) * 4 * kMaxPersistGrid) != hipSuccess) return FCM_ENOMEM;
+    hipError_t e = hipMemsetAsync(h->d_rows, 0, sizeof(uint64_t) * 2 * kMaxPersistGrid * kTaggedStrideMax, h->stream);
+    if (e == hipSuccess) e = hipMemsetAsync(mm, 0, sizeof(uint64_t) * 4 * kMaxPersistGrid, h->stream);
+    if (e != hipSuccess) {
+        (void)hipFree(mm);
+        return dev_err(e, "hipMemsetAsync");
+    }
+    h->d_mmrows = mm;
+    return FCM_OK;
+}
+
 // Grey-level workspace of a handle (histogram, network output, learned
-// start), allocated on first use by the warm start or the histogram driver.
+// start), allocated on first use by a warm start outside the solve's launch.
 int ensure_level_ws(fcm_handle* h) {
     if (h->d_woff) return FCM_OK;
     if (!h->d_wcounts && hipMalloc(&h->d_wcounts, sizeof(uint32_t) * 256 * histogram_copies(1)) != hipSuccess)
@@ -471,12 +550,18 @@ int ensure_level_ws(fcm_handle* h) {
 int enqueue_start(fcm_handle* h) {
     if (h->aborted) {
         FCM_HIP(hipMemsetAsync(h->d_state, 0, sizeof(DevState), h->stream));
-        FCM_HIP(hipMemsetAsync(h->d_rows, 0, sizeof(uint64_t) * 2 * kMaxPersistGrid * kTaggedStrideMax, h->stream));
-        FCM_HIP(hipMemsetAsync(h->d_mmrows, 0, sizeof(uint64_t) * 4 * kMaxPersistGrid, h->stream));
+        FCM_HIP(hipMemsetAsync(h->d_lcounts, 0, sizeof(uint32_t) * 256 * kLvCopies, h->stream));
+        if (h->d_mmrows) {
+            FCM_HIP(hipMemsetAsync(h->d_rows, 0, sizeof(uint64_t) * 2 * kMaxPersistGrid * kTaggedStrideMax,
+                                   h->stream));
+            FCM_HIP(hipMemsetAsync(h->d_mmrows, 0, sizeof(uint64_t) * 4 * kMaxPersistGrid, h->stream));
+        }
         if (h->d_ghist) FCM_HIP(hipMemsetAsync(h->d_ghist, 0, sizeof(uint32_t) * 2 * 256 * kHistCopies, h->stream));
         h->aborted = false;
-    } else {
+        h->mirrored = false;
+    } else if (!use_levels(h)) {  // a level solve writes every result field itself
         FCM_HIP(hipMemsetAsync(h->d_state, 0, offsetof(DevState, sync), h->stream));
+        h->mirrored = false;
     }
     std::memset(h->h_state, 0, sizeof(DevState));
     h->h_state->iters = -1;
@@ -498,12 +583,10 @@ void release(fcm_handle* h) {
     drop_graph(h);
     if (h->cap) (void)hipStreamDestroy(h->cap);
     for (hipEvent_t e : h->ev) (void)hipEventDestroy(e);
-    if (h->d_state) (void)hipFree(h->d_state);
+    if (h->d_arena) (void)hipFree(h->d_arena);
     if (h->d_partials) (void)hipFree(h->d_partials);
-    if (h->d_minmax) (void)hipFree(h->d_minmax);
     if (h->d_rows) (void)hipFree(h->d_rows);
     if (h->d_mmrows) (void)hipFree(h->d_mmrows);
-    if (h->d_hist) (void)hipFree(h->d_hist);
     for (void* p : {(void*)h->d_woff, (void*)h->d_wcounts, (void*)h->d_whist, (void*)h->d_wy, (void*)h->d_wv0,
                     (void*)h->d_ghist})
         if (p) (void)hipFree(p);
@@ -580,16 +663,21 @@ int fcm_init(fcm_handle** out, const uint8_t* d_x, int64_t n, const fcm_params* 
     h->tun.launch = FCM_LAUNCH_RESIDENT;
     if ((rc = resolve_grid(h, &h->grid)) != FCM_OK) return fail(rc);
 
-    if (hipMalloc(&h->d_state, sizeof(DevState)) != hipSuccess) return fail(FCM_ENOMEM);
-    if (hipMalloc(&h->d_partials, sizeof(float) * partial_rows(kMaxC) * kMaxGrid) != hipSuccess)
-        return fail(FCM_ENOMEM);
-    if (hipMalloc(&h->d_minmax, sizeof(uint32_t) * 2 * kMaxGrid) != hipSuccess) return fail(FCM_ENOMEM);
-    if (hipMalloc(&h->d_rows, sizeof(uint64_t) * 2 * kMaxPersistGrid * kTaggedStrideMax) != hipSuccess)
-        return fail(FCM_ENOMEM);
-    if (hipMalloc(&h->d_mmrows, sizeof(uint64_t) * 4 * kMaxPersistGrid) != hipSuccess) return fail(FCM_ENOMEM);
+    // one allocation for what every solve uses
+    auto up = [](size_t b) { return (b + 255) / 256 * 256; };
+    const size_t b_state = up(sizeof(DevState)), b_cnt = up(sizeof(uint32_t) * 256 * kLvCopies);
+    const size_t b_mm = up(sizeof(uint32_t) * 2 * kMaxGrid);
     const size_t hist_doubles = (size_t)(p->max_iter + 2) * (C + 2);
-    if (hipMalloc(&h->d_hist, sizeof(double) * hist_doubles) != hipSuccess) return fail(FCM_ENOMEM);
-    if (hipHostMalloc(&h->h_state, sizeof(DevState), hipHostMallocDefault) != hipSuccess) return fail(FCM_ENOMEM);
+    if (hipMalloc(&h->d_arena, b_state + b_cnt + b_mm + sizeof(double) * hist_doubles) != hipSuccess)
+        return fail(FCM_ENOMEM);
+    char* at = static_cast<char*>(h->d_arena);
+    h->d_state = reinterpret_cast<DevState*>(at);
+    h->d_lcounts = reinterpret_cast<uint32_t*>(at + b_state);
+    h->d_minmax = reinterpret_cast<uint32_t*>(at + b_state + b_cnt);
+    h->d_hist = reinterpret_cast<double*>(at + b_state + b_cnt + b_mm);
+    if (hipHostMalloc(&h->h_state, 2 * sizeof(DevState), hipHostMallocDefault) != hipSuccess) return fail(FCM_ENOMEM);
+    std::memset(h->h_state, 0, 2 * sizeof(DevState));
+    if ((!use_levels(h) || p->init == FCM_INIT_RANDOM_U) && (rc = ensure_voxel_ws(h)) != FCM_OK) return fail(rc);
     h->aborted = true;  // first start clears the handshake and the flags too
     rc = enqueue_start(h);
     if (rc != FCM_OK) return fail(rc);
@@ -610,6 +698,7 @@ int fcm_set_tuning(fcm_handle* h, const fcm_tuning* t) {
     if (t->driver == FCM_DRIVER_PERSISTENT && !h->coop) return FCM_EUNSUPPORTED;
     if (t->driver == FCM_DRIVER_HISTOGRAM && h->p.init == FCM_INIT_RANDOM_U) return FCM_EINVAL;
     if (t->exchange == FCM_EXCHANGE_XCD && (h->p.flags & FCM_F_KAHAN_ONLY)) return FCM_EUNSUPPORTED;
+    if (!level_tuning(h, *t) && (rc = ensure_voxel_ws(h)) != FCM_OK) return rc;
     const fcm_tuning old = h->tun;
     h->tun = *t;
     int grid = 1;
@@ -695,7 +784,7 @@ int fcm_solve(fcm_handle* h, fcm_result* out) {
 
 int fcm_solve_async(fcm_handle* h, uint8_t* d_labels) {
     if (!h) return FCM_EINVAL;
-    if (h->tun.driver != FCM_DRIVER_PERSISTENT || h->p.init == FCM_INIT_RANDOM_U) {
+    if ((h->tun.driver != FCM_DRIVER_PERSISTENT && !use_levels(h)) || h->p.init == FCM_INIT_RANDOM_U) {
         // host-driven solves: the synchronous path
         fcm_result r;
         int rc = fold_async(h);
@@ -720,20 +809,28 @@ int fcm_solve_async(fcm_handle* h, uint8_t* d_labels) {
         h->kernel_ms = 0.0;
         h->pending_init = true;
     }
-    PassArgs a = pass_args(h);
-    a.max_passes = h->p.max_iter + 1;  // always enough: the launch ends the solve
-    a.labels = d_labels;
-    a.labels_bytewise = (((uintptr_t)h->d_x ^ (uintptr_t)d_labels) & 15) ? 1 : 0;
     const bool timing = (h->p.flags & FCM_F_TIMING) != 0;
     if (timing) {
         int rc = ensure_events(h, 2 * (h->async_timed + 1));
         if (rc != FCM_OK) return rc;
         FCM_HIP(hipEventRecord(h->ev[2 * h->async_timed], h->stream));
     }
-    hipError_t e = launch_persist(a, h->p.n_clusters, h->mclass, h->tun.unroll, h->grid,
-                                  h->tun.launch == FCM_LAUNCH_COOPERATIVE, h->stream);
-    if (e != hipSuccess) return dev_err(e, "persistent launch");
-    h->pending_init = false;
+    // max_iter + 1 passes are always enough: the launch ends the solve
+    if (use_levels(h)) {
+        int rc = enqueue_levels(h, h->p.max_iter + 1);
+        if (rc == FCM_OK && d_labels) rc = fcm_labels(h, d_labels);
+        if (rc != FCM_OK) return rc;
+    } else {
+        PassArgs a = pass_args(h);
+        a.max_passes = h->p.max_iter + 1;
+        a.labels = d_labels;
+        a.labels_bytewise = (((uintptr_t)h->d_x ^ (uintptr_t)d_labels) & 15) ? 1 : 0;
+        h->mirrored = false;
+        hipError_t e = launch_persist(a, h->p.n_clusters, h->mclass, h->tun.unroll, h->grid,
+                                      h->tun.launch == FCM_LAUNCH_COOPERATIVE, h->stream);
+        if (e != hipSuccess) return dev_err(e, "persistent launch");
+        h->pending_init = false;
+    }
     if (timing) {
         FCM_HIP(hipEventRecord(h->ev[2 * h->async_timed + 1], h->stream));
         ++h->async_timed;
@@ -757,8 +854,7 @@ int fcm_solve_wait(fcm_handle* h, fcm_result* out, int64_t* total_passes) {
 int fcm_solve_warm(fcm_handle* h, fcm_mlp* net, int32_t check, fcm_result* out, fcm_result* plain, int32_t* used) {
     if (!h || !net || !out) return FCM_EINVAL;
     if (mlp_clusters(net) != h->p.n_clusters) return FCM_EINVAL;
-    int rc = ensure_level_ws(h);
-    if (rc != FCM_OK) return rc;
+    int rc = FCM_OK;
     fcm_result rp{}, rw{};
     if (check) {  // the plain solve from the handle's own start
         if ((rc = enqueue_start(h)) != FCM_OK) return rc;
@@ -771,8 +867,9 @@ int fcm_solve_warm(fcm_handle* h, fcm_mlp* net, int32_t check, fcm_result* out, 
     // ways run the same device code and give the same start.
     const int32_t own_init = h->p.init;
     const double* own_dv0 = h->dv0;
-    if (h->tun.driver == FCM_DRIVER_PERSISTENT) {
-        if (!h->d_ghist) {
+    const bool levels = use_levels(h);
+    if (levels || h->tun.driver == FCM_DRIVER_PERSISTENT) {
+        if (!levels && !h->d_ghist) {
             if (hipMalloc(&h->d_ghist, sizeof(uint32_t) * 2 * 256 * kHistCopies) != hipSuccess) return FCM_ENOMEM;
             FCM_HIP(hipMemsetAsync(h->d_ghist, 0, sizeof(uint32_t) * 2 * 256 * kHistCopies, h->stream));
         }
@@ -780,6 +877,7 @@ int fcm_solve_warm(fcm_handle* h, fcm_mlp* net, int32_t check, fcm_result* out, 
         if (rc != FCM_OK) return rc;
         h->p.init = kInitLearnedFused;
     } else {
+        if ((rc = ensure_level_ws(h)) != FCM_OK) return rc;
         FCM_HIP(launch_histogram(h->d_x, h->d_woff, 1, h->n, h->d_wcounts, h->d_whist, h->stream));
         if ((rc = mlp_warm(net, h->d_whist, 1, h->d_wy, h->d_wv0, h->stream)) != FCM_OK) return rc;
         h->p.init = FCM_INIT_DEVICE;
@@ -789,7 +887,7 @@ int fcm_solve_warm(fcm_handle* h, fcm_mlp* net, int32_t check, fcm_result* out, 
     if (rc == FCM_OK) rc = fcm_solve(h, &rw);
     // a launch that ran to its end (converged, out of iterations or non-finite)
     // zeroed the other counter buffer: the next learned launch uses that one
-    if (h->p.init == kInitLearnedFused && (rc >= 0 || rc == FCM_ENUMERIC)) h->ghist_sel ^= 1u;
+    if (!levels && h->p.init == kInitLearnedFused && (rc >= 0 || rc == FCM_ENUMERIC)) h->ghist_sel ^= 1u;
     h->p.init = own_init;
     h->dv0 = own_dv0;
     h->mlp_w = nullptr;
@@ -1348,6 +1446,7 @@ int handle_shape(const fcm_handle* h, HandleShape* s) {
     s->device = h->device;
     s->ncu = h->ncu;
     s->coop = h->coop;
+    s->grid_asked = h->tun.grid;
     return FCM_OK;
 }
 

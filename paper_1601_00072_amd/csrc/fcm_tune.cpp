@@ -169,6 +169,9 @@ int fcm_autotune(fcm_handle* h, const char* cache_path, int32_t reps, fcm_tuning
         << " nlog2=" << log2_floor(s.n);
     fcm_tuning entry{};
     if ((rc = fcm_get_tuning(h, &entry)) != FCM_OK) return rc;
+    // as set, not as resolved: with grid 0 and the automatic exchange the
+    // library solves over the grey levels, and that stays a candidate
+    entry.grid = s.grid_asked;
     Choice c{};
     if (load_choice(cache_path, key.str(), 6, &c)) {
         fcm_tuning t = entry;
@@ -234,6 +237,7 @@ int fcm_autotune(fcm_handle* h, const char* cache_path, int32_t reps, fcm_tuning
         fcm_tuning got{};
         (void)fcm_get_tuning(h, &got);
         if (t.driver == FCM_DRIVER_PERSISTENT && got.grid != t.grid) continue;  // capped: a duplicate
+        got.grid = t.grid;
         if (fcm_reset(h) != FCM_OK) continue;
         rc = fcm_solve(h, &r);  // parity check of this configuration, once
         if ((rc < 0 && rc != FCM_ENUMERIC) || !agrees(r, ref)) continue;
@@ -247,7 +251,7 @@ int fcm_autotune(fcm_handle* h, const char* cache_path, int32_t reps, fcm_tuning
     fcm_tuning fin{};
     (void)fcm_get_tuning(h, &fin);
     c.v[0] = fin.driver;
-    c.v[1] = fin.grid;
+    c.v[1] = best.grid;
     c.v[2] = fin.unroll;
     c.v[3] = fin.exchange;
     c.v[4] = fin.launch;
