@@ -239,6 +239,9 @@ void fcm_destroy(fcm_handle* h);
  * m, eps, max_iter, init and flags) solved together in one persistent launch:
  * every instance follows Algorithm 1 exactly as fcm_solve would, and the
  * launch ends when every instance has converged or run out of iterations.
+ * Until a block size or a tiling is set, the launch solves over the grey
+ * levels (as FCM_DRIVER_HISTOGRAM; instances below 2^32 voxels); with either
+ * set, it runs every pass over the voxels, in tiles.
  * Instance i is d_x[offsets[i] .. offsets[i+1]) of one concatenated uint8
  * device buffer (borrowed); offsets (count + 1 values, host) must start at 0,
  * be non-decreasing with every instance non-empty.  params: count host
@@ -326,7 +329,9 @@ int fcm_autotune(fcm_handle* h, const char* cache_path, int32_t reps, fcm_tuning
  * or 16 chunks per thread, on the largest grid the device holds and on half
  * of it (the tail tiling stays as set).  Key: instance count, largest C and
  * floor(log2 of the total voxels).  The chosen block size and tiling are
- * applied (fcm_batch_set_block, fcm_batch_set_tiling); outputs may be NULL. */
+ * applied (fcm_batch_set_block, fcm_batch_set_tiling) unless the batch solved
+ * over the grey levels at entry and that was faster (it then goes on doing so);
+ * outputs may be NULL. */
 int fcm_batch_autotune(fcm_batch* b, const char* cache_path, int32_t reps, int32_t* block,
                        int32_t* chunks_per_thread, int32_t* grid, double* ms);
 

@@ -21,9 +21,13 @@ struct HandleShape {
 struct BatchShape {
     int64_t voxels;     // all instances
     int count, max_C, device, max_grid, chunks_per_thread, grid, block;
+    int tiled;          // the caller chose tiles (per-voxel passes)
 };
 int handle_shape(const fcm_handle* h, HandleShape* s);
 int batch_shape(const fcm_batch* b, BatchShape* s);
+
+// Leave the launch of a batch to the library again (solves over the grey levels).
+void batch_untile(fcm_batch* b);
 
 // Text returned by fcm_last_error (per thread).
 std::string& last_error();

@@ -33,6 +33,23 @@ struct LevelArgs {
     const double* dv0;
     const uint16_t* mlp_w;
 };
+
+// Batched level solve: one block per tile of an instance.
+struct LevelBatchArgs {
+    const uint8_t* x;
+    const BatchInst* inst;
+    const BatchTile* tiles;  // in launch order
+    const int32_t* ntiles;   // [I] tiles of the instance
+    const double* m;         // [I] fuzziness
+    uint32_t* counts;        // [I][256] counters, zero at entry and at the end of every launch
+    uint32_t* ticket;        // [I] tiles counted, zero at entry and at the end of every launch
+    BatchRec* recs;
+    BatchRec* host_recs;     // pinned: the same records, for the host to read after a wait
+    uint64_t* host_start;    // pinned: wall clock at the start of the launch
+    double* hist;
+};
+hipError_t launch_levels_batch(const LevelBatchArgs& a, int grid, hipStream_t s);
+
 hipError_t launch_levels(const LevelArgs& a, int C, int mclass, int grid, hipStream_t s);
 
 }  // namespace fcm

@@ -1011,6 +1011,16 @@ struct fcm_batch {
     BatchSync* h_sync = nullptr;
     uint64_t* h_ctl = nullptr;
 
+    // solve over the grey levels (until the caller sets a block size or a tiling)
+    bool tiled = false;            // the caller's tiles: per-voxel passes
+    int32_t level_tiles = 0;
+    void* d_level = nullptr;       // one allocation: counters, m, tiles, tile counts, tickets
+    uint32_t* d_lcounts = nullptr; // [count][256]
+    double* d_lm = nullptr;        // [count]
+    BatchTile* d_ltiles = nullptr;
+    int32_t* d_lntiles = nullptr;  // [count]
+    uint32_t* d_ltickets = nullptr; // [count]
+
     // learned starts (first fcm_batch_set_start with a network)
     int64_t* d_off = nullptr;      // offsets [count + 1]
     uint32_t* d_counts = nullptr;  // [count][256]
@@ -1034,7 +1044,7 @@ void batch_release(fcm_batch* b) {
     batch_free_tiles(b);
     for (void* p : {(void*)b->d_inst, (void*)b->d_ntiles, (void*)b->d_recs, (void*)b->d_hist, (void*)b->d_dec,
                     (void*)b->d_ctl, (void*)b->d_sync, (void*)b->d_off, (void*)b->d_counts, (void*)b->d_whist,
-                    (void*)b->d_wy, (void*)b->d_wv0})
+                    (void*)b->d_wy, (void*)b->d_wv0, b->d_level})
         if (p) (void)hipFree(p);
     if (b->h_recs) (void)hipHostFree(b->h_recs);
     if (b->h_sync) (void)hipHostFree(b->h_sync);
@@ -1098,6 +1108,113 @@ int batch_build_tiles(fcm_batch* b) {
     b->grid = (int)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(want, b->max_grid), most));
     b->round = 0;  // buffers were cleared: tags restart
     return FCM_OK;
+}
+
+// Tiles and workspace of the level solve.  A tile is one block's share of an
+// instance: enough tiles to give every CU two, between 16,384 voxels (below
+// that a block's fixed cost, clearing and adding its counters, outweighs the
+// count) and 131,072.  Instances with more clusters come first, then larger
+// ones: they take most passes, and the launch ends with the longest chain.
+constexpr int64_t kLevelTileMin = 16384, kLevelTileMax = 131072;
+
+int batch_build_levels(fcm_batch* b) {
+    const size_t cnt = (size_t)b->count;
+    for (const BatchInst& in : b->h_inst)
+        if (in.n > (int64_t)UINT32_MAX) {  // beyond the 32-bit counters
+            b->tiled = true;
+            return FCM_OK;
+        }
+    const int64_t share = b->offsets.back() / (2 * (int64_t)b->ncu);
+    const int64_t chunks = std::min(kLevelTileMax, std::max(kLevelTileMin, share)) / 16;
+    std::vector<int32_t> order(cnt), nt(cnt);
+    for (size_t i = 0; i < cnt; ++i) order[i] = (int32_t)i;
+    std::stable_sort(order.begin(), order.end(), [&](int32_t p, int32_t q) {
+        const BatchInst &x = b->h_inst[(size_t)p], &y = b->h_inst[(size_t)q];
+        return x.C != y.C ? x.C > y.C : x.n > y.n;
+    });
+    std::vector<BatchTile> tiles;
+    for (int32_t i : order) {
+        const BatchInst& in = b->h_inst[(size_t)i];
+        int64_t c0 = 0;
+        do {
+            BatchTile t{};
+            t.c0 = c0;
+            t.c1 = std::min<int64_t>(in.nbody, c0 + chunks);
+            t.inst = i;
+            t.ragged = c0 == 0 ? 1 : 0;
+            tiles.push_back(t);
+            ++nt[(size_t)i];
+            c0 = t.c1;
+        } while (c0 < in.nbody);
+    }
+    if (tiles.size() > (size_t)INT32_MAX) {
+        b->tiled = true;
+        return FCM_OK;
+    }
+    std::vector<double> m(cnt);
+    for (size_t i = 0; i < cnt; ++i) m[i] = b->p[i].m;
+    auto up = [](size_t v) { return (v + 255) / 256 * 256; };
+    const size_t o_m = up(sizeof(uint32_t) * 256 * cnt), o_tiles = o_m + up(sizeof(double) * cnt);
+    const size_t o_nt = o_tiles + up(sizeof(BatchTile) * tiles.size()), o_tk = o_nt + up(sizeof(int32_t) * cnt);
+    if (hipMalloc(&b->d_level, o_tk + sizeof(uint32_t) * cnt) != hipSuccess) return FCM_ENOMEM;
+    char* at = static_cast<char*>(b->d_level);
+    b->d_lcounts = reinterpret_cast<uint32_t*>(at);
+    b->d_lm = reinterpret_cast<double*>(at + o_m);
+    b->d_ltiles = reinterpret_cast<BatchTile*>(at + o_tiles);
+    b->d_lntiles = reinterpret_cast<int32_t*>(at + o_nt);
+    b->d_ltickets = reinterpret_cast<uint32_t*>(at + o_tk);
+    b->level_tiles = (int32_t)tiles.size();
+    FCM_HIP(hipMemsetAsync(b->d_lcounts, 0, sizeof(uint32_t) * 256 * cnt, b->stream));
+    FCM_HIP(hipMemsetAsync(b->d_ltickets, 0, sizeof(uint32_t) * cnt, b->stream));
+    FCM_HIP(hipMemcpyAsync(b->d_lm, m.data(), sizeof(double) * cnt, hipMemcpyHostToDevice, b->stream));
+    FCM_HIP(hipMemcpyAsync(b->d_ltiles, tiles.data(), sizeof(BatchTile) * tiles.size(), hipMemcpyHostToDevice,
+                           b->stream));
+    FCM_HIP(hipMemcpyAsync(b->d_lntiles, nt.data(), sizeof(int32_t) * cnt, hipMemcpyHostToDevice, b->stream));
+    FCM_HIP(hipStreamSynchronize(b->stream));  // the host tables end here
+    return FCM_OK;
+}
+
+// Results of a solve, from the records in host memory.
+int batch_results(const fcm_batch* b, fcm_result* out) {
+    int worst = FCM_OK;
+    for (int32_t i = 0; i < b->count; ++i) {
+        const BatchRec& r = b->h_recs[i];
+        fcm_result& o = out[i];
+        std::memset(&o, 0, sizeof(o));
+        o.iters = r.iters < 0 ? 0 : r.iters;
+        o.passes = r.passes;
+        o.status = r.status;
+        o.n_clusters = b->p[i].n_clusters;
+        o.delta = r.delta;
+        o.J = r.J;
+        for (int k = 0; k < o.n_clusters; ++k) o.centroids[k] = r.vres[k];
+        o.lo = r.lo;
+        o.hi = r.hi;
+        if (r.status == FCM_ENUMERIC) worst = FCM_ENUMERIC;
+        else if (r.status != FCM_OK && worst == FCM_OK) worst = r.status;
+    }
+    return worst;
+}
+
+// One launch over the grey levels; every block ends by itself.
+int batch_solve_levels(fcm_batch* b, fcm_result* out) {
+    LevelBatchArgs a{};
+    a.x = b->d_x;
+    a.inst = b->d_inst;
+    a.tiles = b->d_ltiles;
+    a.ntiles = b->d_lntiles;
+    a.m = b->d_lm;
+    a.counts = b->d_lcounts;
+    a.ticket = b->d_ltickets;
+    a.recs = b->d_recs;
+    a.host_recs = b->h_recs;
+    a.host_start = &b->h_sync->t_start;
+    a.hist = b->d_hist;
+    hipError_t e = launch_levels_batch(a, b->level_tiles, b->stream);
+    if (e != hipSuccess) return dev_err(e, "launch_levels_batch");
+    FCM_HIP(hipStreamSynchronize(b->stream));
+    b->solved = true;
+    return batch_results(b, out);
 }
 
 }  // namespace
@@ -1183,6 +1300,7 @@ int fcm_batch_init(fcm_batch** out, const uint8_t* d_x, const int64_t* offsets, 
     if ((e = hipMemsetAsync(b->d_recs, 0, sizeof(BatchRec) * count, b->stream)) != hipSuccess)
         return fail(dev_err(e, "hipMemsetAsync"));
     int rc = batch_build_tiles(b);
+    if (rc == FCM_OK) rc = batch_build_levels(b);
     if (rc != FCM_OK) return fail(rc);
     *out = b;
     return FCM_OK;
@@ -1191,6 +1309,7 @@ int fcm_batch_init(fcm_batch** out, const uint8_t* d_x, const int64_t* offsets, 
 int fcm_batch_set_tiling(fcm_batch* b, int32_t chunks_per_thread, int32_t grid) {
     if (!b || chunks_per_thread < 1 || chunks_per_thread > 64 || grid < 0 || grid > kMaxPersistGrid)
         return FCM_EINVAL;
+    b->tiled = true;
     b->chunks_per_thread = chunks_per_thread;
     b->grid_req = grid;
     b->solved = false;
@@ -1202,6 +1321,7 @@ int fcm_batch_set_block(fcm_batch* b, int32_t threads) {
     int max_grid = 0;
     hipError_t e = batch_max_grid(threads, b->ncu, &max_grid);
     if (e != hipSuccess) return dev_err(e, "occupancy");
+    b->tiled = true;
     b->block = threads;
     b->max_grid = std::max(1, std::min(max_grid, kMaxPersistGrid));
     b->solved = false;
@@ -1210,6 +1330,7 @@ int fcm_batch_set_block(fcm_batch* b, int32_t threads) {
 
 int fcm_batch_set_tail_tiling(fcm_batch* b, int32_t from_pass, int32_t chunks_per_thread) {
     if (!b || from_pass < 0 || chunks_per_thread < 1 || chunks_per_thread > 64) return FCM_EINVAL;
+    b->tiled = true;
     b->fine_from = from_pass;
     b->fine_chunks = chunks_per_thread;
     b->solved = false;
@@ -1258,6 +1379,7 @@ int fcm_batch_set_start(fcm_batch* b, fcm_mlp* net, const uint8_t* use_learned) 
 
 int fcm_batch_solve(fcm_batch* b, fcm_result* out) {
     if (!b || !out) return FCM_EINVAL;
+    if (!b->tiled) return batch_solve_levels(b, out);
     int max_iter = 1;
     for (const fcm_params& q : b->p) max_iter = std::max(max_iter, q.max_iter);
     // tags of this launch: round0 + 1 + phase, phases 0 .. max_iter + 1, and
@@ -1306,24 +1428,7 @@ int fcm_batch_solve(fcm_batch* b, fcm_result* out) {
     }
     b->round = round0 + (uint32_t)max_iter + 3u;
     b->solved = true;
-    int worst = FCM_OK;
-    for (int32_t i = 0; i < b->count; ++i) {
-        const BatchRec& r = b->h_recs[i];
-        fcm_result& o = out[i];
-        std::memset(&o, 0, sizeof(o));
-        o.iters = r.iters < 0 ? 0 : r.iters;
-        o.passes = r.passes;
-        o.status = r.status;
-        o.n_clusters = b->p[i].n_clusters;
-        o.delta = r.delta;
-        o.J = r.J;
-        for (int k = 0; k < o.n_clusters; ++k) o.centroids[k] = r.vres[k];
-        o.lo = r.lo;
-        o.hi = r.hi;
-        if (r.status == FCM_ENUMERIC) worst = FCM_ENUMERIC;
-        else if (r.status != FCM_OK && worst == FCM_OK) worst = r.status;
-    }
-    return worst;
+    return batch_results(b, out);
 }
 
 int fcm_batch_timeline(fcm_batch* b, int32_t inst, double* us, int32_t cap, int32_t* count) {
@@ -1461,7 +1566,14 @@ int batch_shape(const fcm_batch* b, BatchShape* s) {
     s->chunks_per_thread = b->chunks_per_thread;
     s->grid = b->grid_req;
     s->block = b->block;
+    s->tiled = b->tiled ? 1 : 0;
     return FCM_OK;
+}
+
+void batch_untile(fcm_batch* b) {
+    for (const BatchInst& in : b->h_inst)
+        if (in.n > (int64_t)UINT32_MAX) return;
+    b->tiled = b->d_level == nullptr;
 }
 
 }  // namespace fcm

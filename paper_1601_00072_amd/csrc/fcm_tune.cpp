@@ -287,9 +287,17 @@ int fcm_batch_autotune(fcm_batch* b, const char* cache_path, int32_t reps, int32
         if (ms) *ms = t_ms;
     };
     Choice c{};
-    if (load_choice(cache_path, key.str(), 3, &c) && apply(c.v[0], c.v[1], c.v[2]) == FCM_OK) {
-        report(c.v[0], c.v[1], c.v[2], c.ms);
-        return FCM_OK;
+    const int untiled = !s.tiled;  // at entry the library solves over the grey levels
+    if (load_choice(cache_path, key.str(), 3, &c)) {
+        if (c.v[1] == 0) {  // that was the fastest
+            batch_untile(b);
+            report(s.block, s.chunks_per_thread, s.grid, c.ms);
+            return FCM_OK;
+        }
+        if (apply(c.v[0], c.v[1], c.v[2]) == FCM_OK) {
+            report(c.v[0], c.v[1], c.v[2], c.ms);
+            return FCM_OK;
+        }
     }
     std::vector<fcm_result> ref((size_t)s.count), r((size_t)s.count);
     rc = fcm_batch_solve(b, ref.data());
@@ -298,6 +306,7 @@ int fcm_batch_autotune(fcm_batch* b, const char* cache_path, int32_t reps, int32
     int best_bs = e_bs, best_cpt = e_cpt, best_grid = e_grid;
     double best_ms = time_batch(b, reps, r);
     if (best_ms < 0) return FCM_EDEVICE;
+    const double entry_ms = best_ms;
     for (int bs : {512, 256, 128}) {
         for (int cpt : {1, 2, 3, 4, 5, 6, 8, 12, 16}) {
             for (int half : {0, 1}) {
@@ -305,7 +314,7 @@ int fcm_batch_autotune(fcm_batch* b, const char* cache_path, int32_t reps, int32
                 BatchShape cur{};
                 if (batch_shape(b, &cur) != FCM_OK) continue;
                 const int g = half ? std::max(1, cur.max_grid / 2) : 0;
-                if (bs == e_bs && cpt == e_cpt && g == e_grid) continue;  // timed above
+                if (!untiled && bs == e_bs && cpt == e_cpt && g == e_grid) continue;  // timed above
                 if (g && fcm_batch_set_tiling(b, cpt, g) != FCM_OK) continue;
                 rc = fcm_batch_solve(b, r.data());
                 if (rc < 0 && rc != FCM_ENUMERIC) continue;
@@ -323,8 +332,10 @@ int fcm_batch_autotune(fcm_batch* b, const char* cache_path, int32_t reps, int32
         }
     }
     if ((rc = apply(best_bs, best_cpt, best_grid)) != FCM_OK) return rc;
+    const bool keep = untiled && best_ms == entry_ms;
+    if (keep) batch_untile(b);
     c.v[0] = best_bs;
-    c.v[1] = best_cpt;
+    c.v[1] = keep ? 0 : best_cpt;
     c.v[2] = best_grid;
     c.ms = best_ms;
     store_choice(cache_path, key.str(), 3, c);

@@ -109,3 +109,47 @@ def test_autotune_keeps_the_library_choice(dev):
         r = f.solve()
         ora = fcm_hist.solve(fcm_hist.histogram(x), 4, 2.0, 1e-5, 300)
         assert r.status == 0 and np.max(np.abs(r.centroids - ora.v[ora.T])) <= 1e-3
+
+
+def test_batch_tiles(dev):
+    """Instances of one tile, of exactly one, and of many, aligned and not, all
+    cluster counts and fuzziness classes, one launch; repeated, then with the
+    caller's tiles (per-voxel passes) and back to the same bits."""
+    import torch
+    from paper_1601_00072_amd import FCMBatch
+    print("CASE level batch", flush=True)
+    sizes = [1, 17, 4096, SHARE - 1, SHARE, SHARE + 1, 2 * SHARE + 31, 9 * SHARE + 5, 300001, 3 * SHARE]
+    items = []
+    for i, n in enumerate(sizes):
+        p = dict(n_clusters=2 + i % 7, m=[2.0, 1.5, 2.5][i % 3], eps=1e-5)
+        if i == 6:
+            p["init"] = [10.0 + 20.0 * k for k in range(p["n_clusters"])]
+        items.append((data(n, seed=20 + i), p))
+    flat = np.concatenate([x for x, _ in items])
+    params = [p for _, p in items]
+    x = place(dev, flat, 3)
+    with FCMBatch(x, sizes, params) as b:
+        for turn in range(2):
+            res = b.solve()
+            lab = b.labels().cpu().numpy()
+            start = 0
+            for i, ((xi, p), r) in enumerate(zip(items, res)):
+                if np.unique(xi).size > p["n_clusters"]:
+                    traj = [b.trajectory(i, t) for t in range(r.iters + 1)]
+                    check(xi, p["n_clusters"], r, traj, lab[start:start + xi.size], m=p["m"], init=p.get("init"))
+                us = b.timeline(i)
+                assert us.shape == (r.passes + 1,) and us[0] >= 0.0 and np.all(np.diff(us) >= 0.0)
+                start += xi.size
+            if turn:
+                for r, q in zip(res, first):
+                    assert r.iters == q.iters and r.J == q.J and np.array_equal(r.centroids, q.centroids)
+            first = res
+        b.set_tiling(4, 0)
+        tiled = b.solve()
+    with FCMBatch(x, sizes, params) as b:
+        b.set_tiling(4, 0)
+        again = b.solve()
+    for r, q, t in zip(tiled, again, first):
+        assert r.iters == q.iters and np.array_equal(r.centroids, q.centroids)
+        if r.iters == t.iters and r.status == 0:
+            assert np.max(np.abs(r.centroids - t.centroids)) <= 1e-2
