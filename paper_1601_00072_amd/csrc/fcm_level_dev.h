@@ -143,34 +143,75 @@ struct LevelOutcome {
     double delta, J;
 };
 
-// Shared memory of level_iterate (lies over the counting table).  The weights
-// u^m h of a wave's 64 levels pass from "lane = level" to "lane = (cluster,
-// part of the levels)" through `w`; the row stride keeps both directions free
-// of bank conflicts.
-template <int C>
-struct LevelGeom {
-    static constexpr int CP = C <= 2 ? 2 : (C <= 4 ? 4 : 8);  // clusters rounded up
-    static constexpr int PARTS = CP == 8 ? 8 : 16;            // lanes that share a cluster's levels
-    static constexpr int PER = 64 / PARTS;                    // levels per such lane
-    static constexpr int STRIDE = CP == 8 ? 72 : 80;
-};
+// Shared memory of level_iterate (lies over the counting table).
+constexpr int kLvRetry = 1, kLvEnd = 2, kLvStatusShift = 8, kLvStatus0 = 64;
+constexpr int kExpSteps = 32, kLogSteps = 64;
 
 struct LevelScratch {
-    double w[4][8 * 80];
-    double red[2][8][3][4];   // [pass parity][cluster][num, den, J][wave]
-    double dmax[2][4];
+    double red[2][8][2][4];   // [attempt parity][cluster][num, den][wave]
+    int flag[2][4];           // wave: a level changed by eps or more
+    // of an attempt, for the recording wave, which is one barrier behind
+    double dm[3][256];        // largest membership change of a level
+    double jt[3][256];        // its term of Eq.1
+    double vnext[3][8];
+    int dec[3];               // kLvRetry, or status + kLvStatus0 and kLvEnd
     double v[8], vp[8];
+    double ex[kExpSteps];     // 2^(j / kExpSteps)
+    double lg[kLogSteps][2];  // 1 / f_j and log2 f_j, f_j = 1 + (j + 1/2) / kLogSteps
     uint64_t mask[4];
     float h[256], a0[256], a1[128], a2[64], tmp[256], y[8];
     double w0[8];
 };
 static_assert(sizeof(LevelScratch) <= sizeof(LevelTable), "scratch lies over the counting table");
 
+// Block barrier that orders shared memory only: __syncthreads also waits for
+// the wave's global stores, and the recording wave stores a row of the
+// history in every pass (0.5 us each time).
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 __device__ __forceinline__ double readfirst_d(double v) { return readlane_d(v, 0); }
 
-template <int CTRL>
-__device__ __forceinline__ double dpp_add_f64(double v) {
-    return v + dpp_mov_f64<CTRL>(v);
+// (a, b) -> the sums of a over lanes l and l + 32 in the lower half of the
+// wave, of b in the upper half: the instruction swaps a's upper half with b's
+// lower half.
+__device__ __forceinline__ double swap32_add(double a, double b) {
+    const uint64_t x = __builtin_bit_cast(uint64_t, a), y = __builtin_bit_cast(uint64_t, b);
+    const auto l = __builtin_amdgcn_permlane32_swap((uint32_t)x, (uint32_t)y, false, false);
+    const auto h = __builtin_amdgcn_permlane32_swap((uint32_t)(x >> 32), (uint32_t)(y >> 32), false, false);
+    return __builtin_bit_cast(double, ((uint64_t)h[0] << 32) | l[0]) +
+           __builtin_bit_cast(double, ((uint64_t)h[1] << 32) | l[1]);
+}
+
+// The same between rows of 16: a's rows 1 and 3 change places with b's rows 0
+// and 2, so a's row pairs end in rows 0 and 2, b's in rows 1 and 3.
+__device__ __forceinline__ double swap16_add(double a, double b) {
+    const uint64_t x = __builtin_bit_cast(uint64_t, a), y = __builtin_bit_cast(uint64_t, b);
+    const auto l = __builtin_amdgcn_permlane16_swap((uint32_t)x, (uint32_t)y, false, false);
+    const auto h = __builtin_amdgcn_permlane16_swap((uint32_t)(x >> 32), (uint32_t)(y >> 32), false, false);
+    return __builtin_bit_cast(double, ((uint64_t)h[0] << 32) | l[0]) +
+           __builtin_bit_cast(double, ((uint64_t)h[1] << 32) | l[1]);
+}
+
+// Sum over the lane's row of 16, in every lane of the row.
+__device__ __forceinline__ double row_sum_f64(double v) {
+    v += dpp_mov_f64<0xB1>(v);
+    v += dpp_mov_f64<0x4E>(v);
+    v += dpp_mov_f64<0x141>(v);
+    v += dpp_mov_f64<0x140>(v);
+    return v;
+}
+
+// Sums of four values over the wave, value r in row r: each swap folds two
+// values into one register, 21 instructions for four sums in a chain of six
+// adds (one value at a time with moves and adds: 72 in the same chain).  Sums
+// by the 4x4x4 FP64 matrix instruction need fewer instructions still but wait
+// for each other's results: the same time per pass within 5 %.
+__device__ __forceinline__ double quad_sum_f64(double v0, double v1, double v2, double v3) {
+    return row_sum_f64(swap16_add(swap32_add(v0, v2), swap32_add(v1, v3)));
 }
 
 // max over the wave of non-negative values, valid in lane 63 (row butterflies,
@@ -193,11 +234,48 @@ __device__ __forceinline__ double recip_f64(double s) {
     return r;
 }
 
+// log2 of a positive normal number: exponent + log2 f_j + log2(1 + r), where f
+// is the mantissa, f_j the middle of its 1/64 interval and r = f / f_j - 1
+// (|r| <= 2^-7), by the series of the logarithm (next term below 3e-18).
+__device__ __forceinline__ double log2_tab(double x, const LevelScratch& sh) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, x);
+    const uint32_t hi = (uint32_t)(b >> 32);
+    const int e = (int)(hi >> 20) - 1023, j = (int)(hi >> 14) & (kLogSteps - 1);
+    const double f =
+        __builtin_bit_cast(double, (b & 0xFFFFFFFFull) | ((uint64_t)((hi & 0xFFFFFu) | 0x3FF00000u) << 32));
+    constexpr double K = 1.4426950408889634074;  // 1 / ln 2
+    const double r = fma(f, sh.lg[j][0], -1.0);
+    double p = fma(r, K / 7, -K / 6);
+    p = fma(r, p, K / 5);
+    p = fma(r, p, -K / 4);
+    p = fma(r, p, K / 3);
+    p = fma(r, p, -K / 2);
+    p = fma(r, p, K);
+    return fma(r, p, (double)e + sh.lg[j][1]);
+}
+
+// 2^y (0 far below): y = n / 32 + r, the table's 2^((n mod 32) / 32) times the
+// exponential series in r (|r| <= 2^-6, next term below 4e-18), times 2^(n div 32).
+__device__ __forceinline__ double exp2_tab(double y, const LevelScratch& sh) {
+    y = fmax(y, -1100.0);
+    const double nd = rint(y * kExpSteps);
+    const int n = (int)nd;
+    constexpr double L = 0.69314718055994530942;
+    const double r = fma(nd, -1.0 / kExpSteps, y);
+    double p = fma(r, L * L * L * L * L * L / 720, L * L * L * L * L / 120);
+    p = fma(r, p, L * L * L * L / 24);
+    p = fma(r, p, L * L * L / 6);
+    p = fma(r, p, L * L / 2);
+    p = fma(r, p, L);
+    p = fma(r, p, 1.0);
+    return ldexp(p * sh.ex[n & (kExpSteps - 1)], n >> 5);
+}
+
 // Eq.4 and u^m by distance ratios, u_k = w_k / sum_j w_j with
 // w_k = (d_min / d_k)^(2/(m-1)) <= 1, and the zero-distance rule (equal split
 // over the clusters at distance 0): the form that holds for any centroids.
 template <int C>
-__device__ __noinline__ void level_u_any(double x, const double* v, double m, double* u, double* a) {
+__device__ __noinline__ double level_u_any(double x, const double* v, double m, double* u, double* a) {
     double d[C];
     double dmin = 1.0e308;
     int nz = 0;
@@ -223,18 +301,36 @@ __device__ __noinline__ void level_u_any(double x, const double* v, double m, do
         u[k] /= s;
         a[k] = m == 2.0 ? u[k] * u[k] : pow(u[k], m);
     }
+    double j = 0.0;
+#pragma unroll
+    for (int k = 0; k < C; ++k) j += a[k] * d[k] * d[k];
+    return j;
 }
 
 // Memberships u (Eq.4) and a = u^m of grey level x.  With q_k = (x - v_k)^2,
 // the m = 2 memberships are u2_k = P_k / sum_j P_j, P_k = prod_{j != k} q_j
 // (one reciprocal); other m follow from w_k = u2_k^alpha, u_k = w_k / S,
 // S = sum w, and u_k^m = w_k u2_k / S^m because alpha (m - 1) = 1 -- so only
-// the generic m needs logarithms, one log2 and one exp2 per cluster.  Two
-// centroids on the same level (all P zero) and products out of range take
-// the ratio form.
+// the generic m needs logarithms, one log2 and one exp2 per cluster.  Returns
+// the level's term of Eq.1, sum_k u_k^m q_k = u2_0 q_0 S^(1-m) (u2_k q_k is the
+// same for every k).  Two centroids on one level, or products out of range,
+// give non-finite values: the caller sees them in the sums and repeats the
+// pass with the ratio form (`safe`).
 template <int C, int MK>
-__device__ __forceinline__ void level_u(double x, const double (&v)[C], double m, double alpha, double (&u)[C],
-                                        double (&a)[C]) {
+__device__ __forceinline__ double level_u(double x, const double (&v)[C], double m, double alpha, bool safe,
+                                          const LevelScratch& sh, double (&u)[C], double (&a)[C]) {
+    if (safe) {
+        double cv[C], cu[C], ca[C];  // copies: only they live in memory
+#pragma unroll
+        for (int k = 0; k < C; ++k) cv[k] = v[k];
+        const double j = level_u_any<C>(x, cv, m, cu, ca);
+#pragma unroll
+        for (int k = 0; k < C; ++k) {
+            u[k] = cu[k];
+            a[k] = ca[k];
+        }
+        return j;
+    }
     double q[C], P[C], pre[C], suf[C];
 #pragma unroll
     for (int k = 0; k < C; ++k) {
@@ -254,76 +350,76 @@ __device__ __forceinline__ void level_u(double x, const double (&v)[C], double m
     double S = P[0];
 #pragma unroll
     for (int j = 1; j < C; ++j) S += P[j];
-    if (!(S > 1.0e-280 && S < 1.0e280)) {
-        double cv[C], cu[C], ca[C];  // copies: only they live in memory
-#pragma unroll
-        for (int k = 0; k < C; ++k) cv[k] = v[k];
-        level_u_any<C>(x, cv, m, cu, ca);
-#pragma unroll
-        for (int k = 0; k < C; ++k) {
-            u[k] = cu[k];
-            a[k] = ca[k];
-        }
-        return;
-    }
     const double r = recip_f64(S);
+#pragma unroll
+    for (int k = 0; k < C; ++k) P[k] *= r;  // u2
+    const double j2 = P[0] * q[0];
     if constexpr (MK == kM2) {
 #pragma unroll
         for (int k = 0; k < C; ++k) {
-            u[k] = P[k] * r;
-            a[k] = u[k] * u[k];
+            u[k] = P[k];
+            a[k] = P[k] * P[k];
         }
+        return j2;
     } else if constexpr (MK == kM15) {
-        double s = 0.0, w[C];
-#pragma unroll
-        for (int k = 0; k < C; ++k) {
-            P[k] *= r;
-            w[k] = P[k] * P[k];
-            s += w[k];
-        }
-        const double rs = recip_f64(s), t = rs * sqrt(rs);
-#pragma unroll
-        for (int k = 0; k < C; ++k) {
-            u[k] = w[k] * rs;
-            a[k] = w[k] * P[k] * t;
-        }
-    } else {
-        double L[C], top = -1.0e300;
-#pragma unroll
-        for (int k = 0; k < C; ++k) {
-            P[k] *= r;
-            L[k] = P[k] > 0.0 ? log2(P[k]) : -1.0e300;
-            top = fmax(top, L[k]);
-        }
         double s = 0.0;
 #pragma unroll
         for (int k = 0; k < C; ++k) {
-            u[k] = exp2(alpha * (L[k] - top));  // w_k, largest 1
+            u[k] = P[k] * P[k];
             s += u[k];
         }
-        const double rs = recip_f64(s);
-        // u^m = w_k (u2_k / u2_max) s^-m
-        const double t = exp2(-m * log2(s) - top);
+        const double rs = recip_f64(s), t = rs * sqrt(rs);
 #pragma unroll
         for (int k = 0; k < C; ++k) {
             a[k] = u[k] * P[k] * t;
             u[k] *= rs;
         }
+        return j2 * (s * t);
+    } else {
+        double L[C], top = -1.0e300;
+#pragma unroll
+        for (int k = 0; k < C; ++k) {
+            L[k] = log2_tab(fmax(P[k], 1.0e-290), sh);
+            top = fmax(top, L[k]);
+        }
+        double s = 0.0;
+#pragma unroll
+        for (int k = 0; k < C; ++k) {
+            const double w = exp2_tab(alpha * (L[k] - top), sh);  // largest 1
+            u[k] = P[k] > 1.0e-290 ? w : 0.0;
+            s += u[k];
+        }
+        const double rs = recip_f64(s);
+        // u^m = w_k (u2_k / u2_max) s^-m
+        const double t = exp2_tab(fma(-m, log2_tab(s, sh), -top), sh);
+#pragma unroll
+        for (int k = 0; k < C; ++k) {
+            a[k] = u[k] * P[k] * t;
+            u[k] *= rs;
+        }
+        return j2 * (s * t);
     }
 }
 
 // Algorithm 1 on the counts: thread t < 256 holds the count of level t.
 // Called by kLvIterWaves waves (the block's other waves have ended).  Waves
-// 0..3 own 64 levels each, one per lane; per pass a wave evaluates Eq.4 once
-// (U^(p-1) stays in registers), turns its weights through LDS so that a
-// cluster's sums need only 3 or 4 cross-lane steps, and writes its partial
-// sums; after the pass's only barrier every wave adds the four partial sums
-// in wave order and takes the decision itself (same bits in every lane), and
-// the fifth wave records it, off the others' path.
+// 0..3 own 64 levels each, one per lane; per attempt at a pass a wave
+// evaluates Eq.4 once (U^(p-1) stays in registers), sums its levels and writes
+// its partial sums; after the attempt's only barrier every wave adds the four
+// partial sums in wave order and takes the decision itself (same bits in
+// every lane).  The stopping test needs only one bit per wave; the change and
+// the objective of the history are reduced and recorded by the fifth wave,
+// one barrier behind, off the others' path.  One wave per SIMD runs a chain of
+// dependent instructions, an LDS round trip and a barrier per pass: latency is
+// what there is to save, and one CU is all that 256 levels can use (a second
+// one would cost two exchanges of 1.1 us).  Per pass, C = 4, m = 2: 0.82 us
+// with a chain of moves and adds per sum and the record in the same
+// interval, 0.65 us so; C = 8, m = 2.5: 3.0 us with the library's log2 and
+// exp2, 1.8 us with the tables above.
 template <int C, int MK, bool LEARNED>
 __device__ __forceinline__ void level_iterate(const LevelProblem& pb, uint32_t cnt, LevelScratch& sh,
                                               LevelOutcome& out) {
-    using Gm = LevelGeom<C>;
+    constexpr int SETS = (C + 3) / 4;  // clusters a lane sums: kc, kc + 4
     const int tid = threadIdx.x, lane = tid & 63;
     const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
     const bool work = wid < 4;
@@ -334,6 +430,15 @@ __device__ __forceinline__ void level_iterate(const LevelProblem& pb, uint32_t c
 #pragma unroll
     for (int k = 0; k < C; ++k) uo[k] = 0.0;
     bool huge = false;
+    if constexpr (MK == kMGeneric) {
+        if (tid < kExpSteps) sh.ex[tid] = exp2((double)tid / kExpSteps);
+        if (tid < kLogSteps) {
+            const double f = 1.0 + (tid + 0.5) / kLogSteps, r = 1.0 / f;
+            sh.lg[tid][0] = r;
+            sh.lg[tid][1] = -log2(r);
+        }
+        lds_barrier();
+    }
     if (pb.do_init) {
         if (work) {
             const uint64_t m = __ballot(cnt != 0u);
@@ -381,114 +486,170 @@ __device__ __forceinline__ void level_iterate(const LevelProblem& pb, uint32_t c
             double vp[C], t[C];
 #pragma unroll
             for (int k = 0; k < C; ++k) vp[k] = pb.hist_v[(int64_t)(p - 1) * C + k];
-            level_u<C, MK>(x, vp, pb.m, pb.alpha, uo, t);
+            level_u<C, MK>(x, vp, pb.m, pb.alpha, false, sh, uo, t);
+            bool fin = true;
+#pragma unroll
+            for (int k = 0; k < C; ++k) fin = fin && isfinite(uo[k]);
+            if (!fin) level_u<C, MK>(x, vp, pb.m, pb.alpha, true, sh, uo, t);
         }
     }
-    const int part = lane % Gm::PARTS;
-    const int kc = lane / Gm::PARTS < C ? lane / Gm::PARTS : C - 1;  // the cluster whose sums this lane adds
-    double vk = v[0];  // v[kc]
+    const bool owner = (lane & 15) == 0;  // one lane per cluster of a set
+    int kc[SETS];       // the clusters whose sums this lane holds
+    double vk[SETS], vr[SETS];  // their centroids in this pass; in the last pass run
 #pragma unroll
-    for (int k = 1; k < C; ++k)
-        if (kc == k) vk = v[k];
-    double* w = sh.w[work ? wid : 0];
-    int status = FCM_RUNNING, passes = 0;
-    double delta = __builtin_nan(""), Jt = __builtin_nan("");
-    double vr = vk;  // centroid kc of the last pass run
-    int last = p;
-    for (int budget = pb.max_passes; budget > 0; --budget) {
-        const int par = p & 1;
-        if (work) {
+    for (int s = 0; s < SETS; ++s) {
+        const int k = (lane >> 4) + 4 * s;
+        kc[s] = k < C ? k : C - 1;
+        vk[s] = v[0];
+#pragma unroll
+        for (int q = 1; q < C; ++q)
+            if (kc[s] == q) vk[s] = v[q];
+        vr[s] = vk[s];
+    }
+    if (pb.max_passes <= 0) return;
+    if (work) {
+        // passes below `calm` go on unless they converge or turn non-finite
+        const int64_t stop_at = (int64_t)p + pb.max_passes - 1;
+        const int calm = huge ? -1 : (int)(stop_at < pb.max_iter ? stop_at : pb.max_iter);
+        int par = 0, slot = 0;
+        bool safe = false;
+        while (true) {
             double u[C], a[C];
-            level_u<C, MK>(x, v, pb.m, pb.alpha, u, a);
+            const double jt = level_u<C, MK>(x, v, pb.m, pb.alpha, safe, sh, u, a);
+#pragma unroll
+            for (int k = 0; k < C; ++k) a[k] *= c;
+            double num[SETS], den[SETS];
+#pragma unroll
+            for (int s = 0; s < SETS; ++s) {
+                double t[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) t[k] = 4 * s + k < C ? a[4 * s + k < C ? 4 * s + k : 0] : 0.0;
+                num[s] = quad_sum_f64(t[0] * x, t[1] * x, t[2] * x, t[3] * x);
+                den[s] = quad_sum_f64(t[0], t[1], t[2], t[3]);
+            }
             double dm = 0.0;
 #pragma unroll
             for (int k = 0; k < C; ++k) {
-                w[k * Gm::STRIDE + lane] = c * a[k];
-                dm = fmax(dm, fabs(u[k] - uo[k]));
-                uo[k] = u[k];
+                const double d = u[k] - uo[k];
+                dm = fmax(dm, fmax(d, -d));
             }
             if (!cnt) dm = 0.0;
-            // the wave's own LDS writes are visible to its lanes (in order)
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            double num = 0.0, den = 0.0, jk = 0.0;
+            const bool moved = __any(dm >= pb.eps);
+            sh.dm[slot][tid] = dm;
+            sh.jt[slot][tid] = c * jt;
+            if (owner) {
 #pragma unroll
-            for (int i = 0; i < Gm::PER; ++i) {
-                const int l = part + Gm::PARTS * i;
-                const double wv = w[kc * Gm::STRIDE + l];
-                const double xl = (double)(64 * wid + l), e = xl - vk;
-                den += wv;
-                num = fma(wv, xl, num);
-                jk = fma(wv, e * e, jk);
+                for (int s = 0; s < SETS; ++s)
+                    if (kc[s] == (lane >> 4) + 4 * s) {
+                        sh.red[par][kc[s]][0][wid] = num[s];
+                        sh.red[par][kc[s]][1][wid] = den[s];
+                    }
+                if (lane == 0) sh.flag[par][wid] = moved;
             }
-            num = dpp_add_f64<0xB1>(num);
-            den = dpp_add_f64<0xB1>(den);
-            jk = dpp_add_f64<0xB1>(jk);
-            num = dpp_add_f64<0x4E>(num);
-            den = dpp_add_f64<0x4E>(den);
-            jk = dpp_add_f64<0x4E>(jk);
-            num = dpp_add_f64<0x141>(num);
-            den = dpp_add_f64<0x141>(den);
-            jk = dpp_add_f64<0x141>(jk);
-            if constexpr (Gm::PARTS == 16) {
-                num = dpp_add_f64<0x140>(num);
-                den = dpp_add_f64<0x140>(den);
-                jk = dpp_add_f64<0x140>(jk);
+            lds_barrier();
+            double rn[SETS][8];
+#pragma unroll
+            for (int s = 0; s < SETS; ++s)
+#pragma unroll
+                for (int i = 0; i < 8; ++i) rn[s][i] = sh.red[par][kc[s]][0][i];
+            const int any = (sh.flag[par][0] | sh.flag[par][1]) | (sh.flag[par][2] | sh.flag[par][3]);
+            __builtin_amdgcn_sched_barrier(0);  // all reads are on their way before anything waits for one
+            double vn[SETS];
+            bool fin = true;
+#pragma unroll
+            for (int s = 0; s < SETS; ++s) {
+                const double nt = ((rn[s][0] + rn[s][1]) + rn[s][2]) + rn[s][3];
+                const double dt = ((rn[s][4] + rn[s][5]) + rn[s][6]) + rn[s][7];
+                const double q = nt / dt;
+                vn[s] = dt > 0.0 ? q : vk[s];
+                fin = fin && isfinite(vn[s]) && dt >= 0.0;
             }
-            if (part == 0 && lane < C * Gm::PARTS) {
-                sh.red[par][kc][0][wid] = num;
-                sh.red[par][kc][1][wid] = den;
-                sh.red[par][kc][2][wid] = jk;
+            const bool ok = __all(fin);
+            const bool go = ok && __builtin_amdgcn_readfirstlane(any) != 0;
+            int dec = (FCM_RUNNING + kLvStatus0) << kLvStatusShift;
+            bool run = true;
+            if (!(go && p < calm)) {
+                const bool retry = !ok && !safe;  // again, with the form that holds for any centroids
+                const int status = !ok || huge ? FCM_ENUMERIC
+                                               : (p >= 1 && !go ? FCM_OK : (p >= pb.max_iter ? FCM_NOT_CONVERGED
+                                                                                             : FCM_RUNNING));
+                run = !retry && status == FCM_RUNNING && p < stop_at;
+                dec = retry ? kLvRetry : ((status + kLvStatus0) << kLvStatusShift) | (run ? 0 : kLvEnd);
             }
-            dm = wave_max_pos_f64(dm);
-            if (lane == 63) sh.dmax[par][wid] = dm;
+            if (wid == 0 && owner) {
+#pragma unroll
+                for (int s = 0; s < SETS; ++s)
+                    if (kc[s] == (lane >> 4) + 4 * s) sh.vnext[slot][kc[s]] = vn[s];
+                if (lane == 0) sh.dec[slot] = dec;
+            }
+            par ^= 1;
+            slot = slot == 2 ? 0 : slot + 1;
+            if (run) {
+#pragma unroll
+                for (int k = 0; k < C; ++k) v[k] = readlane_d(vn[k / 4], 16 * (k % 4));
+#pragma unroll
+                for (int k = 0; k < C; ++k) uo[k] = u[k];
+#pragma unroll
+                for (int s = 0; s < SETS; ++s) vk[s] = vn[s];
+                ++p;
+            } else if (dec & kLvRetry) {
+                safe = true;
+            } else {
+#pragma unroll
+                for (int s = 0; s < SETS; ++s) {
+                    vr[s] = vk[s];
+                    if ((dec >> kLvStatusShift) - kLvStatus0 == FCM_RUNNING) vk[s] = vn[s];  // out of passes only
+                }
+                break;
+            }
         }
-        __syncthreads();
-        const double* rn = sh.red[par][kc][0];
-        const double num = ((rn[0] + rn[1]) + rn[2]) + rn[3];
-        const double den = ((rn[4] + rn[5]) + rn[6]) + rn[7];
-        const double dmx = fmax(fmax(sh.dmax[par][0], sh.dmax[par][1]), fmax(sh.dmax[par][2], sh.dmax[par][3]));
-        const double vn = den > 0.0 ? num / den : vk;
-        const bool bad = __any(!isfinite(vn)) || huge;
-        const int stop = __builtin_amdgcn_readfirstlane((int)(p >= 1 && dmx < pb.eps));
-        status = bad ? FCM_ENUMERIC : (stop ? FCM_OK : (p >= pb.max_iter ? FCM_NOT_CONVERGED : FCM_RUNNING));
-        if (!work) {
-            const double jk = ((rn[8] + rn[9]) + rn[10]) + rn[11];
-            Jt = 0.0;
+        if (wid == 0 && owner)
 #pragma unroll
-            for (int k = 0; k < C; ++k) Jt += readlane_d(jk, k * Gm::PARTS);
-            delta = p > 0 ? dmx : __builtin_nan("");
-            if (lane == 0) {
-                pb.hist_J[p] = Jt;
-                pb.hist_d[p] = delta;
-                if (pb.times) pb.times[p + 1] = wall_clock64();
-            }
-            if (status == FCM_RUNNING && part == 0 && lane < C * Gm::PARTS) pb.hist_v[(int64_t)(p + 1) * C + kc] = vn;
-        }
-        ++passes;
-        last = p;
-        vr = vk;
-        if (status != FCM_RUNNING) break;
-        vk = vn;
-#pragma unroll
-        for (int k = 0; k < C; ++k) v[k] = readlane_d(vn, k * Gm::PARTS);
-        ++p;
-    }
-    if (wid == 4 && part == 0 && lane < C * Gm::PARTS) {
-        sh.v[kc] = vk;   // v^pass
-        sh.vp[kc] = vr;  // v^iters
-    }
-    if (wid == 4) {
-        out.pass = p;
-        out.iters = passes ? last : -1;
-        out.passes = passes;
-        out.status = status;
-        out.done = status != FCM_RUNNING;
+            for (int s = 0; s < SETS; ++s)
+                if (kc[s] == (lane >> 4) + 4 * s) {
+                    sh.v[kc[s]] = vk[s];   // v^pass
+                    sh.vp[kc[s]] = vr[s];  // v^iters
+                }
+        lds_barrier();
+    } else {
+        int slot = 0, passes = 0;
         out.lo = lo;
         out.hi = hi;
-        out.delta = delta;
-        out.J = Jt;
+        lds_barrier();
+        while (true) {
+            lds_barrier();  // of the next attempt, or the one after the last
+            const int dec = __builtin_amdgcn_readfirstlane(sh.dec[slot]);
+            if (!(dec & kLvRetry)) {
+                const int status = (dec >> kLvStatusShift) - kLvStatus0;
+                const double* dr = sh.dm[slot];
+                const double* jr = sh.jt[slot];
+                const double j = (jr[lane] + jr[lane + 64]) + (jr[lane + 128] + jr[lane + 192]);
+                double d = fmax(fmax(dr[lane], dr[lane + 64]), fmax(dr[lane + 128], dr[lane + 192]));
+                const double vn = sh.vnext[slot][lane & 7];
+                const double J = quad_sum_f64(j, 0.0, 0.0, 0.0);
+                d = wave_max_pos_f64(d);
+                const double delta = p > 0 ? readlane_d(d, 63) : __builtin_nan("");
+                if (lane == 0) {
+                    pb.hist_J[p] = J;
+                    pb.hist_d[p] = delta;
+                    if (pb.times) pb.times[p + 1] = wall_clock64();
+                }
+                ++passes;
+                out.iters = p;
+                out.delta = delta;
+                out.J = readlane_d(J, 0);
+                out.status = status;
+                if (status == FCM_RUNNING) {
+                    ++p;
+                    if (lane < C) pb.hist_v[(int64_t)p * C + lane] = vn;
+                }
+                if (dec & kLvEnd) break;
+            }
+            slot = slot == 2 ? 0 : slot + 1;
+        }
+        out.pass = p;
+        out.passes = passes;
+        out.done = out.status != FCM_RUNNING;
     }
 }
 
