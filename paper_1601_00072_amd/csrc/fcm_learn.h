@@ -30,13 +30,23 @@ hipError_t launch_histogram(const uint8_t* x, const int64_t* d_offsets, int coun
 // the same on counters that are already zero (no memset)
 hipError_t launch_histogram_counts(const uint8_t* x, const int64_t* d_offsets, int count, int64_t max_n,
                                    uint32_t* counts, float* hist, hipStream_t s);
-hipError_t launch_gemm(bool ta, bool tb, const float* A, const float* B, float* Cm, int M, int N, int K,
-                       const float* bias, int relu, const float* mask, hipStream_t s);
-hipError_t launch_colsum(const float* G, int M, int N, float* out, hipStream_t s);
-hipError_t launch_mse(const float* Y, const float* T, int n, float scale, float* dY, float* loss_out, hipStream_t s);
-hipError_t launch_adam(float* theta, const float* g, float* m, float* v, int64_t n, float lr, int step,
-                       hipStream_t s);
-hipError_t launch_gather(const float* X, const int32_t* idx, int rows, int cols, float* out, hipStream_t s);
+// One training step on `rows` samples (rows of X [.][256] and T [.][C] picked
+// by idx, or the first ones if idx is null): loss and gradient at theta, then
+// one Adam update (step counts from 1) -- or, with grad set, the gradient
+// alone.  Offsets o* of the parameter blocks in the flat vector; activations
+// and derivatives hold one row per sample.
+struct TrainStep {
+    const float *X, *T;
+    const int32_t* idx;
+    int rows, C;
+    int64_t oW1, ob1, oW2, ob2, oW3, ob3;
+    float *theta, *m, *v, *grad;
+    float *h1, *h2, *d, *dy, *dz2, *dz1;
+    float* loss;
+    float scale, lr;                 // 1 / (rows C), Adam's step size
+    float b1, b2, eps, c1, c2;       // set by the launcher
+};
+hipError_t launch_train_step(TrainStep a, int step, hipStream_t s);
 // BF16 inference copy (output-major rows; see fcm_learn_dev.h) of the flat parameters
 hipError_t launch_to_bf16(const float* theta, uint16_t* out, int C, hipStream_t s);
 hipError_t launch_mlp_infer(const void* w, bool bf16, const float* X, int count, int C, float* Y, hipStream_t s);

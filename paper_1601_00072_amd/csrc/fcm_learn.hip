@@ -109,156 +109,314 @@ hipError_t launch_histogram(const uint8_t* x, const int64_t* d_offsets, int coun
 }
 
 // ---------------------------------------------------------------------------
-// FP32 GEMM for training: Cm[M][N] = op(A) op(B) (+ bias[N]) (ReLU) (* mask>0)
-// op(A) is A [M][K] or, transposed, A [K][M]; op(B) is B [K][N] or B [N][K].
-// The training shapes are small (K and M up to 256 rows of a minibatch), so
-// the output is cut into 16 x 16 tiles, one output per thread (enough blocks
-// to spread over the chip), K in steps of 16 through LDS.  Each output is a
-// sum over k in increasing order.
+// training step in two launches
 // ---------------------------------------------------------------------------
+//
+// A step is 63 MFLOP at the usual 256 rows: launches, and inside them the
+// latency of reading what another XCD has just written (about 1 us), bound
+// it, not arithmetic (one kernel per product, bias, loss and update took 14
+// launches and 100 us per step; these two take 20 us, 11 + 9).  So each block issues
+// all its reads at once, as 16-byte loads into registers, and passes them
+// through LDS.  The first launch does what a row needs by itself -- forward,
+// loss derivative, the backward pass to both hidden layers -- for kTrainRows
+// rows per block; the second forms every gradient as a sum over the rows and
+// updates its parameter at once.  Every output is one FP32 chain of fused
+// multiply-adds over its inner index in increasing order (rows in batch order
+// for the gradients), whatever block computes it, so results do not depend on
+// the split.
 
-constexpr int kT = 16;  // 16 x 16 outputs per block, one per thread; K in steps of 16
+typedef float vec4 __attribute__((ext_vector_type(4)));
 
-template <bool TA, bool TB>
-__global__ __launch_bounds__(256) void gemm_kernel(const float* A, const float* B, float* Cm, int M, int N, int K,
-                                                   const float* bias, int relu, const float* mask) {
-    __shared__ float As[kT][kT + 1];  // [m][k]
-    __shared__ float Bs[kT][kT + 1];  // [k][n]
-    const int tx = threadIdx.x % kT, ty = threadIdx.x / kT;
-    const int row0 = blockIdx.y * kT, col0 = blockIdx.x * kT;
-    float acc = 0.f;
-    for (int k0 = 0; k0 < K; k0 += kT) {
-        // one element of each tile per thread; consecutive threads take
-        // consecutive addresses of the stored layout (transposed operands
-        // walk the tile the other way round)
-        const int e = threadIdx.x;
-        {
-            const int r = TA ? e % kT : e / kT, c = TA ? e / kT : e % kT;
-            const int gm = row0 + r, gk = k0 + c;
-            float va = 0.f;
-            if (gm < M && gk < K) va = TA ? A[(int64_t)gk * M + gm] : A[(int64_t)gm * K + gk];
-            As[r][c] = va;
-        }
-        {
-            const int rb = TB ? e % kT : e / kT, cb = TB ? e / kT : e % kT;
-            const int gk = k0 + rb, gn = col0 + cb;
-            float vb = 0.f;
-            if (gk < K && gn < N) vb = TB ? B[(int64_t)gn * K + gk] : B[(int64_t)gk * N + gn];
-            Bs[rb][cb] = vb;
-        }
-        __syncthreads();
+constexpr int kTrainRows = 2;   // rows per block: 128 blocks for the usual batch, each reads W1 once (128 KB)
+constexpr int kTileK1 = 4;      // rows of W1 per block of the second launch
+constexpr int kTileK2 = 8;      // rows of W2 per block
+constexpr int kRowChunk = 128;  // rows of the batch staged at a time
+constexpr int kColTile = 16, kRowGroups = 16;  // bias sums
+
+__device__ __forceinline__ int64_t train_row(const TrainStep& a, int i) { return a.idx ? (int64_t)a.idx[i] : i; }
+
+__global__ __launch_bounds__(256) void train_rows_kernel(TrainStep a) {
+    __shared__ __align__(16) float W1s[128 * 128];  // one half of W1 at a time
+    __shared__ float W2s[128][65], W3s[64 * kMaxC];
+    __shared__ float Xs[kTrainRows][256], h1s[kTrainRows][128], h2s[kTrainRows][64], dz2s[kTrainRows][64];
+    __shared__ float dys[kTrainRows][kMaxC];
+    const int t = threadIdx.x, C = a.C;
+    const int row0 = blockIdx.x * kTrainRows;
+    const int nr = a.rows - row0 < kTrainRows ? a.rows - row0 : kTrainRows;
+    const float* th = a.theta;
+    // every read of the block, in flight together
+    const vec4* w1 = reinterpret_cast<const vec4*>(th + a.oW1);
+    const vec4* w2 = reinterpret_cast<const vec4*>(th + a.oW2);
+    vec4 qa[16], qb[16], q2[8];
+    float x[kTrainRows], w3[2];
 #pragma unroll
-        for (int kk = 0; kk < kT; ++kk) acc = fmaf(As[ty][kk], Bs[kk][tx], acc);
-        __syncthreads();
+    for (int r = 0; r < kTrainRows; ++r) x[r] = r < nr ? a.X[train_row(a, row0 + r) * 256 + t] : 0.f;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) qa[i] = w1[i * 256 + t];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) qb[i] = w1[(16 + i) * 256 + t];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) q2[i] = w2[i * 256 + t];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) w3[i] = i * 256 + t < 64 * C ? th[a.oW3 + i * 256 + t] : 0.f;
+    const int u1 = t & 127, r1 = t >> 7;  // (row, unit) of the first hidden layer
+    const int u2 = t & 63, r2 = (t >> 6) & 1;  // of the second (threads below 128)
+    const float bias1 = th[a.ob1 + u1], bias2 = th[a.ob2 + u2];
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int r = 0; r < kTrainRows; ++r) Xs[r][t] = x[r];
+    float z = 0.f;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) reinterpret_cast<vec4*>(W1s)[i * 256 + t] = qa[i];
+    __syncthreads();
+#pragma unroll 16
+    for (int k = 0; k < 128; ++k) z = fmaf(Xs[r1][k], W1s[k * 128 + u1], z);
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 16; ++i) reinterpret_cast<vec4*>(W1s)[i * 256 + t] = qb[i];
+    __syncthreads();
+#pragma unroll 16
+    for (int k = 0; k < 128; ++k) z = fmaf(Xs[r1][128 + k], W1s[k * 128 + u1], z);
+    const float h1 = fmaxf(z + bias1, 0.f);
+    h1s[r1][u1] = h1;
+    if (r1 < nr) a.h1[(int64_t)(row0 + r1) * 128 + u1] = h1;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const int e = 4 * (i * 256 + t);
+        float* d = &W2s[e >> 6][e & 63];
+        d[0] = q2[i].x;
+        d[1] = q2[i].y;
+        d[2] = q2[i].z;
+        d[3] = q2[i].w;
     }
-    const int gm = row0 + ty, gn = col0 + tx;
-    if (gm >= M || gn >= N) return;
-    float v = acc;
-    if (bias) v += bias[gn];
-    if (relu) v = fmaxf(v, 0.f);
-    if (mask && !(mask[(int64_t)gm * N + gn] > 0.f)) v = 0.f;
-    Cm[(int64_t)gm * N + gn] = v;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) W3s[i * 256 + t] = w3[i];
+    __syncthreads();
+    float h2 = 0.f;
+    if (t < 128) {
+        float y = 0.f;
+#pragma unroll 16
+        for (int k = 0; k < 128; ++k) y = fmaf(h1s[r2][k], W2s[k][u2], y);
+        h2 = fmaxf(y + bias2, 0.f);
+        h2s[r2][u2] = h2;
+        if (r2 < nr) a.h2[(int64_t)(row0 + r2) * 64 + u2] = h2;
+    }
+    __syncthreads();
+    if (t < kTrainRows * C) {
+        const int r = t / C, c = t % C;
+        float y = 0.f;
+#pragma unroll 16
+        for (int k = 0; k < 64; ++k) y = fmaf(h2s[r][k], W3s[k * C + c], y);
+        float dy = 0.f;
+        if (r < nr) {
+            const float d = (y + th[a.ob3 + c]) - a.T[train_row(a, row0 + r) * C + c];
+            dy = 2.f * d * a.scale;
+            a.d[(int64_t)(row0 + r) * C + c] = d;
+            a.dy[(int64_t)(row0 + r) * C + c] = dy;
+        }
+        dys[r][c] = dy;
+    }
+    __syncthreads();
+    if (t < 128) {
+        float g = 0.f;
+        for (int c = 0; c < C; ++c) g = fmaf(dys[r2][c], W3s[u2 * C + c], g);
+        if (!(h2 > 0.f)) g = 0.f;  // the ReLU's derivative, from the activation
+        dz2s[r2][u2] = g;
+        if (r2 < nr) a.dz2[(int64_t)(row0 + r2) * 64 + u2] = g;
+    }
+    __syncthreads();
+    float g = 0.f;
+#pragma unroll 16
+    for (int n = 0; n < 64; ++n) g = fmaf(dz2s[r1][n], W2s[u1][n], g);
+    if (r1 < nr) a.dz1[(int64_t)(row0 + r1) * 128 + u1] = h1 > 0.f ? g : 0.f;
 }
 
-hipError_t launch_gemm(bool ta, bool tb, const float* A, const float* B, float* Cm, int M, int N, int K,
-                       const float* bias, int relu, const float* mask, hipStream_t s) {
-    const dim3 grid((N + kT - 1) / kT, (M + kT - 1) / kT);
-    if (!ta && !tb)
-        hipLaunchKernelGGL((gemm_kernel<false, false>), grid, dim3(256), 0, s, A, B, Cm, M, N, K, bias, relu, mask);
-    else if (ta && !tb)
-        hipLaunchKernelGGL((gemm_kernel<true, false>), grid, dim3(256), 0, s, A, B, Cm, M, N, K, bias, relu, mask);
-    else if (!ta && tb)
-        hipLaunchKernelGGL((gemm_kernel<false, true>), grid, dim3(256), 0, s, A, B, Cm, M, N, K, bias, relu, mask);
-    else
-        hipLaunchKernelGGL((gemm_kernel<true, true>), grid, dim3(256), 0, s, A, B, Cm, M, N, K, bias, relu, mask);
-    return hipGetLastError();
+// Adam update of parameter i with gradient gi, or (no update) the gradient itself.
+__device__ __forceinline__ void train_apply(const TrainStep& a, int64_t i, float gi) {
+    if (a.grad) {
+        a.grad[i] = gi;
+        return;
+    }
+    const float mi = a.b1 * a.m[i] + (1.f - a.b1) * gi;
+    const float vi = a.b2 * a.v[i] + (1.f - a.b2) * gi * gi;
+    a.m[i] = mi;
+    a.v[i] = vi;
+    a.theta[i] -= a.lr * (mi / a.c1) / (sqrtf(vi / a.c2) + a.eps);
 }
 
-// column sums of G [M][N] into out[N]: a block takes 16 columns; its 16 row
-// groups (thread (g, c) adds rows g, g + 16, ... of column c) run in
-// parallel, then the groups are added in order g = 0..15 -- a fixed order, so
-// the sums are reproducible run to run
-constexpr int kColTile = 16, kRowGroups = 16;
+// A chunk of kRowChunk rows of G [rows][N] on its way through registers; rows
+// beyond the batch are zero and add nothing.
+template <int N>
+struct RowChunk {
+    static constexpr int Q = kRowChunk * N / 4 / 256;
+    vec4 q[Q];
+    __device__ __forceinline__ void load(const float* G, int i0, int rows) {
+        const int64_t base = (int64_t)i0 * N / 4, end = (int64_t)rows * N / 4;
+#pragma unroll
+        for (int i = 0; i < Q; ++i) {
+            const int64_t e = base + i * 256 + threadIdx.x;
+            q[i] = e < end ? reinterpret_cast<const vec4*>(G)[e] : vec4{};
+        }
+    }
+    __device__ __forceinline__ void store(float* s) const {
+#pragma unroll
+        for (int i = 0; i < Q; ++i) reinterpret_cast<vec4*>(s)[i * 256 + threadIdx.x] = q[i];
+    }
+};
 
-__global__ __launch_bounds__(kColTile * kRowGroups) void colsum_kernel(const float* G, int M, int N, float* out) {
-    __shared__ float part[kRowGroups][kColTile + 1];
+constexpr int kTileLds = kRowChunk * 128;  // floats of a staged chunk of G
+
+// Gradient rows k0 .. k0 + TK - 1 of a layer with input A (row i at arow(i),
+// TK consecutive values) and output derivative G [rows][N]: thread (g, n)
+// holds TK * N / 256 rows of column n.
+template <int TK, int N, typename ARow>
+__device__ __forceinline__ void train_tile(const TrainStep& a, const ARow& arow, const float* G, int64_t out,
+                                           float* sg, float* sa) {
+    constexpr int GROUPS = 256 / N, PER = TK / GROUPS;
+    const int t = threadIdx.x, n = t % N, g = t / N;
+    float acc[PER] = {};
+    RowChunk<N> next;
+    float av[TK];
+    auto load = [&](int i0) {
+        const float* src = t < kRowChunk && i0 + t < a.rows ? arow(i0 + t) : nullptr;
+#pragma unroll
+        for (int q = 0; q < TK; ++q) av[q] = src ? src[q] : 0.f;  // the caller's histograms: 4-byte alignment
+        next.load(G, i0, a.rows);
+    };
+    load(0);
+    for (int i0 = 0; i0 < a.rows; i0 += kRowChunk) {
+        __syncthreads();
+        if (t < kRowChunk)
+#pragma unroll
+            for (int q = 0; q < TK; ++q) sa[t * TK + q] = av[q];
+        next.store(sg);
+        __syncthreads();
+        if (i0 + kRowChunk < a.rows) load(i0 + kRowChunk);
+#pragma unroll 16
+        for (int i = 0; i < kRowChunk; ++i) {
+            const float gv = sg[i * N + n];
+#pragma unroll
+            for (int p = 0; p < PER; ++p) acc[p] = fmaf(sa[i * TK + g * PER + p], gv, acc[p]);
+        }
+    }
+#pragma unroll
+    for (int p = 0; p < PER; ++p) train_apply(a, out + (int64_t)(g * PER + p) * N + n, acc[p]);
+}
+
+// Gradient of W3 [64][C]: up to two outputs per thread.
+__device__ __forceinline__ void train_w3(const TrainStep& a, float* sg, float* sa) {
+    const int t = threadIdx.x, C = a.C;
+    float acc[2] = {};
+    RowChunk<64> next;
+    float dv[kRowChunk * kMaxC / 256];
+    auto load = [&](int i0) {
+        next.load(a.h2, i0, a.rows);
+#pragma unroll
+        for (int q = 0; q < kRowChunk * kMaxC / 256; ++q) {
+            const int e = q * 256 + t;
+            dv[q] = e < kRowChunk * C && (int64_t)i0 * C + e < (int64_t)a.rows * C ? a.dy[(int64_t)i0 * C + e] : 0.f;
+        }
+    };
+    load(0);
+    for (int i0 = 0; i0 < a.rows; i0 += kRowChunk) {
+        __syncthreads();
+        next.store(sg);
+#pragma unroll
+        for (int q = 0; q < kRowChunk * kMaxC / 256; ++q) sa[q * 256 + t] = dv[q];
+        __syncthreads();
+        if (i0 + kRowChunk < a.rows) load(i0 + kRowChunk);
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+            const int e = p * 256 + t;
+            if (e < 64 * C) {
+                const int k = e / C, c = e % C;
+#pragma unroll 16
+                for (int i = 0; i < kRowChunk; ++i) acc[p] = fmaf(sg[i * 64 + k], sa[i * C + c], acc[p]);
+            }
+        }
+    }
+#pragma unroll
+    for (int p = 0; p < 2; ++p)
+        if (p * 256 + t < 64 * C) train_apply(a, a.oW3 + p * 256 + t, acc[p]);
+}
+
+// Column sums of G [rows][N], 16 columns per block: 16 row groups (thread (g,
+// c) adds rows g, g + 16, ... of column c), then the groups in order.
+__device__ __forceinline__ void train_bias(const TrainStep& a, const float* G, int N, int block, int64_t out,
+                                           float* s) {
     const int c = threadIdx.x % kColTile, g = threadIdx.x / kColTile;
-    const int j = blockIdx.x * kColTile + c;
-    float s = 0.f;
+    const int j = block * kColTile + c;
+    float v = 0.f;
     if (j < N)
-        for (int i = g; i < M; i += kRowGroups) s += G[(int64_t)i * N + j];
-    part[g][c] = s;
+#pragma unroll 8
+        for (int i = g; i < a.rows; i += kRowGroups) v += G[(int64_t)i * N + j];
+    s[g * (kColTile + 1) + c] = v;
     __syncthreads();
     if (g == 0 && j < N) {
-        float t = part[0][c];
-        for (int r = 1; r < kRowGroups; ++r) t += part[r][c];
-        out[j] = t;
+        float t = s[c];
+        for (int r = 1; r < kRowGroups; ++r) t += s[r * (kColTile + 1) + c];
+        train_apply(a, out + j, t);
     }
 }
 
-hipError_t launch_colsum(const float* G, int M, int N, float* out, hipStream_t s) {
-    hipLaunchKernelGGL(colsum_kernel, dim3((N + kColTile - 1) / kColTile), dim3(kColTile * kRowGroups), 0, s, G, M, N,
-                       out);
-    return hipGetLastError();
-}
+constexpr int kBlocksW1 = 256 / kTileK1, kBlocksW2 = 128 / kTileK2;
+constexpr int kBlocksB1 = 128 / kColTile, kBlocksB2 = 64 / kColTile;
+constexpr int kTrainBlocks = kBlocksW1 + kBlocksW2 + kBlocksB1 + kBlocksB2 + 3;  // and W3, b3, the loss
 
-// dY = 2 (Y - T) / (B C); loss_out[slot] = sum (Y - T)^2 / (B C) (one block, fixed order)
-__global__ __launch_bounds__(256) void mse_kernel(const float* Y, const float* T, int n, float scale, float* dY,
-                                                  float* loss_out) {
-    __shared__ double part[256];
-    double s = 0.0;
-    for (int i = threadIdx.x; i < n; i += 256) {
-        const float d = Y[i] - T[i];
-        dY[i] = 2.f * d * scale;
-        s += (double)d * d;
+__global__ __launch_bounds__(256) void train_update_kernel(TrainStep a) {
+    __shared__ __align__(16) float s[kTileLds];
+    __shared__ float sa[kRowChunk * 8];
+    static_assert(kTileK1 <= 8 && kTileK2 <= 8 && kMaxC <= 8, "sa holds a chunk of the narrow operand");
+    const int t = threadIdx.x, C = a.C;
+    int b = blockIdx.x;
+    if (b < kBlocksW1) {
+        const int k0 = b * kTileK1;
+        train_tile<kTileK1, 128>(a, [&](int i) { return a.X + train_row(a, i) * 256 + k0; }, a.dz1,
+                                 a.oW1 + (int64_t)k0 * 128, s, sa);
+        return;
     }
-    part[threadIdx.x] = s;
+    b -= kBlocksW1;
+    if (b < kBlocksW2) {
+        const int k0 = b * kTileK2;
+        train_tile<kTileK2, 64>(a, [&](int i) { return a.h1 + (int64_t)i * 128 + k0; }, a.dz2,
+                                a.oW2 + (int64_t)k0 * 64, s, sa);
+        return;
+    }
+    b -= kBlocksW2;
+    if (b == 0) return train_w3(a, s, sa);
+    --b;
+    if (b < kBlocksB1) return train_bias(a, a.dz1, 128, b, a.ob1, s);
+    b -= kBlocksB1;
+    if (b < kBlocksB2) return train_bias(a, a.dz2, 64, b, a.ob2, s);
+    b -= kBlocksB2;
+    if (b == 0) return train_bias(a, a.dy, C, 0, a.ob3, s);
+    // the batch's loss: sum (Y - T)^2 / (rows C), FP64, in a fixed order
+    double* part = reinterpret_cast<double*>(s);
+    double v = 0.0;
+    const int64_t n = (int64_t)a.rows * C;
+    for (int64_t i = t; i < n; i += 256) {
+        const float d = a.d[i];
+        v += (double)d * d;
+    }
+    part[t] = v;
     __syncthreads();
     for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) part[threadIdx.x] += part[threadIdx.x + w];
+        if (t < w) part[t] += part[t + w];
         __syncthreads();
     }
-    if (threadIdx.x == 0) *loss_out = (float)(part[0] * scale);
+    if (t == 0) *a.loss = (float)(part[0] * a.scale);
 }
 
-hipError_t launch_mse(const float* Y, const float* T, int n, float scale, float* dY, float* loss_out,
-                      hipStream_t s) {
-    hipLaunchKernelGGL(mse_kernel, dim3(1), dim3(256), 0, s, Y, T, n, scale, dY, loss_out);
-    return hipGetLastError();
-}
-
-__global__ void adam_kernel(float* theta, const float* g, float* m, float* v, int64_t n, float lr, float b1,
-                            float b2, float eps, float c1, float c2) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const float gi = g[i];
-    const float mi = b1 * m[i] + (1.f - b1) * gi;
-    const float vi = b2 * v[i] + (1.f - b2) * gi * gi;
-    m[i] = mi;
-    v[i] = vi;
-    theta[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
-}
-
-hipError_t launch_adam(float* theta, const float* g, float* m, float* v, int64_t n, float lr, int step,
-                       hipStream_t s) {
-    const float b1 = 0.9f, b2 = 0.999f;
-    const float c1 = 1.f - powf(b1, (float)step), c2 = 1.f - powf(b2, (float)step);
-    hipLaunchKernelGGL(adam_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, theta, g, m, v, n, lr, b1,
-                       b2, 1e-8f, c1, c2);
-    return hipGetLastError();
-}
-
-__global__ void gather_rows_kernel(const float* X, const int32_t* idx, int rows, int cols, float* out) {
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= (int64_t)rows * cols) return;
-    const int r = (int)(e / cols), c = (int)(e % cols);
-    out[e] = X[(int64_t)idx[r] * cols + c];
-}
-
-hipError_t launch_gather(const float* X, const int32_t* idx, int rows, int cols, float* out, hipStream_t s) {
-    const int64_t n = (int64_t)rows * cols;
-    hipLaunchKernelGGL(gather_rows_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, X, idx, rows, cols,
-                       out);
+hipError_t launch_train_step(TrainStep a, int step, hipStream_t s) {
+    a.b1 = 0.9f;
+    a.b2 = 0.999f;
+    a.eps = 1e-8f;
+    a.c1 = 1.f - powf(a.b1, (float)step);
+    a.c2 = 1.f - powf(a.b2, (float)step);
+    hipLaunchKernelGGL(train_rows_kernel, dim3((a.rows + kTrainRows - 1) / kTrainRows), dim3(256), 0, s, a);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(train_update_kernel, dim3(kTrainBlocks), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 

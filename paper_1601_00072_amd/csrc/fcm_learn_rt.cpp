@@ -3,10 +3,8 @@
 //
 // Everything numeric runs in the kernels of fcm_learn.hip; the host owns the
 // buffers, draws the initial weights and the sample order from a counter
-// generator, and sequences the launches of one training step:
-//   gather the minibatch -> three forward GEMMs (bias and ReLU fused) ->
-//   loss and dL/dy -> backward GEMMs (ReLU masks fused) and bias column sums
-//   -> Adam over the flat parameter vector.
+// generator, and enqueues two launches per training step: the rows' forward
+// and backward passes, then the gradients with Adam's update.
 
 #include <hip/hip_runtime.h>
 
@@ -82,8 +80,7 @@ struct fcm_mlp {
 
     // training workspace, `cap` rows
     int cap = 0;
-    float *Xb = nullptr, *Tb = nullptr, *h1 = nullptr, *h2 = nullptr, *y = nullptr, *dy = nullptr,
-          *dz2 = nullptr, *dz1 = nullptr;
+    float *h1 = nullptr, *h2 = nullptr, *d = nullptr, *dy = nullptr, *dz2 = nullptr, *dz1 = nullptr;
     float* losses = nullptr;  // per-step losses of one epoch
     int64_t loss_cap = 0;
     int32_t* idx = nullptr;   // sample order of one epoch
@@ -100,9 +97,8 @@ void free_ptr(void* p) {
 
 void mlp_release(fcm_mlp* n) {
     if (!n) return;
-    for (void* p : {(void*)n->theta, (void*)n->grad, (void*)n->am, (void*)n->av, (void*)n->wb, (void*)n->Xb,
-                    (void*)n->Tb, (void*)n->h1, (void*)n->h2, (void*)n->y, (void*)n->dy, (void*)n->dz2,
-                    (void*)n->dz1, (void*)n->losses, (void*)n->idx, (void*)n->ybuf})
+    for (void* p : {(void*)n->theta, (void*)n->grad, (void*)n->am, (void*)n->av, (void*)n->wb, (void*)n->h1,
+                    (void*)n->h2, (void*)n->d, (void*)n->dy, (void*)n->dz2, (void*)n->dz1, (void*)n->losses, (void*)n->idx, (void*)n->ybuf})
         free_ptr(p);
     delete n;
 }
@@ -122,17 +118,15 @@ int grow(T*& p, int64_t& cap, int64_t want, hipStream_t s) {
 int ensure_rows(fcm_mlp* n, int rows) {
     if (rows <= n->cap) return FCM_OK;
     FCM_HIP(hipStreamSynchronize(n->stream));
-    for (float** p : {&n->Xb, &n->Tb, &n->h1, &n->h2, &n->y, &n->dy, &n->dz2, &n->dz1}) {
+    for (float** p : {&n->h1, &n->h2, &n->d, &n->dy, &n->dz2, &n->dz1}) {
         free_ptr(*p);
         *p = nullptr;
     }
     n->cap = 0;
     const size_t r = (size_t)rows;
-    if (hipMalloc(&n->Xb, sizeof(float) * r * kIn) != hipSuccess) return FCM_ENOMEM;
-    if (hipMalloc(&n->Tb, sizeof(float) * r * n->C) != hipSuccess) return FCM_ENOMEM;
     if (hipMalloc(&n->h1, sizeof(float) * r * kH1) != hipSuccess) return FCM_ENOMEM;
     if (hipMalloc(&n->h2, sizeof(float) * r * kH2) != hipSuccess) return FCM_ENOMEM;
-    if (hipMalloc(&n->y, sizeof(float) * r * n->C) != hipSuccess) return FCM_ENOMEM;
+    if (hipMalloc(&n->d, sizeof(float) * r * n->C) != hipSuccess) return FCM_ENOMEM;
     if (hipMalloc(&n->dy, sizeof(float) * r * n->C) != hipSuccess) return FCM_ENOMEM;
     if (hipMalloc(&n->dz2, sizeof(float) * r * kH2) != hipSuccess) return FCM_ENOMEM;
     if (hipMalloc(&n->dz1, sizeof(float) * r * kH1) != hipSuccess) return FCM_ENOMEM;
@@ -140,35 +134,36 @@ int ensure_rows(fcm_mlp* n, int rows) {
     return FCM_OK;
 }
 
-// FP32 forward of `rows` samples already in Xb: h1, h2, y.
-int forward_f32(fcm_mlp* n, int rows) {
+// One step on `rows` samples of X, T (picked by idx if given).
+int train_step(fcm_mlp* n, const float* X, const float* T, const int32_t* idx, int rows, float* loss, float lr,
+               bool update) {
     const Layout L(n->C);
-    const float* th = n->theta;
-    hipStream_t s = n->stream;
-    FCM_HIP(launch_gemm(false, false, n->Xb, th + L.W1, n->h1, rows, kH1, kIn, th + L.b1, 1, nullptr, s));
-    FCM_HIP(launch_gemm(false, false, n->h1, th + L.W2, n->h2, rows, kH2, kH1, th + L.b2, 1, nullptr, s));
-    FCM_HIP(launch_gemm(false, false, n->h2, th + L.W3, n->y, rows, n->C, kH2, th + L.b3, 0, nullptr, s));
-    return FCM_OK;
-}
-
-// Loss slot and dL/dy from y and Tb, then the gradient into n->grad.  The
-// ReLU derivative is taken from the stored activations (h > 0 exactly where
-// the pre-activation is > 0).
-int backward(fcm_mlp* n, int rows, float* loss_slot) {
-    const Layout L(n->C);
-    const int C = n->C;
-    const float* th = n->theta;
-    float* g = n->grad;
-    hipStream_t s = n->stream;
-    FCM_HIP(launch_mse(n->y, n->Tb, rows * C, 1.0f / (float)(rows * C), n->dy, loss_slot, s));
-    FCM_HIP(launch_gemm(true, false, n->h2, n->dy, g + L.W3, kH2, C, rows, nullptr, 0, nullptr, s));
-    FCM_HIP(launch_colsum(n->dy, rows, C, g + L.b3, s));
-    FCM_HIP(launch_gemm(false, true, n->dy, th + L.W3, n->dz2, rows, kH2, C, nullptr, 0, n->h2, s));
-    FCM_HIP(launch_gemm(true, false, n->h1, n->dz2, g + L.W2, kH1, kH2, rows, nullptr, 0, nullptr, s));
-    FCM_HIP(launch_colsum(n->dz2, rows, kH2, g + L.b2, s));
-    FCM_HIP(launch_gemm(false, true, n->dz2, th + L.W2, n->dz1, rows, kH1, kH2, nullptr, 0, n->h1, s));
-    FCM_HIP(launch_gemm(true, false, n->Xb, n->dz1, g + L.W1, kIn, kH1, rows, nullptr, 0, nullptr, s));
-    FCM_HIP(launch_colsum(n->dz1, rows, kH1, g + L.b1, s));
+    TrainStep a{};
+    a.X = X;
+    a.T = T;
+    a.idx = idx;
+    a.rows = rows;
+    a.C = n->C;
+    a.oW1 = L.W1;
+    a.ob1 = L.b1;
+    a.oW2 = L.W2;
+    a.ob2 = L.b2;
+    a.oW3 = L.W3;
+    a.ob3 = L.b3;
+    a.theta = n->theta;
+    a.m = n->am;
+    a.v = n->av;
+    a.grad = update ? nullptr : n->grad;
+    a.h1 = n->h1;
+    a.h2 = n->h2;
+    a.d = n->d;
+    a.dy = n->dy;
+    a.dz2 = n->dz2;
+    a.dz1 = n->dz1;
+    a.loss = loss;
+    a.scale = 1.0f / (float)(rows * n->C);
+    a.lr = lr;
+    FCM_HIP(launch_train_step(a, update ? ++n->step : 1, n->stream));
     return FCM_OK;
 }
 
@@ -372,11 +367,7 @@ int fcm_mlp_loss_grad(fcm_mlp* n, const float* d_hist, const float* d_target, in
     int rc = ensure_rows(n, count);
     if (rc != FCM_OK) return rc;
     if ((rc = grow(n->losses, n->loss_cap, 1, n->stream)) != FCM_OK) return rc;
-    FCM_HIP(hipMemcpyAsync(n->Xb, d_hist, sizeof(float) * (size_t)count * kIn, hipMemcpyDeviceToDevice, n->stream));
-    FCM_HIP(hipMemcpyAsync(n->Tb, d_target, sizeof(float) * (size_t)count * n->C, hipMemcpyDeviceToDevice,
-                           n->stream));
-    if ((rc = forward_f32(n, count)) != FCM_OK) return rc;
-    if ((rc = backward(n, count, n->losses)) != FCM_OK) return rc;
+    if ((rc = train_step(n, d_hist, d_target, nullptr, count, n->losses, 0.f, false)) != FCM_OK) return rc;
     float l = 0.f;
     FCM_HIP(hipMemcpyAsync(&l, n->losses, sizeof(float), hipMemcpyDeviceToHost, n->stream));
     if (grad) FCM_HIP(hipMemcpyAsync(grad, n->grad, sizeof(float) * (size_t)n->P, hipMemcpyDeviceToHost, n->stream));
@@ -411,11 +402,7 @@ int fcm_mlp_train(fcm_mlp* n, const float* d_hist, const float* d_target, int32_
         for (int64_t b = 0; b < nb; ++b) {
             const int rows = (int)std::min<int64_t>(B, (int64_t)count - b * B);
             const int32_t* ib = n->idx + b * B;
-            FCM_HIP(launch_gather(d_hist, ib, rows, kIn, n->Xb, n->stream));
-            FCM_HIP(launch_gather(d_target, ib, rows, n->C, n->Tb, n->stream));
-            if ((rc = forward_f32(n, rows)) != FCM_OK) return rc;
-            if ((rc = backward(n, rows, n->losses + b)) != FCM_OK) return rc;
-            FCM_HIP(launch_adam(n->theta, n->grad, n->am, n->av, n->P, cfg->lr, ++n->step, n->stream));
+            if ((rc = train_step(n, d_hist, d_target, ib, rows, n->losses + b, cfg->lr, true)) != FCM_OK) return rc;
         }
         FCM_HIP(hipMemcpyAsync(losses.data(), n->losses, sizeof(float) * (size_t)nb, hipMemcpyDeviceToHost,
                                n->stream));
