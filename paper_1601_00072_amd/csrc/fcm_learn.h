@@ -27,7 +27,8 @@ const uint16_t* mlp_bf16_weights(fcm_mlp* net, hipStream_t s, int* rc);
 int histogram_copies(int count);
 hipError_t launch_histogram(const uint8_t* x, const int64_t* d_offsets, int count, int64_t max_n, uint32_t* counts,
                             float* hist, hipStream_t s);
-// the same on counters that are already zero (no memset)
+// the same on counters that are already zero (no memset); whether they have to be
+bool histogram_needs_zero(int count, int64_t max_n);
 hipError_t launch_histogram_counts(const uint8_t* x, const int64_t* d_offsets, int count, int64_t max_n,
                                    uint32_t* counts, float* hist, hipStream_t s);
 // One training step on `rows` samples (rows of X [.][256] and T [.][C] picked

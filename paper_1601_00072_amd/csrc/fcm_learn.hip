@@ -18,52 +18,47 @@
 #include "fcm_internal.h"
 #include "fcm_learn.h"
 #include "fcm_learn_dev.h"
+#include "fcm_level_dev.h"
 
 namespace fcm {
-
-constexpr int kWaveTables = kBlock / 64;
 
 // ---------------------------------------------------------------------------
 // histogram of each instance (integer counts, then normalised to sum 1)
 // ---------------------------------------------------------------------------
 
-// counts layout: [count][copies][256]; block x of instance y adds into copy
-// x % copies (spreads the atomics of one busy level over `copies` addresses)
-__global__ __launch_bounds__(kBlock) void hist_count_kernel(const uint8_t* x, const int64_t* offsets,
-                                                            uint32_t* counts, int copies) {
-    __shared__ uint32_t bins[kWaveTables][256];
+// Block (x, y) counts its share of instance y with one counter column per lane
+// (level_count; 4 tables shared by all lanes of a wave serialised on busy
+// levels: 1,024 slices of 256x256 took 63 us with
+// the normalisation, 23 us so).  A single block per
+// instance writes the totals and the normalised histogram itself; more blocks
+// add into copy x % copies of the instance's counters ([count][copies][256],
+// zero at entry; the copies spread the adds to a busy level).
+__global__ __launch_bounds__(kLvBlock) void hist_count_kernel(const uint8_t* x, const int64_t* offsets,
+                                                              uint32_t* counts, float* hist, int copies) {
+    __shared__ __align__(16) uint32_t tab[256 * 64];
     const int inst = blockIdx.y;
     const int tid = threadIdx.x;
-    uint32_t* mine = bins[tid >> 6];  // one table per wave: fewer same-address conflicts
-    for (int w = 0; w < kWaveTables; ++w) bins[w][tid] = 0u;
-    __syncthreads();
+    level_clear(tab);
     const int64_t b0 = offsets[inst], n = offsets[inst + 1] - b0;
     const uint8_t* xi = x + b0;
     const int64_t lead = (int64_t)((16 - ((uintptr_t)xi & 15)) & 15);
     const int64_t head = n < lead ? n : lead;
     const int64_t nbody = (n - head) / 16;
-    const uint4* body = reinterpret_cast<const uint4*>(xi + head);
-    for (int64_t c = (int64_t)blockIdx.x * kBlock + tid; c < nbody; c += (int64_t)gridDim.x * kBlock) {
-        const uint4 w = body[c];
-        const uint32_t words[4] = {w.x, w.y, w.z, w.w};
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-#pragma unroll
-            for (int b = 0; b < 4; ++b) atomicAdd(&mine[(words[q] >> (8 * b)) & 0xFFu], 1u);
-        }
-    }
-    if (blockIdx.x == 0) {
-        const int64_t tail0 = head + 16 * nbody;
-        const int64_t nr = head + (n - tail0);
-        for (int64_t r = tid; r < nr; r += kBlock) {
-            const int64_t i = r < head ? r : tail0 + (r - head);
-            atomicAdd(&mine[xi[i]], 1u);
-        }
-    }
     __syncthreads();
-    uint32_t c = 0u;
-    for (int w = 0; w < kWaveTables; ++w) c += bins[w][tid];
-    if (c) atomicAdd(counts + ((int64_t)inst * copies + blockIdx.x % copies) * 256 + tid, c);
+    char* t8 = reinterpret_cast<char*>(tab);
+    level_count(t8, reinterpret_cast<const uint4*>(xi + head), (int64_t)blockIdx.x * kLvBlock + tid, nbody,
+                (int64_t)gridDim.x * kLvBlock);
+    if (blockIdx.x == 0) level_ragged(t8, xi, n, head, nbody);
+    __syncthreads();
+    const uint32_t c = level_total(tab);
+    if (tid >= 256) return;
+    uint32_t* ci = counts + (int64_t)inst * copies * 256;
+    if (gridDim.x == 1) {
+        ci[tid] = c;
+        hist[(int64_t)inst * 256 + tid] = hist_norm(c, n);
+    } else if (c) {
+        atomicAdd(ci + (blockIdx.x % copies) * 256 + tid, c);
+    }
 }
 
 // totals of the copies -> copy 0 (integer counts) and count / n (FP64, stored FP32)
@@ -79,32 +74,46 @@ __global__ __launch_bounds__(kBlock) void hist_norm_kernel(uint32_t* counts, con
 
 int histogram_copies(int count) { return count == 1 ? kHistCopies : 1; }
 
-// counting and normalisation on counters that are already zero
+// Blocks per instance: enough that the launch gives every CU two, with 16,384
+// (below that a block's clearing and totals outweigh its count) to 131,072
+// voxels each; a single instance takes at most one per CU (the reads of two
+// are no faster).
+static int hist_blocks(int count, int64_t max_n) {
+    constexpr int64_t kCus = 256, kMin = 16384, kMax = 131072;
+    int64_t share = max_n * count / (2 * kCus);
+    share = share < kMin ? kMin : (share > kMax && count > 1 ? kMax : share);
+    int64_t gx = (max_n + share - 1) / share;
+    if (count == 1 && gx > kCus) gx = kCus;
+    return (int)(gx < 1 ? 1 : (gx > 4096 ? 4096 : gx));
+}
+
+bool histogram_needs_zero(int count, int64_t max_n) { return hist_blocks(count, max_n) > 1; }
+
+// counting and normalisation on counters that are already zero (where that is needed)
 hipError_t launch_histogram_counts(const uint8_t* x, const int64_t* d_offsets, int count, int64_t max_n,
                                    uint32_t* counts, float* hist, hipStream_t s) {
     const int copies = histogram_copies(count);
     hipError_t e;
-    const int64_t chunks = (max_n + 15) / 16;
-    const int64_t cap = count == 1 ? 1024 : 64;  // a single instance may use the whole device
-    int64_t gx64 = (chunks + kBlock * 16 - 1) / (kBlock * 16);
-    gx64 = gx64 < 1 ? 1 : (gx64 > cap ? cap : gx64);
-    const int gx = (int)gx64;
+    const int gx = hist_blocks(count, max_n);
     constexpr int kMaxY = 65535;  // grid y limit: instances per launch
     for (int c0 = 0; c0 < count; c0 += kMaxY) {
         const int cnt = count - c0 < kMaxY ? count - c0 : kMaxY;
-        hipLaunchKernelGGL(hist_count_kernel, dim3(gx, cnt), dim3(kBlock), 0, s, x, d_offsets + c0,
-                           counts + (int64_t)c0 * copies * 256, copies);
+        hipLaunchKernelGGL(hist_count_kernel, dim3(gx, cnt), dim3(kLvBlock), 0, s, x, d_offsets + c0,
+                           counts + (int64_t)c0 * copies * 256, hist + (int64_t)c0 * 256, copies);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
+    if (gx == 1) return hipSuccess;
     hipLaunchKernelGGL(hist_norm_kernel, dim3(count), dim3(256), 0, s, counts, d_offsets, hist, copies);
     return hipGetLastError();
 }
 
 hipError_t launch_histogram(const uint8_t* x, const int64_t* d_offsets, int count, int64_t max_n, uint32_t* counts,
                             float* hist, hipStream_t s) {
-    const int copies = histogram_copies(count);
-    hipError_t e = hipMemsetAsync(counts, 0, sizeof(uint32_t) * 256 * (size_t)count * copies, s);
-    if (e != hipSuccess) return e;
+    if (histogram_needs_zero(count, max_n)) {
+        const int64_t words = 256 * (int64_t)count * histogram_copies(count);
+        hipError_t e = hipMemsetAsync(counts, 0, sizeof(uint32_t) * (size_t)words, s);
+        if (e != hipSuccess) return e;
+    }
     return launch_histogram_counts(x, d_offsets, count, max_n, counts, hist, s);
 }
 
@@ -459,27 +468,95 @@ __global__ __launch_bounds__(256) void mlp_infer_kernel(const void* w, const flo
     mlp_block_forward<BF16>(w, X + s * 256, C, a0, a1, a2, tmp, Y + s * C);
 }
 
+// The BF16 network on kInferRows histograms per block: the arithmetic and its
+// order are mlp_block_forward's, but a block reads the weights (83 KB) once for
+// all of them.
+constexpr int kInferRows = 4;
+
+__global__ __launch_bounds__(256) void mlp_infer_rows_kernel(const uint16_t* w, const float* X, int count, int C,
+                                                             float* Y) {
+    using L = InferLayout;
+    __shared__ float a0[kInferRows][256], a1[kInferRows][128], a2[kInferRows][64], tmp[kInferRows][256];
+    const int t = threadIdx.x;
+    const int64_t s0 = (int64_t)blockIdx.x * kInferRows;
+    const int m = count - s0 < kInferRows ? (int)(count - s0) : kInferRows;
+#pragma unroll
+    for (int h = 0; h < kInferRows; ++h) a0[h][t] = h < m ? act<true>(X[(s0 + h) * 256 + t]) : 0.f;
+    uint4 w2[16], w3[8];
+    if (t < 64) load_bf16<16>(w + L::W2 + t * 128, w2);
+    if (t < C) load_bf16<8>(w + L::W3 + t * 64, w3);
+    __syncthreads();
+    const int o = t & 127, half = t >> 7;
+    float z[kInferRows];
+#pragma unroll
+    for (int h = 0; h < kInferRows; ++h) z[h] = half ? 0.f : from_bf16(w[L::b1 + o]);
+#pragma unroll
+    for (int c = 0; c < 128; c += 64) {
+        uint4 q[8];
+        load_bf16<8>(w + L::W1 + o * 256 + 128 * half + c, q);
+#pragma unroll
+        for (int h = 0; h < kInferRows; ++h) z[h] = dot_bf16_regs<8>(z[h], a0[h] + 128 * half + c, q);
+    }
+#pragma unroll
+    for (int h = 0; h < kInferRows; ++h) tmp[h][t] = z[h];
+    __syncthreads();
+    for (int e = t; e < kInferRows * 128; e += 256) {
+        const int h = e >> 7, u = e & 127;
+        a1[h][u] = act<true>(fmaxf(tmp[h][u] + tmp[h][u + 128], 0.f));
+    }
+    __syncthreads();
+    if (t < 64)
+#pragma unroll
+        for (int h = 0; h < kInferRows; ++h)
+            a2[h][t] = act<true>(fmaxf(dot_bf16_regs<16>(from_bf16(w[L::b2 + t]), a1[h], w2), 0.f));
+    __syncthreads();
+    if (t < C)
+#pragma unroll
+        for (int h = 0; h < kInferRows; ++h)
+            if (h < m) Y[(s0 + h) * C + t] = dot_bf16_regs<8>(from_bf16(w[L::b3(C) + t]), a2[h], w3);
+}
+
+// Several histograms per block from the count on that still gives every second
+// CU a block (1,024 histograms: 19 us one per block, 12 us four per block).
 hipError_t launch_mlp_infer(const void* w, bool bf16, const float* X, int count, int C, float* Y, hipStream_t s) {
-    if (bf16)
+    if (bf16 && count >= 128 * kInferRows)
+        hipLaunchKernelGGL(mlp_infer_rows_kernel, dim3((count + kInferRows - 1) / kInferRows), dim3(256), 0, s,
+                           static_cast<const uint16_t*>(w), X, count, C, Y);
+    else if (bf16)
         hipLaunchKernelGGL(mlp_infer_kernel<true>, dim3(count), dim3(256), 0, s, w, X, C, Y);
     else
         hipLaunchKernelGGL(mlp_infer_kernel<false>, dim3(count), dim3(256), 0, s, w, X, C, Y);
     return hipGetLastError();
 }
 
-// Network output -> start centroids, one thread per instance (warm_post_one).
-__global__ void warm_post_kernel(const float* Y, const float* hist, int count, int C, double* v0) {
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
+// Network output -> start centroids (warm_post_one), one wave per instance:
+// its lanes look at four levels each for the range (one thread that walked
+// the levels waited for a load per empty level: 13 us for 1,024 instances, 5 us
+// so).
+__global__ __launch_bounds__(256) void warm_post_kernel(const float* Y, const float* hist, int count, int C,
+                                                        double* v0) {
+    const int s = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (s >= count) return;
     const float* h = hist + (int64_t)s * 256;
-    int lo = 0, hi = 255;
-    while (lo < 255 && !(h[lo] > 0.f)) ++lo;
-    while (hi > 0 && !(h[hi] > 0.f)) --hi;
-    warm_post_one(Y + (int64_t)s * C, lo, hi, C, v0 + (int64_t)s * C);
+    float v[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) v[q] = h[64 * q + lane];
+    int lo = 255, hi = 0;  // what a walk over no positive level ends with
+#pragma unroll
+    for (int q = 3; q >= 0; --q) {
+        const uint64_t m = __ballot(v[q] > 0.f);
+        if (m) lo = 64 * q + __builtin_ctzll(m);
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const uint64_t m = __ballot(v[q] > 0.f);
+        if (m) hi = 64 * q + 63 - __builtin_clzll(m);
+    }
+    if (lane == 0) warm_post_one(Y + (int64_t)s * C, lo, hi, C, v0 + (int64_t)s * C);
 }
 
 hipError_t launch_warm_post(const float* Y, const float* hist, int count, int C, double* v0, hipStream_t s) {
-    hipLaunchKernelGGL(warm_post_kernel, dim3((count + 127) / 128), dim3(128), 0, s, Y, hist, count, C, v0);
+    hipLaunchKernelGGL(warm_post_kernel, dim3((count + 3) / 4), dim3(256), 0, s, Y, hist, count, C, v0);
     return hipGetLastError();
 }
 
@@ -549,12 +626,14 @@ extern "C" int fcm_histogram_noalloc(const uint8_t* d_x, const int64_t* offsets,
     hipStream_t s = (hipStream_t)stream;
     int64_t* d_off = reinterpret_cast<int64_t*>(base);
     uint32_t* d_counts = reinterpret_cast<uint32_t*>(static_cast<unsigned char*>(base) + kNoAllocOffBytes);
-    const int64_t words = 256 * (int64_t)count * histogram_copies(count);
     FCM_HIP(hipMemcpyAsync(d_off, offsets, sizeof(int64_t) * ((size_t)count + 1), hipMemcpyHostToDevice, s));
-    // the array keeps the previous call's counts: clear them (a kernel, no memset node)
-    const int zgrid = (int)((words + kBlock - 1) / kBlock < 1024 ? (words + kBlock - 1) / kBlock : 1024);
-    hipLaunchKernelGGL(zero_words_kernel, dim3(zgrid), dim3(kBlock), 0, s, d_counts, words);
-    FCM_HIP(hipGetLastError());
+    if (histogram_needs_zero(count, max_n)) {
+        // the array keeps the previous call's counts: clear them (a kernel, no memset node)
+        const int64_t words = 256 * (int64_t)count * histogram_copies(count);
+        const int zgrid = (int)((words + kBlock - 1) / kBlock < 1024 ? (words + kBlock - 1) / kBlock : 1024);
+        hipLaunchKernelGGL(zero_words_kernel, dim3(zgrid), dim3(kBlock), 0, s, d_counts, words);
+        FCM_HIP(hipGetLastError());
+    }
     FCM_HIP(launch_histogram_counts(d_x, d_off, count, max_n, d_counts, d_hist, s));
     FCM_HIP(hipStreamSynchronize(s));
     return FCM_OK;

@@ -433,19 +433,16 @@ int fcm_histogram(const uint8_t* d_x, const int64_t* offsets, int32_t count, flo
     }
     if (max_n > (int64_t)UINT32_MAX) return FCM_EINVAL;
     hipStream_t s = (hipStream_t)stream;
-    int64_t* d_off = nullptr;
+    // one temporary: the counters, then the offsets
+    const size_t b_counts = sizeof(uint32_t) * 256 * (size_t)count * histogram_copies(count);
     uint32_t* d_counts = nullptr;
-    if (hipMalloc(&d_off, sizeof(int64_t) * ((size_t)count + 1)) != hipSuccess) return FCM_ENOMEM;
-    if (hipMalloc(&d_counts, sizeof(uint32_t) * 256 * (size_t)count * histogram_copies(count)) != hipSuccess) {
-        (void)hipFree(d_off);
-        return FCM_ENOMEM;
-    }
+    if (hipMalloc(&d_counts, b_counts + sizeof(int64_t) * ((size_t)count + 1)) != hipSuccess) return FCM_ENOMEM;
+    int64_t* d_off = reinterpret_cast<int64_t*>(reinterpret_cast<char*>(d_counts) + b_counts);
     int rc = FCM_OK;
     hipError_t e = hipMemcpyAsync(d_off, offsets, sizeof(int64_t) * ((size_t)count + 1), hipMemcpyHostToDevice, s);
     if (e == hipSuccess) e = launch_histogram(d_x, d_off, count, max_n, d_counts, d_hist, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) rc = dev_err(e, "fcm_histogram");
-    (void)hipFree(d_off);
     (void)hipFree(d_counts);
     return rc;
 }

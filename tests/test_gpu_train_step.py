@@ -44,3 +44,40 @@ def test_rows(rows, C):
     clear = np.abs(ref) > 1e-5
     moved = after.astype(np.float64) - theta
     assert np.max(np.abs(moved[clear] + 1e-3 * np.sign(ref[clear]))) <= 1e-3 * 2e-3
+
+
+@pytest.mark.parametrize("sizes", [[1], [16384], [16385], [5, 70000, 131072, 1], [4096] * 600, [40000] * 70])
+def test_histogram_splits(sizes):
+    """Counts of one and of several blocks per instance, against numpy."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.fail("no GPU visible")
+    from paper_1601_00072_amd import histogram
+    print("CASE histogram", len(sizes), sizes[:4], flush=True)
+    rng = np.random.default_rng(len(sizes))
+    x = rng.integers(0, 256, sum(sizes) + 3, dtype=np.uint8)
+    x[: x.size // 2] = 0
+    got = histogram(torch.from_numpy(x).to("cuda:0")[3:], sizes).cpu().numpy()
+    off = 3
+    for g, n in zip(got, sizes):
+        want = np.bincount(x[off:off + n], minlength=256).astype(np.float64) / n
+        assert np.array_equal(g, want.astype(np.float32))
+        off += n
+
+
+@pytest.mark.parametrize("count", [1, 511, 512, 513, 515])
+def test_inference_splits(count):
+    """One and four histograms per block give the same bits, row by row."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.fail("no GPU visible")
+    from paper_1601_00072_amd import MLP
+    print("CASE inference count", count, flush=True)
+    h = torch.rand(count, 256, device="cuda:0")
+    h[:, 200:] = 0
+    h /= h.sum(dim=1, keepdim=True)
+    with MLP(4, seed=2) as net:
+        y = net.forward(h, bf16=True)
+        for i in {0, count // 2, count - 1}:
+            assert torch.equal(y[i:i + 1], net.forward(h[i:i + 1], bf16=True))
+            assert torch.equal(net.warm_centroids(h)[i], net.warm_centroids(h[i:i + 1])[0])
