@@ -44,6 +44,16 @@ def _result(r: L.FcmResult) -> Result:
                   lo=r.lo, hi=r.hi)
 
 
+def _results(out) -> list:
+    """Results of an array of FcmResult records, read column by column (a
+    field at a time through ctypes costs more than a batched solve)."""
+    a = np.ctypeslib.as_array(out)
+    cols = [a[f].tolist() for f in ("iters", "passes", "status", "delta", "J")]
+    v = [row[:c] for row, c in zip(a["centroids"].copy(), a["n_clusters"].tolist())]
+    tail = [a[f].tolist() for f in ("kernel_ms", "lo", "hi")]
+    return [Result(*q) for q in zip(*cols, v, *tail)]
+
+
 def _stream_handle(stream, device):
     import torch
     if stream is None:
@@ -303,7 +313,7 @@ class FCMBatch:
         rc = self._lib.fcm_batch_solve(self._h, out)
         if rc < 0 and rc != L.FCM_ENUMERIC:
             raise FcmError(rc, "fcm_batch_solve")
-        return [_result(r) for r in out]
+        return _results(out)
 
     def autotune(self, cache: str | None = None, reps: int = 2):
         """Pick the block size, tile size and grid (see fcm_batch_autotune);
@@ -340,8 +350,7 @@ class FCMBatch:
         rc = self._lib.fcm_batch_solve_warm(self._h, net._h, 1 if check else 0, out, plain, used)
         if rc < 0 and rc != L.FCM_ENUMERIC:
             raise FcmError(rc, "fcm_batch_solve_warm")
-        return ([_result(r) for r in out], np.array(used[:], dtype=bool),
-                None if plain is None else [_result(r) for r in plain])
+        return (_results(out), np.array(used[:], dtype=bool), None if plain is None else _results(plain))
 
     def targets(self, C: int, out=None):
         """Network training targets of the last solve (fcm_batch_targets):

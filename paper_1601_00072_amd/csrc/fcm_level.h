@@ -17,7 +17,8 @@ struct LevelArgs {
     const uint8_t* x;
     int64_t n, head, nbody;
     DevState* st;
-    DevState* host;          // pinned copy of the state's result fields, for the host to read after a wait
+    DevState* host;          // pinned copy of the state's result fields, for the host to read after a wait;
+                             // its ticket becomes `seq` once the others are written
     uint32_t* counts;        // [kLvCopies][256] counters, zero at entry and at the end of every launch
     double* hist_v;
     double* hist_d;
@@ -28,7 +29,7 @@ struct LevelArgs {
     int32_t given;           // start mode: 0 evenly spaced, 1 v0 below, 2 dv0 (device), 3 learned (mlp_w)
     int32_t max_passes;      // passes this launch may run
     int32_t fp32_range;      // report starts whose FP32 distances overflow as non-finite
-    int32_t pad;
+    uint32_t seq;
     double v0[kMaxC];
     const double* dv0;
     const uint16_t* mlp_w;

@@ -11,6 +11,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <chrono>
 #include <cmath>
 #include <cstdint>
 #include <cstddef>
@@ -115,6 +116,7 @@ struct fcm_handle {
     double* d_hist = nullptr;      // v: (max_iter + 2) * C, then delta, then J: (max_iter + 2) each
     DevState* h_state = nullptr;   // pinned: [0] the host's view, [1] written by the level solve itself
     bool mirrored = false;         // h_state[1] holds the state that the last launch left
+    uint32_t seq = 0;              // its number: h_state[1].ticket once that launch has written its result
 
     fcm_tuning tun{};
     int grid = 1;               // resolved grid of the current driver
@@ -268,9 +270,37 @@ int build_graph(fcm_handle* h) {
     return FCM_OK;
 }
 
-int read_state(fcm_handle* h) {
+// Wait for the level launch that has just been enqueued, with nothing behind
+// it.  Its result is in host memory some microseconds before the runtime
+// reports the stream idle (256x256 pixels, solve and labels: 32 us waiting for
+// the stream, 27 for the result), so look for the launch's number there first;
+// a launch that takes longer (queued behind other work) is waited for on the
+// stream.
+int wait_own_launch(fcm_handle* h) {
+    if (!(h->p.flags & FCM_F_TIMING)) {  // timed launches need their events
+        const uint32_t* at = &h->h_state[1].ticket;
+        const auto until = std::chrono::steady_clock::now() + std::chrono::microseconds(200);
+        do {
+            for (int i = 0; i < 64; ++i) {
+                if (__atomic_load_n(at, __ATOMIC_ACQUIRE) == h->seq) return FCM_OK;
+                __builtin_ia32_pause();
+            }
+        } while (std::chrono::steady_clock::now() < until);
+    }
+    FCM_HIP(hipStreamSynchronize(h->stream));
+    return FCM_OK;
+}
+
+// State as of the work enqueued so far; waits for the stream, or (own_launch)
+// for the level launch just enqueued.
+int read_state(fcm_handle* h, bool own_launch = false) {
     if (h->mirrored) {  // the launch itself left its result in host memory
-        FCM_HIP(hipStreamSynchronize(h->stream));
+        if (own_launch) {
+            int rc = wait_own_launch(h);
+            if (rc != FCM_OK) return rc;
+        } else {
+            FCM_HIP(hipStreamSynchronize(h->stream));
+        }
         const DevState& m = h->h_state[1];
         std::memcpy(h->h_state, &m, offsetof(DevState, sync));
         h->h_state->sync.passes_total = m.sync.passes_total;
@@ -359,6 +389,7 @@ int enqueue_levels(fcm_handle* h, int max_passes) {
     for (int k = 0; k < kMaxC; ++k) a.v0[k] = h->given[k];
     a.dv0 = h->dv0;
     a.mlp_w = h->mlp_w;
+    a.seq = ++h->seq;
     hipError_t e = launch_levels(a, h->p.n_clusters, h->mclass, level_grid(h), h->stream);
     if (e != hipSuccess) return dev_err(e, "launch_levels");
     h->pending_init = false;
@@ -435,7 +466,7 @@ int run_batch(fcm_handle* h, int batch) {
         }
         if ((rc = enqueue_levels(h, batch)) != FCM_OK) return rc;
         if (timing) FCM_HIP(hipEventRecord(h->ev[1], h->stream));
-        if ((rc = read_state(h)) != FCM_OK) return rc;
+        if ((rc = read_state(h, true)) != FCM_OK) return rc;
         if (timing) {
             float ms = 0.f;
             FCM_HIP(hipEventElapsedTime(&ms, h->ev[0], h->ev[1]));
