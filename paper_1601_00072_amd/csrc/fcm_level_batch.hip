@@ -73,9 +73,10 @@ __global__ __launch_bounds__(kLvBlock, 4) void fcm_level_batch_kernel(LevelBatch
         }
         __syncthreads();
         if (tid == 0) {
+            // as in the single solve: released, and read with atomic loads
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
             const uint32_t prev =
-                __hip_atomic_fetch_add(a.ticket + i, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_fetch_add(a.ticket + i, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             s_last = prev == (uint32_t)nt - 1u;
         }
         __syncthreads();

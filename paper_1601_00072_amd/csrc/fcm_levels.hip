@@ -72,8 +72,14 @@ __global__ __launch_bounds__(kLvBlock, LEARNED ? 2 : 4) void fcm_level_kernel(Le
         }
         __syncthreads();
         if (tid == 0) {
+            // the block's adds have been performed; the release orders them
+            // before its arrival.  No acquire on the other side: what the last
+            // block reads of the others are the counters, with atomic loads
+            // issued after this add's value is known, which are served where
+            // the adds were performed (an acquire invalidates the XCD's L2).
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-            const uint32_t prev = __hip_atomic_fetch_add(&st->ticket, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+            const uint32_t prev =
+                __hip_atomic_fetch_add(&st->ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             s_last = prev == (uint32_t)G - 1u;
         }
         __syncthreads();
