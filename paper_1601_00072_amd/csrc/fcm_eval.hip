@@ -30,10 +30,14 @@ __global__ __launch_bounds__(kBlock) void zero_counts_kernel(unsigned long long*
 }
 
 // Counting tables.  Few class pairs (the usual case: C clusters against a
-// handful of tissues): every thread owns a column of counters, bin-major
-// [kSmallBins + 1][kBlock], so the 64 lanes of a wave touch 64 distinct
-// words (no bank conflicts, no contended atomics) whatever the labels are.  More pairs:
-// one shared table per wave, updated with LDS atomics.
+// handful of tissues): every lane of a wave owns a column of counters,
+// bin-major [kSmallBins + 1][64], shared by the block's waves, so the 64 lanes
+// touch 64 distinct words (no bank conflicts, no contended adds in a wave)
+// whatever the labels are; and four voxels are taken at a time as long as all
+// their labels are in range: their bins are the bytes of one product and one
+// sum.  512x512x256 voxels: 35 us with a column per thread and a voxel at a
+// time, 33.8 us so (the reads alone take 30).  More pairs: one shared table per wave, updated with LDS
+// atomics.
 constexpr int kSmallBins = 32;
 
 template <bool SMALL>
@@ -41,12 +45,17 @@ struct Tables;
 
 template <>
 struct Tables<true> {
-    uint32_t t[kSmallBins + 1][kBlock];
+    uint32_t t[kSmallBins + 1][64];
     __device__ __forceinline__ void clear(int tid) {
-        for (int b = 0; b <= kSmallBins; ++b) t[b][tid] = 0u;
+        for (int i = tid; i < (kSmallBins + 1) * 64; i += kBlock) t[0][i] = 0u;
     }
     // LDS add without return: no read-after-write wait between voxels
-    __device__ __forceinline__ void add(int tid, uint32_t bin) { atomicAdd(&t[bin][tid], 1u); }
+    __device__ __forceinline__ void add(int tid, uint32_t bin) { atomicAdd(&t[bin][tid & 63], 1u); }
+    __device__ __forceinline__ void bump(uint32_t off) {
+        char* at = reinterpret_cast<char*>(&t[0][0]) + off;  // off is a multiple of 4
+        __hip_atomic_fetch_add(reinterpret_cast<uint32_t*>(__builtin_assume_aligned(at, 4)), 1u, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
     static constexpr uint32_t kOut = kSmallBins;
 };
 
@@ -68,6 +77,28 @@ __device__ __forceinline__ void count_pair(Tables<SMALL>& tab, int tid, uint32_t
                                            uint32_t nt) {
     // labels are bytes and nt <= 16: the 24-bit multiply (full rate) is exact
     tab.add(tid, (p < np && t < nt) ? __umul24(p, nt) + t : Tables<SMALL>::kOut);
+}
+
+// Four voxels, one byte each in p and t.
+template <bool SMALL>
+__device__ __forceinline__ void count_word(Tables<SMALL>& tab, int tid, uint32_t p, uint32_t t, uint32_t np,
+                                           uint32_t nt) {
+    if constexpr (SMALL) {
+        // byte + (128 - limit) reaches 128 exactly where byte >= limit (bytes
+        // of 128 and more are caught by themselves)
+        const uint32_t over = ((p + (128u - np) * 0x01010101u) | p | (t + (128u - nt) * 0x01010101u) | t) & 0x80808080u;
+        if (over == 0u) {
+            const uint32_t w = p * nt + t;  // every byte < np nt <= 32: no carries
+            const uint32_t lane4 = ((uint32_t)tid & 63u) << 2;
+            tab.bump(((w << 8) & 0xFF00u) | lane4);
+            tab.bump((w & 0xFF00u) | lane4);
+            tab.bump(((w >> 8) & 0xFF00u) | lane4);
+            tab.bump(((w >> 16) & 0xFF00u) | lane4);
+            return;
+        }
+    }
+#pragma unroll
+    for (int b = 0; b < 4; ++b) count_pair(tab, tid, (p >> (8 * b)) & 0xFFu, (t >> (8 * b)) & 0xFFu, np, nt);
 }
 
 __device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v) {
@@ -109,11 +140,7 @@ __global__ __launch_bounds__(kBlock) void confusion_kernel(const uint8_t* pred, 
                 const uint32_t pv[4] = {pw[u].x, pw[u].y, pw[u].z, pw[u].w};
                 const uint32_t tv[4] = {tw[u].x, tw[u].y, tw[u].z, tw[u].w};
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-#pragma unroll
-                    for (int b = 0; b < 4; ++b)
-                        count_pair(tab, tid, (pv[q] >> (8 * b)) & 0xFFu, (tv[q] >> (8 * b)) & 0xFFu, np, nt);
-                }
+                for (int q = 0; q < 4; ++q) count_word(tab, tid, pv[q], tv[q], np, nt);
             }
         }
     }
@@ -127,16 +154,14 @@ __global__ __launch_bounds__(kBlock) void confusion_kernel(const uint8_t* pred, 
     __syncthreads();
     const int used = (int)(np * nt);
     if constexpr (SMALL) {
-        // wave w folds bins w, w + 4, ...: four columns per lane, then the
-        // wave; the totals go out as one atomic instruction per block (one
+        // wave w folds bins w, w + 4, ...; the totals go out as one atomic instruction per block (one
         // request per cache line of counters: the blocks' atomics on the same
         // few lines serialise, so their number is what costs)
         __shared__ uint32_t s_tot[kSmallBins + 1];
         const int lane = tid & 63, wid = tid >> 6;
         for (int b = wid; b <= used; b += kTables) {
             const int row = b == used ? kSmallBins : b;
-            uint32_t v = tab.t[row][lane] + tab.t[row][lane + 64] + tab.t[row][lane + 128] + tab.t[row][lane + 192];
-            v = wave_sum_u32(v);
+            const uint32_t v = wave_sum_u32(tab.t[row][lane]);
             if (lane == 0) s_tot[b] = v;
         }
         __syncthreads();

@@ -580,8 +580,8 @@ int ensure_level_ws(fcm_handle* h) {
 // wait was aborted, which clears it together with the tagged row buffers.
 int enqueue_start(fcm_handle* h) {
     if (h->aborted) {
-        FCM_HIP(hipMemsetAsync(h->d_state, 0, sizeof(DevState), h->stream));
-        FCM_HIP(hipMemsetAsync(h->d_lcounts, 0, sizeof(uint32_t) * 256 * kLvCopies, h->stream));
+        // the state and the level counters lie next to each other in the arena
+        FCM_HIP(hipMemsetAsync(h->d_state, 0, (size_t)((char*)h->d_minmax - (char*)h->d_state), h->stream));
         if (h->d_mmrows) {
             FCM_HIP(hipMemsetAsync(h->d_rows, 0, sizeof(uint64_t) * 2 * kMaxPersistGrid * kTaggedStrideMax,
                                    h->stream));
