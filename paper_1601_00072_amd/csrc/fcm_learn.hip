@@ -124,106 +124,158 @@ hipError_t launch_histogram(const uint8_t* x, const int64_t* d_offsets, int coun
 // A step is 63 MFLOP at the usual 256 rows: launches, and inside them the
 // latency of reading what another XCD has just written (about 1 us), bound
 // it, not arithmetic (one kernel per product, bias, loss and update took 14
-// launches and 100 us per step; these two take 20 us, 11 + 9).  So each block issues
-// all its reads at once, as 16-byte loads into registers, and passes them
-// through LDS.  The first launch does what a row needs by itself -- forward,
-// loss derivative, the backward pass to both hidden layers -- for kTrainRows
-// rows per block; the second forms every gradient as a sum over the rows and
-// updates its parameter at once.  Every output is one FP32 chain of fused
-// multiply-adds over its inner index in increasing order (rows in batch order
-// for the gradients), whatever block computes it, so results do not depend on
-// the split.
+// launches and 100 us per step).  So each block issues all its reads at once,
+// as 16-byte loads into registers, and multiplies the wide operand there: a
+// thread holds four columns of every 8th (128 columns) or 16th row, the
+// narrow operand is broadcast from LDS, and the partial sums of the row
+// groups meet in two half-wave exchanges and one LDS add over the four waves.
+// Passing the wide operand through LDS instead, one chain per output, took
+// 10.9 us for the first launch and 8.75 us for the second; 6.2 and 6.3 us so.
+// The first launch does what a row needs by itself -- forward, loss
+// derivative, the backward pass to both hidden layers -- for kTrainRows rows
+// per block; the second forms every gradient as a sum over the rows and
+// updates its parameter at once.  Every output is a fixed tree of FP32 chains
+// of fused multiply-adds over its inner index, whatever block computes it, so
+// results do not depend on the split.
 
 typedef float vec4 __attribute__((ext_vector_type(4)));
 
 constexpr int kTrainRows = 2;   // rows per block: 128 blocks for the usual batch, each reads W1 once (128 KB)
 constexpr int kTileK1 = 4;      // rows of W1 per block of the second launch
 constexpr int kTileK2 = 8;      // rows of W2 per block
-constexpr int kRowChunk = 128;  // rows of the batch staged at a time
+constexpr int kRowChunk = 128;  // rows of the batch read at a time
 constexpr int kColTile = 16, kRowGroups = 16;  // bias sums
 
 __device__ __forceinline__ int64_t train_row(const TrainStep& a, int i) { return a.idx ? (int64_t)a.idx[i] : i; }
 
+// (a, b) -> the sums of a over lanes l and l + 32 in the lower half of the
+// wave, of b in the upper half.
+__device__ __forceinline__ float half_add(float a, float b) {
+    const auto p = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, b),
+                                                    false, false);
+    return __builtin_bit_cast(float, (uint32_t)p[0]) + __builtin_bit_cast(float, (uint32_t)p[1]);
+}
+
+// The same between rows of 16 lanes: a's sums in rows 0 and 2, b's in 1 and 3.
+__device__ __forceinline__ float row_add(float a, float b) {
+    const auto p = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, b),
+                                                    false, false);
+    return __builtin_bit_cast(float, (uint32_t)p[0]) + __builtin_bit_cast(float, (uint32_t)p[1]);
+}
+
+__device__ __forceinline__ vec4 half_add(vec4 a, vec4 b) {
+    return vec4{half_add(a.x, b.x), half_add(a.y, b.y), half_add(a.z, b.z), half_add(a.w, b.w)};
+}
+__device__ __forceinline__ vec4 row_add(vec4 a, vec4 b) {
+    return vec4{row_add(a.x, b.x), row_add(a.y, b.y), row_add(a.z, b.z), row_add(a.w, b.w)};
+}
+
+template <int CTRL>
+__device__ __forceinline__ float dpp_f32(float v) {
+    return __builtin_bit_cast(
+        float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, false));
+}
+constexpr int kDppMirror = 0x140, kDppHalfMirror = 0x141, kDppXor2 = 0x4E, kDppXor1 = 0xB1;
+
+__device__ __forceinline__ vec4 fma4(float s, vec4 q, vec4 z) {
+    return vec4{fmaf(s, q.x, z.x), fmaf(s, q.y, z.y), fmaf(s, q.z, z.z), fmaf(s, q.w, z.w)};
+}
+
 __global__ __launch_bounds__(256) void train_rows_kernel(TrainStep a) {
-    __shared__ __align__(16) float W1s[128 * 128];  // one half of W1 at a time
-    __shared__ float W2s[128][65], W3s[64 * kMaxC];
-    __shared__ float Xs[kTrainRows][256], h1s[kTrainRows][128], h2s[kTrainRows][64], dz2s[kTrainRows][64];
-    __shared__ float dys[kTrainRows][kMaxC];
-    const int t = threadIdx.x, C = a.C;
+    // inner index k of a layer's input at [k mod groups][k div groups]: a
+    // thread's rows of the weights are consecutive
+    __shared__ __align__(16) float Xs[kTrainRows][8][36], h1s[kTrainRows][16][8];
+    __shared__ __align__(16) float part[4][kTrainRows][128];
+    __shared__ __align__(16) float h2s[kTrainRows][64], dz2s[kTrainRows][64];
+    __shared__ float W3s[64 * kMaxC], dys[kTrainRows][kMaxC];
+    static_assert(kTrainRows == 2, "the half-wave exchange takes one row per half");
+    const int t = threadIdx.x, C = a.C, lane = t & 63, w = t >> 6;
     const int row0 = blockIdx.x * kTrainRows;
     const int nr = a.rows - row0 < kTrainRows ? a.rows - row0 : kTrainRows;
     const float* th = a.theta;
+    const int u1 = t & 127, r1 = t >> 7;       // (row, unit) of the first hidden layer
+    const int u2 = t & 63, r2 = (t >> 6) & 1;  // of the second (threads below 128)
+    const int l16 = t & 15, o3 = t >> 4;       // 16 lanes per output of the last layer
+    const int r3 = o3 / C, c3 = o3 - r3 * C;
+    const bool out3 = r3 < nr;
     // every read of the block, in flight together
     const vec4* w1 = reinterpret_cast<const vec4*>(th + a.oW1);
     const vec4* w2 = reinterpret_cast<const vec4*>(th + a.oW2);
-    vec4 qa[16], qb[16], q2[8];
+    int64_t xr[kTrainRows];
+#pragma unroll
+    for (int r = 0; r < kTrainRows; ++r) xr[r] = r < nr ? train_row(a, row0 + r) : 0;
+    vec4 q1[32], q2[8];
     float x[kTrainRows], w3[2];
 #pragma unroll
-    for (int r = 0; r < kTrainRows; ++r) x[r] = r < nr ? a.X[train_row(a, row0 + r) * 256 + t] : 0.f;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) qa[i] = w1[i * 256 + t];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) qb[i] = w1[(16 + i) * 256 + t];
+    for (int i = 0; i < 32; ++i) q1[i] = w1[i * 256 + t];
 #pragma unroll
     for (int i = 0; i < 8; ++i) q2[i] = w2[i * 256 + t];
 #pragma unroll
     for (int i = 0; i < 2; ++i) w3[i] = i * 256 + t < 64 * C ? th[a.oW3 + i * 256 + t] : 0.f;
-    const int u1 = t & 127, r1 = t >> 7;  // (row, unit) of the first hidden layer
-    const int u2 = t & 63, r2 = (t >> 6) & 1;  // of the second (threads below 128)
-    const float bias1 = th[a.ob1 + u1], bias2 = th[a.ob2 + u2];
+    const float bias1 = th[a.ob1 + u1], bias2 = th[a.ob2 + u2], bias3 = out3 ? th[a.ob3 + c3] : 0.f;
+#pragma unroll
+    for (int r = 0; r < kTrainRows; ++r) x[r] = r < nr ? a.X[xr[r] * 256 + t] : 0.f;
+    const float want = out3 ? a.T[(r3 ? xr[1] : xr[0]) * C + c3] : 0.f;
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int r = 0; r < kTrainRows; ++r) Xs[r][t] = x[r];
-    float z = 0.f;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) reinterpret_cast<vec4*>(W1s)[i * 256 + t] = qa[i];
-    __syncthreads();
-#pragma unroll 16
-    for (int k = 0; k < 128; ++k) z = fmaf(Xs[r1][k], W1s[k * 128 + u1], z);
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < 16; ++i) reinterpret_cast<vec4*>(W1s)[i * 256 + t] = qb[i];
-    __syncthreads();
-#pragma unroll 16
-    for (int k = 0; k < 128; ++k) z = fmaf(Xs[r1][128 + k], W1s[k * 128 + u1], z);
-    const float h1 = fmaxf(z + bias1, 0.f);
-    h1s[r1][u1] = h1;
-    if (r1 < nr) a.h1[(int64_t)(row0 + r1) * 128 + u1] = h1;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const int e = 4 * (i * 256 + t);
-        float* d = &W2s[e >> 6][e & 63];
-        d[0] = q2[i].x;
-        d[1] = q2[i].y;
-        d[2] = q2[i].z;
-        d[3] = q2[i].w;
-    }
+    for (int r = 0; r < kTrainRows; ++r) Xs[r][t & 7][t >> 3] = x[r];
 #pragma unroll
     for (int i = 0; i < 2; ++i) W3s[i * 256 + t] = w3[i];
     __syncthreads();
+    {
+        vec4 z0{}, z1{};  // units 4 (t mod 32) .. + 3 over the rows t div 32 + 8 i
+        const int g = t >> 5;
+#pragma unroll
+        for (int i = 0; i < 32; ++i) {
+            z0 = fma4(Xs[0][g][i], q1[i], z0);
+            z1 = fma4(Xs[1][g][i], q1[i], z1);
+        }
+        *reinterpret_cast<vec4*>(&part[w][lane >> 5][4 * (t & 31)]) = half_add(z0, z1);
+    }
+    __syncthreads();
+    const float h1 =
+        fmaxf(((part[0][r1][u1] + part[1][r1][u1]) + (part[2][r1][u1] + part[3][r1][u1])) + bias1, 0.f);
+    h1s[r1][u1 & 15][u1 >> 4] = h1;
+    if (r1 < nr) a.h1[(int64_t)(row0 + r1) * 128 + u1] = h1;
+    __syncthreads();
+    {
+        vec4 z0{}, z1{};  // units 4 (t mod 16) .. + 3 over the rows t div 16 + 16 i
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            z0 = fma4(h1s[0][o3][i], q2[i], z0);
+            z1 = fma4(h1s[1][o3][i], q2[i], z1);
+        }
+        const vec4 z = half_add(z0, z1);
+        float* d = &part[w][lane >> 5][4 * l16 + ((lane >> 4) & 1)];
+        d[0] = row_add(z.x, z.y);
+        d[2] = row_add(z.z, z.w);
+    }
+    __syncthreads();
     float h2 = 0.f;
     if (t < 128) {
-        float y = 0.f;
-#pragma unroll 16
-        for (int k = 0; k < 128; ++k) y = fmaf(h1s[r2][k], W2s[k][u2], y);
-        h2 = fmaxf(y + bias2, 0.f);
+        h2 = fmaxf(((part[0][r2][u2] + part[1][r2][u2]) + (part[2][r2][u2] + part[3][r2][u2])) + bias2, 0.f);
         h2s[r2][u2] = h2;
         if (r2 < nr) a.h2[(int64_t)(row0 + r2) * 64 + u2] = h2;
     }
     __syncthreads();
-    if (t < kTrainRows * C) {
-        const int r = t / C, c = t % C;
+    {
         float y = 0.f;
-#pragma unroll 16
-        for (int k = 0; k < 64; ++k) y = fmaf(h2s[r][k], W3s[k * C + c], y);
-        float dy = 0.f;
-        if (r < nr) {
-            const float d = (y + th[a.ob3 + c]) - a.T[train_row(a, row0 + r) * C + c];
-            dy = 2.f * d * a.scale;
-            a.d[(int64_t)(row0 + r) * C + c] = d;
-            a.dy[(int64_t)(row0 + r) * C + c] = dy;
+        if (r3 < kTrainRows)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) y = fmaf(h2s[r3][4 * l16 + q], W3s[(4 * l16 + q) * C + c3], y);
+        y += dpp_f32<kDppXor1>(y);
+        y += dpp_f32<kDppXor2>(y);
+        y += dpp_f32<kDppHalfMirror>(y);
+        y += dpp_f32<kDppMirror>(y);
+        if (l16 == 0 && r3 < kTrainRows) {
+            const float d = (y + bias3) - want;
+            const float dy = out3 ? 2.f * d * a.scale : 0.f;
+            if (out3) {
+                a.d[(int64_t)(row0 + r3) * C + c3] = d;
+                a.dy[(int64_t)(row0 + r3) * C + c3] = dy;
+            }
+            dys[r3][c3] = dy;
         }
-        dys[r][c] = dy;
     }
     __syncthreads();
     if (t < 128) {
@@ -234,27 +286,60 @@ __global__ __launch_bounds__(256) void train_rows_kernel(TrainStep a) {
         if (r2 < nr) a.dz2[(int64_t)(row0 + r2) * 64 + u2] = g;
     }
     __syncthreads();
-    float g = 0.f;
-#pragma unroll 16
-    for (int n = 0; n < 64; ++n) g = fmaf(dz2s[r1][n], W2s[u1][n], g);
-    if (r1 < nr) a.dz1[(int64_t)(row0 + r1) * 128 + u1] = h1 > 0.f ? g : 0.f;
-}
-
-// Adam update of parameter i with gradient gi, or (no update) the gradient itself.
-__device__ __forceinline__ void train_apply(const TrainStep& a, int64_t i, float gi) {
-    if (a.grad) {
-        a.grad[i] = gi;
-        return;
+    {
+        // rows of W2 times dz2: four columns per lane, then the sum over 16
+        // lanes by halving: lane l ends with value l of 2 rows x 8
+        float v[16];
+        const vec4 d0 = *reinterpret_cast<const vec4*>(&dz2s[0][4 * l16]);
+        const vec4 d1 = *reinterpret_cast<const vec4*>(&dz2s[1][4 * l16]);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            v[i] = fmaf(d0.w, q2[i].w, fmaf(d0.z, q2[i].z, fmaf(d0.y, q2[i].y, d0.x * q2[i].x)));
+            v[8 + i] = fmaf(d1.w, q2[i].w, fmaf(d1.z, q2[i].z, fmaf(d1.y, q2[i].y, d1.x * q2[i].x)));
+        }
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+            v[j] = ((l16 & 8) ? v[j + 8] : v[j]) + dpp_f32<kDppMirror>((l16 & 8) ? v[j] : v[j + 8]);
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            v[j] = ((l16 & 4) ? v[j + 4] : v[j]) + dpp_f32<kDppHalfMirror>((l16 & 4) ? v[j] : v[j + 4]);
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+            v[j] = ((l16 & 2) ? v[j + 2] : v[j]) + dpp_f32<kDppXor2>((l16 & 2) ? v[j] : v[j + 2]);
+        const float g = ((l16 & 1) ? v[1] : v[0]) + dpp_f32<kDppXor1>((l16 & 1) ? v[0] : v[1]);
+        part[0][l16 >> 3][(l16 & 7) * 16 + o3] = g;
     }
-    const float mi = a.b1 * a.m[i] + (1.f - a.b1) * gi;
-    const float vi = a.b2 * a.v[i] + (1.f - a.b2) * gi * gi;
-    a.m[i] = mi;
-    a.v[i] = vi;
-    a.theta[i] -= a.lr * (mi / a.c1) / (sqrtf(vi / a.c2) + a.eps);
+    __syncthreads();
+    if (r1 < nr) a.dz1[(int64_t)(row0 + r1) * 128 + u1] = h1 > 0.f ? part[0][r1][u1] : 0.f;
 }
 
-// A chunk of kRowChunk rows of G [rows][N] on its way through registers; rows
-// beyond the batch are zero and add nothing.
+// Parameter i with its moments, read before the gradient is known.
+struct TrainParam {
+    int64_t i;
+    float m, v, th;
+    __device__ __forceinline__ void load(const TrainStep& a, int64_t index) {
+        i = index;
+        if (a.grad) return;
+        m = a.m[i];
+        v = a.v[i];
+        th = a.theta[i];
+    }
+    // Adam update with gradient gi, or (no update) the gradient itself.
+    __device__ __forceinline__ void apply(const TrainStep& a, float gi) const {
+        if (a.grad) {
+            a.grad[i] = gi;
+            return;
+        }
+        const float mi = a.b1 * m + (1.f - a.b1) * gi;
+        const float vi = a.b2 * v + (1.f - a.b2) * gi * gi;
+        a.m[i] = mi;
+        a.v[i] = vi;
+        a.theta[i] = th - a.lr * (mi / a.c1) / (sqrtf(vi / a.c2) + a.eps);
+    }
+};
+
+// A chunk of kRowChunk rows of G [rows][N] in registers, a thread's rows N / 4
+// threads apart; rows beyond the batch are zero and add nothing.
 template <int N>
 struct RowChunk {
     static constexpr int Q = kRowChunk * N / 4 / 256;
@@ -267,86 +352,73 @@ struct RowChunk {
             q[i] = e < end ? reinterpret_cast<const vec4*>(G)[e] : vec4{};
         }
     }
-    __device__ __forceinline__ void store(float* s) const {
-#pragma unroll
-        for (int i = 0; i < Q; ++i) reinterpret_cast<vec4*>(s)[i * 256 + threadIdx.x] = q[i];
-    }
 };
 
-constexpr int kTileLds = kRowChunk * 128;  // floats of a staged chunk of G
-
-// Gradient rows k0 .. k0 + TK - 1 of a layer with input A (row i at arow(i),
-// TK consecutive values) and output derivative G [rows][N]: thread (g, n)
-// holds TK * N / 256 rows of column n.
-template <int TK, int N, typename ARow>
-__device__ __forceinline__ void train_tile(const TrainStep& a, const ARow& arow, const float* G, int64_t out,
-                                           float* sg, float* sa) {
-    constexpr int GROUPS = 256 / N, PER = TK / GROUPS;
-    const int t = threadIdx.x, n = t % N, g = t / N;
-    float acc[PER] = {};
-    RowChunk<N> next;
-    float av[TK];
-    auto load = [&](int i0) {
+// Sums over the batch's rows i of A[i][k] G[i][n], k < TK, n < N: A's row i at
+// arow(i), `width` <= TK consecutive values; output (k, n) belongs to
+// parameter at(k, n).  TK x N = 512: every thread ends with two outputs.
+template <int TK, int N, typename ARow, typename At>
+__device__ __forceinline__ void train_tile(const TrainStep& a, const ARow& arow, int width, const float* G,
+                                           const At& at, float (*part)[512], float* sa) {
+    constexpr int LANES = N / 4, GROUPS = 256 / LANES, STEPS = kRowChunk / GROUPS;
+    static_assert(TK * N == 512 && (N == 128 || N == 64), "two outputs per thread");
+    const int t = threadIdx.x, lane = t & 63, g = t / LANES;
+    RowChunk<N> cur, next;
+    float av[TK], an[TK];
+    auto load = [&](int i0, RowChunk<N>& c, float (&v)[TK]) {
         const float* src = t < kRowChunk && i0 + t < a.rows ? arow(i0 + t) : nullptr;
+        c.load(G, i0, a.rows);
 #pragma unroll
-        for (int q = 0; q < TK; ++q) av[q] = src ? src[q] : 0.f;  // the caller's histograms: 4-byte alignment
-        next.load(G, i0, a.rows);
+        for (int q = 0; q < TK; ++q) v[q] = src && q < width ? src[q] : 0.f;  // the caller's histograms: 4-byte alignment
     };
-    load(0);
+    load(0, cur, av);
+    TrainParam prm[2];
+    int kk[2], nn[2];
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+        const int e = p * 256 + t;
+        kk[p] = e / N;
+        nn[p] = e % N;
+        if (kk[p] < width) prm[p].load(a, at(kk[p], nn[p]));
+    }
+    vec4 acc[TK] = {};
     for (int i0 = 0; i0 < a.rows; i0 += kRowChunk) {
-        __syncthreads();
+        const bool more = i0 + kRowChunk < a.rows;
+        if (more) load(i0 + kRowChunk, next, an);
+        if (i0) __syncthreads();  // the rows of A before are used
         if (t < kRowChunk)
 #pragma unroll
             for (int q = 0; q < TK; ++q) sa[t * TK + q] = av[q];
-        next.store(sg);
         __syncthreads();
-        if (i0 + kRowChunk < a.rows) load(i0 + kRowChunk);
-#pragma unroll 16
-        for (int i = 0; i < kRowChunk; ++i) {
-            const float gv = sg[i * N + n];
 #pragma unroll
-            for (int p = 0; p < PER; ++p) acc[p] = fmaf(sa[i * TK + g * PER + p], gv, acc[p]);
+        for (int i = 0; i < STEPS; ++i)
+#pragma unroll
+            for (int k = 0; k < TK; ++k) acc[k] = fma4(sa[(i * GROUPS + g) * TK + k], cur.q[i], acc[k]);
+        if (more) {
+            cur = next;
+#pragma unroll
+            for (int q = 0; q < TK; ++q) av[q] = an[q];
         }
     }
+    // the wave's row groups: halves, then rows of 16; each step leaves half the
+    // values in either part
+    int k0 = (lane >> 5) * (TK / 2);
 #pragma unroll
-    for (int p = 0; p < PER; ++p) train_apply(a, out + (int64_t)(g * PER + p) * N + n, acc[p]);
-}
-
-// Gradient of W3 [64][C]: up to two outputs per thread.
-__device__ __forceinline__ void train_w3(const TrainStep& a, float* sg, float* sa) {
-    const int t = threadIdx.x, C = a.C;
-    float acc[2] = {};
-    RowChunk<64> next;
-    float dv[kRowChunk * kMaxC / 256];
-    auto load = [&](int i0) {
-        next.load(a.h2, i0, a.rows);
+    for (int k = 0; k < TK / 2; ++k) acc[k] = half_add(acc[k], acc[k + TK / 2]);
+    if constexpr (N == 64) {
 #pragma unroll
-        for (int q = 0; q < kRowChunk * kMaxC / 256; ++q) {
-            const int e = q * 256 + t;
-            dv[q] = e < kRowChunk * C && (int64_t)i0 * C + e < (int64_t)a.rows * C ? a.dy[(int64_t)i0 * C + e] : 0.f;
-        }
-    };
-    load(0);
-    for (int i0 = 0; i0 < a.rows; i0 += kRowChunk) {
-        __syncthreads();
-        next.store(sg);
-#pragma unroll
-        for (int q = 0; q < kRowChunk * kMaxC / 256; ++q) sa[q * 256 + t] = dv[q];
-        __syncthreads();
-        if (i0 + kRowChunk < a.rows) load(i0 + kRowChunk);
-#pragma unroll
-        for (int p = 0; p < 2; ++p) {
-            const int e = p * 256 + t;
-            if (e < 64 * C) {
-                const int k = e / C, c = e % C;
-#pragma unroll 16
-                for (int i = 0; i < kRowChunk; ++i) acc[p] = fmaf(sg[i * 64 + k], sa[i * C + c], acc[p]);
-            }
-        }
+        for (int k = 0; k < TK / 4; ++k) acc[k] = row_add(acc[k], acc[k + TK / 4]);
+        k0 += ((lane >> 4) & 1) * (TK / 4);
     }
 #pragma unroll
-    for (int p = 0; p < 2; ++p)
-        if (p * 256 + t < 64 * C) train_apply(a, a.oW3 + p * 256 + t, acc[p]);
+    for (int k = 0; k < 2; ++k)
+        *reinterpret_cast<vec4*>(&part[t >> 6][(k0 + k) * N + 4 * (t % LANES)]) = acc[k];
+    __syncthreads();
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+        const int e = p * 256 + t;
+        if (kk[p] < width) prm[p].apply(a, (part[0][e] + part[1][e]) + (part[2][e] + part[3][e]));
+    }
 }
 
 // Column sums of G [rows][N], 16 columns per block: 16 row groups (thread (g,
@@ -355,16 +427,18 @@ __device__ __forceinline__ void train_bias(const TrainStep& a, const float* G, i
                                            float* s) {
     const int c = threadIdx.x % kColTile, g = threadIdx.x / kColTile;
     const int j = block * kColTile + c;
+    TrainParam prm;
+    if (g == 0 && j < N) prm.load(a, out + j);
     float v = 0.f;
     if (j < N)
-#pragma unroll 8
+#pragma unroll 16
         for (int i = g; i < a.rows; i += kRowGroups) v += G[(int64_t)i * N + j];
     s[g * (kColTile + 1) + c] = v;
     __syncthreads();
     if (g == 0 && j < N) {
         float t = s[c];
         for (int r = 1; r < kRowGroups; ++r) t += s[r * (kColTile + 1) + c];
-        train_apply(a, out + j, t);
+        prm.apply(a, t);
     }
 }
 
@@ -373,26 +447,32 @@ constexpr int kBlocksB1 = 128 / kColTile, kBlocksB2 = 64 / kColTile;
 constexpr int kTrainBlocks = kBlocksW1 + kBlocksW2 + kBlocksB1 + kBlocksB2 + 3;  // and W3, b3, the loss
 
 __global__ __launch_bounds__(256) void train_update_kernel(TrainStep a) {
-    __shared__ __align__(16) float s[kTileLds];
-    __shared__ float sa[kRowChunk * 8];
+    __shared__ __align__(16) float part[4][512];
+    __shared__ __align__(16) float sa[kRowChunk * 8];
     static_assert(kTileK1 <= 8 && kTileK2 <= 8 && kMaxC <= 8, "sa holds a chunk of the narrow operand");
     const int t = threadIdx.x, C = a.C;
+    float* s = &part[0][0];
     int b = blockIdx.x;
     if (b < kBlocksW1) {
-        const int k0 = b * kTileK1;
-        train_tile<kTileK1, 128>(a, [&](int i) { return a.X + train_row(a, i) * 256 + k0; }, a.dz1,
-                                 a.oW1 + (int64_t)k0 * 128, s, sa);
+        const int64_t k0 = b * kTileK1, out = a.oW1 + k0 * 128;
+        train_tile<kTileK1, 128>(a, [&](int i) { return a.X + train_row(a, i) * 256 + k0; }, kTileK1, a.dz1,
+                                 [=](int k, int n) { return out + k * 128 + n; }, part, sa);
         return;
     }
     b -= kBlocksW1;
     if (b < kBlocksW2) {
-        const int k0 = b * kTileK2;
-        train_tile<kTileK2, 64>(a, [&](int i) { return a.h1 + (int64_t)i * 128 + k0; }, a.dz2,
-                                a.oW2 + (int64_t)k0 * 64, s, sa);
+        const int64_t k0 = b * kTileK2, out = a.oW2 + k0 * 64;
+        train_tile<kTileK2, 64>(a, [&](int i) { return a.h1 + (int64_t)i * 128 + k0; }, kTileK2, a.dz2,
+                                [=](int k, int n) { return out + k * 64 + n; }, part, sa);
         return;
     }
     b -= kBlocksW2;
-    if (b == 0) return train_w3(a, s, sa);
+    if (b == 0) {  // W3 [64][C], transposed: the wide operand is the activation
+        const int64_t out = a.oW3;
+        train_tile<8, 64>(a, [&](int i) { return a.dy + (int64_t)i * C; }, C, a.h2,
+                          [=](int k, int n) { return out + (int64_t)n * C + k; }, part, sa);
+        return;
+    }
     --b;
     if (b < kBlocksB1) return train_bias(a, a.dz1, 128, b, a.ob1, s);
     b -= kBlocksB1;
@@ -400,20 +480,20 @@ __global__ __launch_bounds__(256) void train_update_kernel(TrainStep a) {
     b -= kBlocksB2;
     if (b == 0) return train_bias(a, a.dy, C, 0, a.ob3, s);
     // the batch's loss: sum (Y - T)^2 / (rows C), FP64, in a fixed order
-    double* part = reinterpret_cast<double*>(s);
+    double* sum = reinterpret_cast<double*>(s);
     double v = 0.0;
     const int64_t n = (int64_t)a.rows * C;
     for (int64_t i = t; i < n; i += 256) {
         const float d = a.d[i];
         v += (double)d * d;
     }
-    part[t] = v;
+    sum[t] = v;
     __syncthreads();
     for (int w = 128; w > 0; w >>= 1) {
-        if (t < w) part[t] += part[t + w];
+        if (t < w) sum[t] += sum[t + w];
         __syncthreads();
     }
-    if (t == 0) *a.loss = (float)(part[0] * a.scale);
+    if (t == 0) *a.loss = (float)(sum[0] * a.scale);
 }
 
 hipError_t launch_train_step(TrainStep a, int step, hipStream_t s) {
