@@ -333,6 +333,12 @@ def roofline_entry(shape, n, C, m, passes_per_launch, launch_s, tuning, kernel):
     }
 
 
+def per_voxel(f, **kw):
+    """The persistent solve over the voxels in its default shape: by default
+    the driver iterates over the grey levels, a named grid asks for voxels."""
+    f.set_tuning(grid=f.tuning["grid"], **kw)
+
+
 def solve_steps(dev, x, C, m, eps, steps, warmup, launch, autotune, tune_cache):
     """The timed steps on one resident input: `warmup` + `steps` whole solves
     with labels enqueued back to back (fcm_solve_async), then the same solves
@@ -343,7 +349,7 @@ def solve_steps(dev, x, C, m, eps, steps, warmup, launch, autotune, tune_cache):
     labels = torch.empty_like(x)
     stream = torch.cuda.current_stream(dev)
     f = FCM(x, C, m=m, eps=eps, max_iter=300, timing=True, stream=stream)
-    f.set_tuning(launch=0 if launch == "cooperative" else 1)
+    per_voxel(f, launch=0 if launch == "cooperative" else 1)
     if autotune:
         f.autotune(cache=tune_cache, reps=3)
     timed_async(f, warmup, labels)
@@ -370,7 +376,8 @@ def small_workloads(dev, steps, launch, tune_cache):
     for name, shape, seed, ctx in cases:
         x = torch.from_numpy(phantom(PhantomParams(shape=shape, seed=seed)).ravel()).to(dev)
         n = x.numel()
-        st = solve_steps(dev, x, 4, 2.0, 1e-5, steps, 5, launch, True, tune_cache)
+        # no recorded choice for the slice: the autotuner would take the level solve
+        st = solve_steps(dev, x, 4, 2.0, 1e-5, steps, 5, launch, len(shape) == 3, tune_cache)
         r = st["r"]
         pps = st["passes"] / steps
         launch_s = st["kernel_ms"] / steps * 1e-3
@@ -394,7 +401,7 @@ def histogram_domain(dev, cases):
     """Exact histogram-domain solve (FCM_DRIVER_HISTOGRAM) on the given
     volumes ((name, device tensor) pairs): one pass over the data, then the
     iteration over grey levels; time to converge with labels, against the
-    per-voxel persistent solve on the same handle configuration."""
+    per-voxel persistent solve."""
     import torch
 
     from paper_1601_00072_amd import FCM
@@ -404,7 +411,7 @@ def histogram_domain(dev, cases):
         res = {}
         for drv in (3, 2):
             with FCM(x, 4) as f:
-                f.set_tuning(driver=drv)
+                f.set_tuning(driver=3) if drv == 3 else per_voxel(f)
                 timed_solves(f, 2, labels)
                 el, passes, _, r = timed_solves(f, 10, labels)
             res[drv] = (el / 10 * 1e3, r.iters)
@@ -530,6 +537,8 @@ def batched(dev, tune_cache):
         views.append(flat[off:off + a.size])
         off += a.size
     handles = [FCM(v, c) for v, c in zip(views, Cs)]
+    for h in handles:
+        per_voxel(h)
     for h in handles:
         h.solve()
     torch.cuda.synchronize()
