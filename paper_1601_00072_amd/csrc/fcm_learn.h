@@ -10,11 +10,10 @@ struct fcm_mlp;
 namespace fcm {
 
 // Output width C of a network, and its warm start: BF16 inference of `count`
-// normalised histograms into d_y (count x C) and the post-processing into
-// start centroids d_v0 (count x C doubles; a row of NaN where no valid start
-// exists).  Enqueued on s; returns an FCM_* status.
+// normalised histograms and the post-processing into start centroids d_v0
+// (count x C doubles; a row of NaN where no valid start exists).  Enqueued on s; returns an FCM_* status.
 int mlp_clusters(const fcm_mlp* net);
-int mlp_warm(fcm_mlp* net, const float* d_hist, int count, float* d_y, double* d_v0, hipStream_t s);
+int mlp_warm(fcm_mlp* net, const float* d_hist, int count, double* d_v0, hipStream_t s);
 
 // The network's BF16 parameters, brought up to date on stream s (for the
 // persistent solve's in-kernel inference); *rc receives an FCM_* status.
@@ -51,6 +50,6 @@ hipError_t launch_train_step(TrainStep a, int step, hipStream_t s);
 // BF16 inference copy (output-major rows; see fcm_learn_dev.h) of the flat parameters
 hipError_t launch_to_bf16(const float* theta, uint16_t* out, int C, hipStream_t s);
 hipError_t launch_mlp_infer(const void* w, bool bf16, const float* X, int count, int C, float* Y, hipStream_t s);
-hipError_t launch_warm_post(const float* Y, const float* hist, int count, int C, double* v0, hipStream_t s);
+hipError_t launch_mlp_starts(const void* w, const float* X, int count, int C, double* v0, hipStream_t s);
 
 }  // namespace fcm

@@ -537,31 +537,70 @@ hipError_t launch_to_bf16(const float* theta, uint16_t* out, int C, hipStream_t 
     return hipGetLastError();
 }
 
-// One block (256 threads) per histogram (mlp_block_forward).
-template <bool BF16>
-__global__ __launch_bounds__(256) void mlp_infer_kernel(const void* w, const float* X, int C, float* Y) {
+// What follows the network where start centroids are wanted (warm_post_one):
+// `range`, the histogram's levels above zero, is collected as the histogram is
+// read, so the inference launch ends with the starts.  A launch of its own for
+// this, with the outputs and the histograms read again, took 5.4 us for 1,024
+// instances and a launch gap (histograms and starts of 1,024 slices: 92.6 us
+// so, 89.2 in one launch).
+__device__ __forceinline__ void start_row(const uint64_t (&range)[4], const float* y, int C, double* v0) {
+    int lo = 255, hi = 0;  // what a walk over no positive level ends with
+#pragma unroll
+    for (int q = 3; q >= 0; --q)
+        if (range[q]) lo = 64 * q + __builtin_ctzll(range[q]);
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+        if (range[q]) hi = 64 * q + 63 - __builtin_clzll(range[q]);
+    warm_post_one(y, lo, hi, C, v0);
+}
+
+// One block (256 threads) per histogram (mlp_block_forward); outputs to Y, or
+// (STARTS) start centroids to v0.
+template <bool BF16, bool STARTS>
+__global__ __launch_bounds__(256) void mlp_infer_kernel(const void* w, const float* X, int C, float* Y, double* v0) {
     __shared__ float a0[256];
     __shared__ float a1[128];
     __shared__ float a2[64];
     __shared__ float tmp[256];
     const int64_t s = blockIdx.x;
-    mlp_block_forward<BF16>(w, X + s * 256, C, a0, a1, a2, tmp, Y + s * C);
+    if constexpr (STARTS) {
+        __shared__ uint64_t range[4];
+        __shared__ float y[kMaxC];
+        const int t = threadIdx.x;
+        const uint64_t m = __ballot(X[s * 256 + t] > 0.f);
+        if ((t & 63) == 0) range[t >> 6] = m;
+        mlp_block_forward<BF16>(w, X + s * 256, C, a0, a1, a2, tmp, y);
+        __syncthreads();
+        if (t == 0) start_row(range, y, C, v0 + s * C);
+    } else {
+        mlp_block_forward<BF16>(w, X + s * 256, C, a0, a1, a2, tmp, Y + s * C);
+    }
 }
 
 // The BF16 network on kInferRows histograms per block: the arithmetic and its
 // order are mlp_block_forward's, but a block reads the weights (83 KB) once for
 // all of them.
-constexpr int kInferRows = 4;
+constexpr int kInferRows = 4;  // one per wave for the starts
 
+template <bool STARTS>
 __global__ __launch_bounds__(256) void mlp_infer_rows_kernel(const uint16_t* w, const float* X, int count, int C,
-                                                             float* Y) {
+                                                             float* Y, double* v0) {
     using L = InferLayout;
     __shared__ float a0[kInferRows][256], a1[kInferRows][128], a2[kInferRows][64], tmp[kInferRows][256];
+    __shared__ uint64_t range[kInferRows][4];
+    __shared__ float ys[kInferRows][kMaxC];
     const int t = threadIdx.x;
     const int64_t s0 = (int64_t)blockIdx.x * kInferRows;
     const int m = count - s0 < kInferRows ? (int)(count - s0) : kInferRows;
 #pragma unroll
-    for (int h = 0; h < kInferRows; ++h) a0[h][t] = h < m ? act<true>(X[(s0 + h) * 256 + t]) : 0.f;
+    for (int h = 0; h < kInferRows; ++h) {
+        const float x = h < m ? X[(s0 + h) * 256 + t] : 0.f;
+        a0[h][t] = act<true>(x);
+        if constexpr (STARTS) {
+            const uint64_t r = __ballot(x > 0.f);
+            if ((t & 63) == 0) range[h][t >> 6] = r;
+        }
+    }
     uint4 w2[16], w3[8];
     if (t < 64) load_bf16<16>(w + L::W2 + t * 128, w2);
     if (t < C) load_bf16<8>(w + L::W3 + t * 64, w3);
@@ -592,52 +631,41 @@ __global__ __launch_bounds__(256) void mlp_infer_rows_kernel(const uint16_t* w, 
     __syncthreads();
     if (t < C)
 #pragma unroll
-        for (int h = 0; h < kInferRows; ++h)
-            if (h < m) Y[(s0 + h) * C + t] = dot_bf16_regs<8>(from_bf16(w[L::b3(C) + t]), a2[h], w3);
+        for (int h = 0; h < kInferRows; ++h) {
+            const float y = dot_bf16_regs<8>(from_bf16(w[L::b3(C) + t]), a2[h], w3);
+            if constexpr (STARTS)
+                ys[h][t] = y;
+            else if (h < m)
+                Y[(s0 + h) * C + t] = y;
+        }
+    if constexpr (STARTS) {
+        __syncthreads();
+        const int h = t >> 6;
+        if ((t & 63) == 0 && h < m) start_row(range[h], ys[h], C, v0 + (s0 + h) * C);
+    }
 }
 
 // Several histograms per block from the count on that still gives every second
 // CU a block (1,024 histograms: 19 us one per block, 12 us four per block).
-hipError_t launch_mlp_infer(const void* w, bool bf16, const float* X, int count, int C, float* Y, hipStream_t s) {
-    if (bf16 && count >= 128 * kInferRows)
-        hipLaunchKernelGGL(mlp_infer_rows_kernel, dim3((count + kInferRows - 1) / kInferRows), dim3(256), 0, s,
-                           static_cast<const uint16_t*>(w), X, count, C, Y);
-    else if (bf16)
-        hipLaunchKernelGGL(mlp_infer_kernel<true>, dim3(count), dim3(256), 0, s, w, X, C, Y);
+template <bool STARTS>
+static hipError_t launch_bf16(const void* w, const float* X, int count, int C, float* Y, double* v0, hipStream_t s) {
+    if (count >= 128 * kInferRows)
+        hipLaunchKernelGGL(mlp_infer_rows_kernel<STARTS>, dim3((count + kInferRows - 1) / kInferRows), dim3(256), 0, s,
+                           static_cast<const uint16_t*>(w), X, count, C, Y, v0);
     else
-        hipLaunchKernelGGL(mlp_infer_kernel<false>, dim3(count), dim3(256), 0, s, w, X, C, Y);
+        hipLaunchKernelGGL((mlp_infer_kernel<true, STARTS>), dim3(count), dim3(256), 0, s, w, X, C, Y, v0);
     return hipGetLastError();
 }
 
-// Network output -> start centroids (warm_post_one), one wave per instance:
-// its lanes look at four levels each for the range (one thread that walked
-// the levels waited for a load per empty level: 13 us for 1,024 instances, 5 us
-// so).
-__global__ __launch_bounds__(256) void warm_post_kernel(const float* Y, const float* hist, int count, int C,
-                                                        double* v0) {
-    const int s = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-    if (s >= count) return;
-    const float* h = hist + (int64_t)s * 256;
-    float v[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) v[q] = h[64 * q + lane];
-    int lo = 255, hi = 0;  // what a walk over no positive level ends with
-#pragma unroll
-    for (int q = 3; q >= 0; --q) {
-        const uint64_t m = __ballot(v[q] > 0.f);
-        if (m) lo = 64 * q + __builtin_ctzll(m);
-    }
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const uint64_t m = __ballot(v[q] > 0.f);
-        if (m) hi = 64 * q + 63 - __builtin_clzll(m);
-    }
-    if (lane == 0) warm_post_one(Y + (int64_t)s * C, lo, hi, C, v0 + (int64_t)s * C);
+hipError_t launch_mlp_infer(const void* w, bool bf16, const float* X, int count, int C, float* Y, hipStream_t s) {
+    if (bf16) return launch_bf16<false>(w, X, count, C, Y, nullptr, s);
+    hipLaunchKernelGGL((mlp_infer_kernel<false, false>), dim3(count), dim3(256), 0, s, w, X, C, Y,
+                       static_cast<double*>(nullptr));
+    return hipGetLastError();
 }
 
-hipError_t launch_warm_post(const float* Y, const float* hist, int count, int C, double* v0, hipStream_t s) {
-    hipLaunchKernelGGL(warm_post_kernel, dim3((count + 3) / 4), dim3(256), 0, s, Y, hist, count, C, v0);
-    return hipGetLastError();
+hipError_t launch_mlp_starts(const void* w, const float* X, int count, int C, double* v0, hipStream_t s) {
+    return launch_bf16<true>(w, X, count, C, nullptr, v0, s);
 }
 
 // ---------------------------------------------------------------------------

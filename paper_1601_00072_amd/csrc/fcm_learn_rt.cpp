@@ -85,8 +85,6 @@ struct fcm_mlp {
     int64_t loss_cap = 0;
     int32_t* idx = nullptr;   // sample order of one epoch
     int64_t idx_cap = 0;
-    float* ybuf = nullptr;    // inference output scratch (fcm_warm_centroids)
-    int64_t ybuf_cap = 0;
 };
 
 namespace {
@@ -98,7 +96,7 @@ void free_ptr(void* p) {
 void mlp_release(fcm_mlp* n) {
     if (!n) return;
     for (void* p : {(void*)n->theta, (void*)n->grad, (void*)n->am, (void*)n->av, (void*)n->wb, (void*)n->h1,
-                    (void*)n->h2, (void*)n->d, (void*)n->dy, (void*)n->dz2, (void*)n->dz1, (void*)n->losses, (void*)n->idx, (void*)n->ybuf})
+                    (void*)n->h2, (void*)n->d, (void*)n->dy, (void*)n->dz2, (void*)n->dz1, (void*)n->losses, (void*)n->idx})
         free_ptr(p);
     delete n;
 }
@@ -218,11 +216,10 @@ const uint16_t* mlp_bf16_weights(fcm_mlp* net, hipStream_t s, int* rc) {
     return net->wb;
 }
 
-int mlp_warm(fcm_mlp* net, const float* d_hist, int count, float* d_y, double* d_v0, hipStream_t s) {
+int mlp_warm(fcm_mlp* net, const float* d_hist, int count, double* d_v0, hipStream_t s) {
     int rc = refresh_bf16(net, s);
     if (rc != FCM_OK) return rc;
-    FCM_HIP(launch_mlp_infer(net->wb, true, d_hist, count, net->C, d_y, s));
-    FCM_HIP(launch_warm_post(d_y, d_hist, count, net->C, d_v0, s));
+    FCM_HIP(launch_mlp_starts(net->wb, d_hist, count, net->C, d_v0, s));
     return FCM_OK;
 }
 
@@ -449,10 +446,7 @@ int fcm_histogram(const uint8_t* d_x, const int64_t* offsets, int32_t count, flo
 
 int fcm_warm_centroids(fcm_mlp* n, const float* d_hist, int32_t count, double* d_v0, void* stream) {
     if (!n || !d_hist || !d_v0 || count < 1) return FCM_EINVAL;
-    hipStream_t s = (hipStream_t)stream;
-    int rc = grow(n->ybuf, n->ybuf_cap, (int64_t)count * n->C, s);
-    if (rc != FCM_OK) return rc;
-    return mlp_warm(n, d_hist, count, n->ybuf, d_v0, s);
+    return mlp_warm(n, d_hist, count, d_v0, (hipStream_t)stream);
 }
 
 }  // extern "C"

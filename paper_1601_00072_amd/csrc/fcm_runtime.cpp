@@ -137,7 +137,6 @@ struct fcm_handle {
     int64_t* d_woff = nullptr;     // {0, n}
     uint32_t* d_wcounts = nullptr; // [kHistCopies][256] histogram workspace (copy 0: totals)
     float* d_whist = nullptr;      // [256]
-    float* d_wy = nullptr;         // [kMaxC] network output
     double* d_wv0 = nullptr;       // [kMaxC] learned start
     uint32_t* d_ghist = nullptr;   // [2][kHistCopies][256] counters of the in-kernel histogram; a learned
                                    // launch uses buffer ghist_sel and zeroes the other one
@@ -155,11 +154,11 @@ int64_t chunk_blocks(const fcm_handle* h) { return (h->nbody + kBlock - 1) / kBl
 
 // Blocks of a level solve: one per 16,384 voxels, at most one per CU.  Fewer,
 // larger shares leave the count of a small input to too few CUs (256x256
-// pixels, solve and labels: 35.9 us with 65,536 voxels per block, 33.6 with
-// 16,384; 128x128x64 voxels: 23.3 and 20.1); smaller ones pay for more blocks
-// at the global counters (8,192: 20.9).  Two blocks per CU do not read faster
-// and contend there (512x512x256 voxels: 93 us with 512 blocks, 75 with 256,
-// 85 with 128).
+// pixels, solve and labels: 28.8 us with 65,536 voxels per block, 26.3 with
+// 16,384; 128x128x64 voxels enqueued: 22.0 and 18.5); smaller ones pay for
+// more blocks at the global counters (8,192: 26.7 and 19.1).  Two blocks per
+// CU do not read faster and contend there (512x512x256 voxels: 74.2 us with
+// 512 blocks, 68.5 with 256, 79.9 with 128).
 constexpr int64_t kLevelVoxelsPerBlock = 16384;
 int level_grid(const fcm_handle* h) {
     return (int)std::max<int64_t>(
@@ -180,8 +179,8 @@ int start_mode(int init) {
 // library: an explicit grid, exchange or cooperative launch asks for the
 // per-voxel pass in that shape, as do the loop and graph drivers.  Measured
 // (C = 4, m = 2, solve and labels, per voxel and over the levels): 256x256
-// pixels 99.7 and 33.6 us, 128x128x64 voxels 108 and 20 us (enqueued),
-// 512x512x256 voxels 1,547 and 75 us; there is no size at which the
+// pixels 99.7 and 26.3 us, 128x128x64 voxels 108 and 18.5 us (enqueued),
+// 512x512x256 voxels 1,547 and 68.5 us; there is no size at which the
 // per-voxel pass is the faster one.  The 32-bit counters bound n.
 bool level_tuning(const fcm_handle* h, const fcm_tuning& t) {
     if (h->n > (int64_t)UINT32_MAX) return false;
@@ -560,7 +559,6 @@ int ensure_level_ws(fcm_handle* h) {
     if (!h->d_wcounts && hipMalloc(&h->d_wcounts, sizeof(uint32_t) * 256 * histogram_copies(1)) != hipSuccess)
         return FCM_ENOMEM;
     if (!h->d_whist && hipMalloc(&h->d_whist, sizeof(float) * 256) != hipSuccess) return FCM_ENOMEM;
-    if (!h->d_wy && hipMalloc(&h->d_wy, sizeof(float) * kMaxC) != hipSuccess) return FCM_ENOMEM;
     if (!h->d_wv0 && hipMalloc(&h->d_wv0, sizeof(double) * kMaxC) != hipSuccess) return FCM_ENOMEM;
     int64_t* off = nullptr;
     if (hipMalloc(&off, sizeof(int64_t) * 2) != hipSuccess) return FCM_ENOMEM;
@@ -618,7 +616,7 @@ void release(fcm_handle* h) {
     if (h->d_partials) (void)hipFree(h->d_partials);
     if (h->d_rows) (void)hipFree(h->d_rows);
     if (h->d_mmrows) (void)hipFree(h->d_mmrows);
-    for (void* p : {(void*)h->d_woff, (void*)h->d_wcounts, (void*)h->d_whist, (void*)h->d_wy, (void*)h->d_wv0,
+    for (void* p : {(void*)h->d_woff, (void*)h->d_wcounts, (void*)h->d_whist, (void*)h->d_wv0,
                     (void*)h->d_ghist})
         if (p) (void)hipFree(p);
     if (h->h_state) (void)hipHostFree(h->h_state);
@@ -910,7 +908,7 @@ int fcm_solve_warm(fcm_handle* h, fcm_mlp* net, int32_t check, fcm_result* out, 
     } else {
         if ((rc = ensure_level_ws(h)) != FCM_OK) return rc;
         FCM_HIP(launch_histogram(h->d_x, h->d_woff, 1, h->n, h->d_wcounts, h->d_whist, h->stream));
-        if ((rc = mlp_warm(net, h->d_whist, 1, h->d_wy, h->d_wv0, h->stream)) != FCM_OK) return rc;
+        if ((rc = mlp_warm(net, h->d_whist, 1, h->d_wv0, h->stream)) != FCM_OK) return rc;
         h->p.init = FCM_INIT_DEVICE;
         h->dv0 = h->d_wv0;
     }
@@ -1056,7 +1054,6 @@ struct fcm_batch {
     int64_t* d_off = nullptr;      // offsets [count + 1]
     uint32_t* d_counts = nullptr;  // [count][256]
     float* d_whist = nullptr;      // [count][256]
-    float* d_wy = nullptr;         // [count][kMaxC]
     double* d_wv0 = nullptr;       // [count][kMaxC]
 };
 
@@ -1075,7 +1072,7 @@ void batch_release(fcm_batch* b) {
     batch_free_tiles(b);
     for (void* p : {(void*)b->d_inst, (void*)b->d_ntiles, (void*)b->d_recs, (void*)b->d_hist, (void*)b->d_dec,
                     (void*)b->d_ctl, (void*)b->d_sync, (void*)b->d_off, (void*)b->d_counts, (void*)b->d_whist,
-                    (void*)b->d_wy, (void*)b->d_wv0, b->d_level})
+                    (void*)b->d_wv0, b->d_level})
         if (p) (void)hipFree(p);
     if (b->h_recs) (void)hipHostFree(b->h_recs);
     if (b->h_sync) (void)hipHostFree(b->h_sync);
@@ -1377,7 +1374,6 @@ int fcm_batch_set_start(fcm_batch* b, fcm_mlp* net, const uint8_t* use_learned) 
             if (hipMalloc(&b->d_counts, sizeof(uint32_t) * 256 * cnt * histogram_copies(b->count)) != hipSuccess)
                 return FCM_ENOMEM;
             if (hipMalloc(&b->d_whist, sizeof(float) * 256 * cnt) != hipSuccess) return FCM_ENOMEM;
-            if (hipMalloc(&b->d_wy, sizeof(float) * kMaxC * cnt) != hipSuccess) return FCM_ENOMEM;
             if (hipMalloc(&b->d_wv0, sizeof(double) * kMaxC * cnt) != hipSuccess) return FCM_ENOMEM;
             int64_t* off = nullptr;
             if (hipMalloc(&off, sizeof(int64_t) * (cnt + 1)) != hipSuccess) return FCM_ENOMEM;
@@ -1389,7 +1385,7 @@ int fcm_batch_set_start(fcm_batch* b, fcm_mlp* net, const uint8_t* use_learned) 
         int64_t max_n = 1;
         for (int32_t i = 0; i < b->count; ++i) max_n = std::max<int64_t>(max_n, b->h_inst[i].n);
         FCM_HIP(launch_histogram(b->d_x, b->d_off, b->count, max_n, b->d_counts, b->d_whist, b->stream));
-        int rc = mlp_warm(net, b->d_whist, b->count, b->d_wy, b->d_wv0, b->stream);
+        int rc = mlp_warm(net, b->d_whist, b->count, b->d_wv0, b->stream);
         if (rc != FCM_OK) return rc;
     }
     for (int32_t i = 0; i < b->count; ++i) {
