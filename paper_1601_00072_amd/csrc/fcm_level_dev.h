@@ -133,7 +133,7 @@ struct LevelProblem {
     int32_t max_iter, max_passes;
     int32_t do_init;          // start from v^0; else continue at `pass` from the history
     int32_t given;            // start mode: 0 evenly spaced, 1 v0, 2 dv0 (device); LEARNED: the network's (mlp_w)
-    int32_t pass;             // do_init == 0: index of the next pass (>= 1)
+    int32_t pass;             // do_init == 0: index of the next pass (0: v^0 is committed, no pass has run)
     int32_t fp32_range;       // report starts whose FP32 distances overflow as non-finite
     int64_t n;
     const double* v0;
@@ -480,9 +480,6 @@ __device__ __forceinline__ void level_iterate(const LevelProblem& pb, uint32_t c
         __syncthreads();
 #pragma unroll
         for (int k = 0; k < C; ++k) v[k] = readfirst_d(sh.v[k]);
-        if (pb.fp32_range)
-#pragma unroll
-            for (int k = 0; k < C; ++k) huge = huge || !(fabs(v[k]) < 1.8e19);
         if (wid == 4) {
             if (lane < C) pb.hist_v[lane] = sh.v[lane];
             if (pb.times && lane == 0) pb.times[0] = wall_clock64();
@@ -502,6 +499,10 @@ __device__ __forceinline__ void level_iterate(const LevelProblem& pb, uint32_t c
             if (!fin) level_u<C, MK>(x, vp, pb.m, pb.alpha, true, sh, uo, t);
         }
     }
+    // also where v^0 was committed before this launch (a query or labels first)
+    if (pb.fp32_range && p == 0)
+#pragma unroll
+        for (int k = 0; k < C; ++k) huge = huge || !(fabs(v[k]) < 1.8e19);
     const bool owner = (lane & 15) == 0;  // one lane per cluster of a set
     int kc[SETS];       // the clusters whose sums this lane holds
     double vk[SETS], vr[SETS];  // their centroids in this pass; in the last pass run
@@ -635,7 +636,8 @@ __device__ __forceinline__ void level_iterate(const LevelProblem& pb, uint32_t c
                 const double j = (jr[lane] + jr[lane + 64]) + (jr[lane + 128] + jr[lane + 192]);
                 double d = fmax(fmax(dr[lane], dr[lane + 64]), fmax(dr[lane + 128], dr[lane + 192]));
                 const double vn = sh.vnext[slot][lane & 7];
-                const double J = quad_sum_f64(j, 0.0, 0.0, 0.0);
+                double J = quad_sum_f64(j, 0.0, 0.0, 0.0);
+                if (huge) J = __builtin_nan("");  // as its FP32 terms would make it
                 d = wave_max_pos_f64(d);
                 const double delta = p > 0 ? readlane_d(d, 63) : __builtin_nan("");
                 if (lane == 0) {

@@ -1,0 +1,63 @@
+"""The level solve (default tuning) where its result must not depend on how
+the solve was reached: queries before it, steps, other routes' launches."""
+import numpy as np
+import pytest
+
+from phantom import PhantomParams, phantom
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def dev():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.fail("no GPU visible")
+    from paper_1601_00072_amd import _lib
+    _lib.load()
+    return torch.device("cuda:0")
+
+
+def volume(dev, shape=(5, 64, 64), seed=1):
+    import torch
+    return torch.from_numpy(phantom(PhantomParams(shape=shape, seed=seed)).ravel()).to(dev)
+
+
+@pytest.mark.parametrize("init", [[1e20, 10.0, 50.0], [-3.0e38, 0.0, 3.0e38], [10.0, 50.0, 1.9e19]])
+@pytest.mark.parametrize("first", ["none", "centroids", "iterate", "labels"])
+def test_start_out_of_range_after_a_query(dev, init, first):
+    """A start whose squared distances overflow FP32 is reported as the
+    per-voxel pass reports it (status, iteration 0, J and delta NaN), also
+    when the start was read or labelled before the solve."""
+    from paper_1601_00072_amd import FCM
+    print("CASE start out of range", init, "after", first, flush=True)
+    x = volume(dev)
+    got = []
+    for kw in ({}, dict(driver=2, grid=4)):
+        with FCM(x, 3, init=init) as f:
+            if kw:
+                f.set_tuning(**kw)
+            v0 = np.asarray(init, np.float32).astype(np.float64)
+            if first == "centroids":
+                assert np.array_equal(f.centroids(), v0)
+            elif first == "iterate":
+                assert f.iterate(0).status == 2
+            elif first == "labels":
+                f.labels()
+            r = f.solve()
+            v, d, J = f.trajectory(0)
+            assert np.array_equal(v, v0) and np.isnan(d) and np.isnan(J)
+            got.append((r.status, r.iters, r.passes))
+            assert np.isnan(r.J) and np.isnan(r.delta) and np.array_equal(r.centroids, v0)
+    assert got[0] == got[1] == (-5, 0, 1)
+
+
+def test_batch_start_out_of_range(dev):
+    from paper_1601_00072_amd import FCMBatch
+    print("CASE batch start out of range", flush=True)
+    x = volume(dev)
+    n = x.numel()
+    with FCMBatch(x, [n // 2, n - n // 2], [dict(n_clusters=3, init=[1e20, 10.0, 50.0]), dict(n_clusters=3)]) as b:
+        a, ok = b.solve()
+    assert a.status == -5 and a.iters == 0 and a.passes == 1 and np.isnan(a.J) and np.isnan(a.delta)
+    assert ok.status == 0 and np.isfinite(ok.J)
