@@ -303,10 +303,11 @@ int read_state(fcm_handle* h, bool own_launch = false) {
         const DevState& m = h->h_state[1];
         std::memcpy(h->h_state, &m, offsetof(DevState, sync));
         h->h_state->sync.passes_total = m.sync.passes_total;
-        return FCM_OK;
+        h->h_state->sync.abort = m.sync.abort;
+    } else {
+        FCM_HIP(hipMemcpyAsync(h->h_state, h->d_state, sizeof(DevState), hipMemcpyDeviceToHost, h->stream));
+        FCM_HIP(hipStreamSynchronize(h->stream));
     }
-    FCM_HIP(hipMemcpyAsync(h->h_state, h->d_state, sizeof(DevState), hipMemcpyDeviceToHost, h->stream));
-    FCM_HIP(hipStreamSynchronize(h->stream));
     if (h->h_state->sync.abort) {
         h->aborted = true;
         last_error() = "a cross-block wait exceeded its time limit; the solve was aborted (reset the handle)";

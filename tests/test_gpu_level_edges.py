@@ -61,3 +61,54 @@ def test_batch_start_out_of_range(dev):
         a, ok = b.solve()
     assert a.status == -5 and a.iters == 0 and a.passes == 1 and np.isnan(a.J) and np.isnan(a.delta)
     assert ok.status == 0 and np.isfinite(ok.J)
+
+
+TINY, DEFAULT = 1e-8, 5.0  # wait limits in seconds: about one clock tick (every wait gives up), the library's own
+
+
+def test_pending_wait_limit_is_reported_behind_a_level_solve(dev):
+    """An asynchronous per-voxel solve whose waits give up is reported by the
+    next fcm_solve_wait also when a level solve was enqueued behind it; the
+    handle then recovers on both routes."""
+    import torch
+    from paper_1601_00072_amd import FCM
+    from paper_1601_00072_amd.api import FcmError
+    print("CASE pending abort, then a level solve", flush=True)
+    x = volume(dev, (64, 128, 128), 2)
+    lab = torch.empty_like(x)
+    with FCM(x, 4) as f:
+        ref = f.solve()
+        f.set_tuning(driver=2, launch=1, grid=256)
+        f.set_wait_limit(TINY)
+        f.solve_async(lab)
+        f.set_wait_limit(DEFAULT)
+        f.set_tuning(driver=2)
+        f.solve_async(lab)
+        with pytest.raises(FcmError) as e:
+            f.result()
+        assert e.value.status == -3
+        f.solve_async(lab)
+        r, _ = f.result()
+        assert r.status == 0 and r.J == ref.J and np.array_equal(r.centroids, ref.centroids)
+        f.set_tuning(driver=2, launch=1, grid=256)
+        f.solve_async(lab)
+        r, _ = f.result()
+        assert r.status == 0 and np.max(np.abs(r.centroids - ref.centroids) / ref.centroids) <= 1e-4
+
+
+def test_solve_behind_a_pending_wait_limit(dev):
+    """The synchronous level solve behind such a launch runs again from its start, as the per-voxel one does."""
+    from paper_1601_00072_amd import FCM
+    print("CASE pending abort, then a synchronous level solve", flush=True)
+    x = volume(dev, (64, 128, 128), 2)
+    with FCM(x, 4) as f:
+        ref = f.solve()
+        f.set_tuning(driver=2, launch=1, grid=256)
+        f.set_wait_limit(TINY)
+        f.solve_async()
+        f.set_wait_limit(DEFAULT)
+        f.set_tuning(driver=2)
+        f.reset()
+        r = f.solve()
+        assert f.set_wait_limit(0) == 1
+    assert r.status == 0 and r.J == ref.J and np.array_equal(r.centroids, ref.centroids)
