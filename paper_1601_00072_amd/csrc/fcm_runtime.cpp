@@ -116,6 +116,7 @@ struct fcm_handle {
     double* d_hist = nullptr;      // v: (max_iter + 2) * C, then delta, then J: (max_iter + 2) each
     DevState* h_state = nullptr;   // pinned: [0] the host's view, [1] written by the level solve itself
     bool mirrored = false;         // h_state[1] holds the state that the last launch left
+    bool graphed = false;          // a captured per-voxel solve may run after it without the host's knowledge
     uint32_t seq = 0;              // its number: h_state[1].ticket once that launch has written its result
 
     fcm_tuning tun{};
@@ -293,7 +294,7 @@ int wait_own_launch(fcm_handle* h) {
 // State as of the work enqueued so far; waits for the stream, or (own_launch)
 // for the level launch just enqueued.
 int read_state(fcm_handle* h, bool own_launch = false) {
-    if (h->mirrored) {  // the launch itself left its result in host memory
+    if (h->mirrored && (own_launch || !h->graphed)) {  // the launch itself left its result in host memory
         if (own_launch) {
             int rc = wait_own_launch(h);
             if (rc != FCM_OK) return rc;
@@ -856,6 +857,11 @@ int fcm_solve_async(fcm_handle* h, uint8_t* d_labels) {
         a.labels = d_labels;
         a.labels_bytewise = (((uintptr_t)h->d_x ^ (uintptr_t)d_labels) & 15) ? 1 : 0;
         h->mirrored = false;
+        if (!h->graphed && h->stream) {
+            hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+            if (hipStreamIsCapturing(h->stream, &cs) != hipSuccess) (void)hipGetLastError();
+            h->graphed = cs != hipStreamCaptureStatusNone;
+        }
         hipError_t e = launch_persist(a, h->p.n_clusters, h->mclass, h->tun.unroll, h->grid,
                                       h->tun.launch == FCM_LAUNCH_COOPERATIVE, h->stream);
         if (e != hipSuccess) return dev_err(e, "persistent launch");

@@ -112,3 +112,45 @@ def test_solve_behind_a_pending_wait_limit(dev):
         r = f.solve()
         assert f.set_wait_limit(0) == 1
     assert r.status == 0 and r.J == ref.J and np.array_equal(r.centroids, ref.centroids)
+
+
+@pytest.mark.parametrize("captured", ["voxels", "levels"])
+def test_captured_solve_and_the_other_route(dev, captured):
+    """A graph of one route's asynchronous solve, replayed after solves of the
+    other route and on new contents of the input: the result read is the
+    replayed solve's."""
+    import torch
+    from paper_1601_00072_amd import FCM
+    print("CASE captured", captured, flush=True)
+    a, b = volume(dev, (64, 128, 128), 2), volume(dev, (64, 128, 128), 5)
+    x, lab = a.clone(), torch.empty_like(a)
+    routes = {"voxels": dict(driver=2, launch=1, grid=64, exchange=1), "levels": dict(driver=2, exchange=0)}
+    other = "levels" if captured == "voxels" else "voxels"
+    want = {}
+    for name, src in (("a", a), ("b", b)):
+        with FCM(src, 4) as f:
+            f.set_tuning(**routes[captured])
+            want[name] = f.solve()
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(s), FCM(x, 4) as f:
+        f.set_tuning(**routes[captured])
+        f.solve_async(lab)
+        s.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=s):
+            f.solve_async(lab)
+        f.set_tuning(**routes[other])
+        for turn in range(3):
+            for name, src in (("b", b), ("a", a)):
+                x.copy_(a if name == "b" else b)
+                f.reset()
+                f.solve()                  # the other route, on other contents
+                f.solve_async(lab)
+                assert f.result()[0].J != want[name].J
+                x.copy_(src)
+                g.replay()
+                r, _ = f.result()
+                assert r.J == want[name].J and r.iters == want[name].iters
+                assert np.array_equal(r.centroids, want[name].centroids)
+                assert np.array_equal(f.trajectory(r.iters)[0], r.centroids)
