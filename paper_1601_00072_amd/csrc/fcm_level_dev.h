@@ -322,12 +322,15 @@ __device__ __noinline__ double level_u_any(double x, const double* v, double m, 
 // S = sum w, and u_k^m = w_k u2_k / S^m because alpha (m - 1) = 1 -- so only
 // the generic m needs logarithms, one log2 and one exp2 per cluster.  Returns
 // the level's term of Eq.1, sum_k u_k^m q_k = u2_0 q_0 S^(1-m) (u2_k q_k is the
-// same for every k).  Two centroids on one level, or products out of range,
-// give non-finite values: the caller sees them in the sums and repeats the
-// pass with the ratio form (`safe`).
+// same for every k).  Products out of range (centroids far beyond the grey
+// levels) give non-finite values: the caller sees them in the sums and repeats
+// that pass with the ratio form (`safe`).  `twins`: some centroids are equal.
+// They have equal memberships, and so must keep them to the last bit: the
+// products of two equal centroids round differently, and Algorithm 1 moves
+// away from coinciding centroids exponentially once they differ.
 template <int C, int MK>
 __device__ __forceinline__ double level_u(double x, const double (&v)[C], double m, double alpha, bool safe,
-                                          const LevelScratch& sh, double (&u)[C], double (&a)[C]) {
+                                          bool twins, const LevelScratch& sh, double (&u)[C], double (&a)[C]) {
     if (safe) {
         double cv[C], cu[C], ca[C];  // copies: only they live in memory
 #pragma unroll
@@ -356,9 +359,28 @@ __device__ __forceinline__ double level_u(double x, const double (&v)[C], double
     P[C - 1] = pre[C - 1];
 #pragma unroll
     for (int k = 1; k < C - 1; ++k) P[k] = pre[k] * suf[k + 1];
+    if (twins)
+#pragma unroll
+        for (int k = 1; k < C; ++k)
+#pragma unroll
+            for (int j = k - 1; j >= 0; --j)
+                if (v[j] == v[k]) P[k] = P[j];  // the lowest such j is the last one written
     double S = P[0];
 #pragma unroll
     for (int j = 1; j < C; ++j) S += P[j];
+    if (__any(S == 0.0)) {
+        // two or more centroids on a level of this wave: every product is 0,
+        // and the zero-distance rule splits equally over them
+        const bool zero = S == 0.0;
+        double nz = 0.0;
+#pragma unroll
+        for (int k = 0; k < C; ++k) {
+            const double on = q[k] == 0.0 ? 1.0 : 0.0;
+            P[k] = zero ? on : P[k];
+            nz += on;
+        }
+        S = zero ? nz : S;
+    }
     const double r = recip_f64(S);
 #pragma unroll
     for (int k = 0; k < C; ++k) P[k] *= r;  // u2
@@ -410,6 +432,17 @@ __device__ __forceinline__ double level_u(double x, const double (&v)[C], double
     }
 }
 
+// Whether any two of the centroids (the same in every lane) are equal.
+template <int C>
+__device__ __forceinline__ bool any_equal(const double (&v)[C]) {
+    bool eq = false;
+#pragma unroll
+    for (int k = 1; k < C; ++k)
+#pragma unroll
+        for (int j = 0; j < k; ++j) eq = eq || v[j] == v[k];
+    return __builtin_amdgcn_readfirstlane(eq) != 0;
+}
+
 // Algorithm 1 on the counts: thread t < 256 holds the count of level t.
 // Called by kLvIterWaves waves (the block's other waves have ended).  Waves
 // 0..3 own 64 levels each, one per lane; per attempt at a pass a wave
@@ -438,7 +471,7 @@ __device__ __forceinline__ void level_iterate(const LevelProblem& pb, uint32_t c
     double uo[C];
 #pragma unroll
     for (int k = 0; k < C; ++k) uo[k] = 0.0;
-    bool huge = false;
+    bool huge = false, twins = false;
     if constexpr (MK == kMGeneric) {
         if (tid < kExpSteps) sh.ex[tid] = exp2((double)tid / kExpSteps);
         if (tid < kLogSteps) {
@@ -480,6 +513,7 @@ __device__ __forceinline__ void level_iterate(const LevelProblem& pb, uint32_t c
         __syncthreads();
 #pragma unroll
         for (int k = 0; k < C; ++k) v[k] = readfirst_d(sh.v[k]);
+        twins = any_equal<C>(v);
         if (wid == 4) {
             if (lane < C) pb.hist_v[lane] = sh.v[lane];
             if (pb.times && lane == 0) pb.times[0] = wall_clock64();
@@ -488,15 +522,16 @@ __device__ __forceinline__ void level_iterate(const LevelProblem& pb, uint32_t c
         p = pb.pass;
 #pragma unroll
         for (int k = 0; k < C; ++k) v[k] = readfirst_d(pb.hist_v[(int64_t)p * C + k]);
+        twins = any_equal<C>(v);
         if (work && p > 0) {
             double vp[C], t[C];
 #pragma unroll
             for (int k = 0; k < C; ++k) vp[k] = pb.hist_v[(int64_t)(p - 1) * C + k];
-            level_u<C, MK>(x, vp, pb.m, pb.alpha, false, sh, uo, t);
+            level_u<C, MK>(x, vp, pb.m, pb.alpha, false, twins, sh, uo, t);
             bool fin = true;
 #pragma unroll
             for (int k = 0; k < C; ++k) fin = fin && isfinite(uo[k]);
-            if (!fin) level_u<C, MK>(x, vp, pb.m, pb.alpha, true, sh, uo, t);
+            if (!fin) level_u<C, MK>(x, vp, pb.m, pb.alpha, true, twins, sh, uo, t);
         }
     }
     // also where v^0 was committed before this launch (a query or labels first)
@@ -525,7 +560,7 @@ __device__ __forceinline__ void level_iterate(const LevelProblem& pb, uint32_t c
         bool safe = false;
         while (true) {
             double u[C], a[C];
-            const double jt = level_u<C, MK>(x, v, pb.m, pb.alpha, safe, sh, u, a);
+            const double jt = level_u<C, MK>(x, v, pb.m, pb.alpha, safe, twins, sh, u, a);
 #pragma unroll
             for (int k = 0; k < C; ++k) a[k] *= c;
             double num[SETS], den[SETS];
@@ -601,6 +636,7 @@ __device__ __forceinline__ void level_iterate(const LevelProblem& pb, uint32_t c
                 for (int k = 0; k < C; ++k) uo[k] = u[k];
 #pragma unroll
                 for (int s = 0; s < SETS; ++s) vk[s] = vn[s];
+                safe = false;
                 ++p;
             } else if (dec & kLvRetry) {
                 safe = true;
