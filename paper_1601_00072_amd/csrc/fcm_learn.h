@@ -20,16 +20,23 @@ int mlp_warm(fcm_mlp* net, const float* d_hist, int count, double* d_v0, hipStre
 const uint16_t* mlp_bf16_weights(fcm_mlp* net, hipStream_t s, int* rc);
 
 // Histograms of `count` instances: counts is a workspace of
-// count * histogram_copies(count) * 256 words; on completion copy 0 of each
-// instance's counts holds its integer totals and hist[count][256] the
-// normalised histogram.
+// count * histogram_copies(count) * 256 words, unused (may be null) unless
+// histogram_needs_counts; hist[count][256] receives the normalised histograms.  The split follows from the host's copy of the
+// offsets (count + 1); a kHistList also needs `first` (host, count + 1 values,
+// written then; unused for one instance) on the device.
 int histogram_copies(int count);
-hipError_t launch_histogram(const uint8_t* x, const int64_t* d_offsets, int count, int64_t max_n, uint32_t* counts,
-                            float* hist, hipStream_t s);
-// the same on counters that are already zero (no memset); whether they have to be
-bool histogram_needs_zero(int count, int64_t max_n);
-hipError_t launch_histogram_counts(const uint8_t* x, const int64_t* d_offsets, int count, int64_t max_n,
-                                   uint32_t* counts, float* hist, hipStream_t s);
+enum HistForm : int { kHistRect = 0, kHistList = 1, kHistWaves = 2 };
+struct HistSplit {
+    int form;
+    int blocks;  // kHistRect: of each instance, else in all
+};
+HistSplit histogram_split(const int64_t* offsets, int count, int32_t* first);
+hipError_t launch_histogram(const uint8_t* x, const int64_t* d_offsets, const int32_t* d_first, HistSplit sp, int count,
+                            uint32_t* counts, float* hist, hipStream_t s);
+bool histogram_needs_counts(HistSplit sp);
+// the same on counters that are already zero (no memset)
+hipError_t launch_histogram_counts(const uint8_t* x, const int64_t* d_offsets, const int32_t* d_first, HistSplit sp,
+                                   int count, uint32_t* counts, float* hist, hipStream_t s);
 // One training step on `rows` samples (rows of X [.][256] and T [.][C] picked
 // by idx, or the first ones if idx is null): loss and gradient at theta, then
 // one Adam update (step counts from 1) -- or, with grad set, the gradient

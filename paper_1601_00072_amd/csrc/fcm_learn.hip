@@ -11,6 +11,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <mutex>
 
 #include "fcm.h"
@@ -26,95 +27,177 @@ namespace fcm {
 // histogram of each instance (integer counts, then normalised to sum 1)
 // ---------------------------------------------------------------------------
 
-// Block (x, y) counts its share of instance y with one counter column per lane
+// A block counts its share of an instance with one counter column per lane
 // (level_count; 4 tables shared by all lanes of a wave serialised on busy
 // levels: 1,024 slices of 256x256 took 63 us with
 // the normalisation, 23 us so).  A single block per
-// instance writes the totals and the normalised histogram itself; more blocks
+// instance writes the normalised histogram itself; more blocks
 // add into copy x % copies of the instance's counters ([count][copies][256],
-// zero at entry; the copies spread the adds to a busy level).
+// zero at entry; the copies spread the adds to a busy level).  Block (x, y) of
+// a rectangular grid takes share x of instance y; block x of a list (LIST)
+// belongs to the instance whose blocks first[i] .. first[i + 1] contain x.
+template <bool LIST>
 __global__ __launch_bounds__(kLvBlock) void hist_count_kernel(const uint8_t* x, const int64_t* offsets,
-                                                              uint32_t* counts, float* hist, int copies) {
+                                                              const int32_t* first, int count, uint32_t* counts,
+                                                              float* hist, int copies) {
     __shared__ __align__(16) uint32_t tab[256 * 64];
-    const int inst = blockIdx.y;
     const int tid = threadIdx.x;
-    level_clear(tab);
+    int inst = blockIdx.y, share = blockIdx.x, shares = gridDim.x;
+    if constexpr (LIST) {
+        const int b = blockIdx.x, lane = tid & 63;
+        int lo = 0, hi = count;  // first[lo] <= b < first[hi]; 64 places looked at together
+        while (hi - lo > 1) {
+            const int step = (hi - lo + 63) / 64, i = lo + lane * step;
+            const uint64_t below = __ballot(i < hi && first[i < hi ? i : lo] <= b);  // a run of lanes from lane 0
+            lo += (__popcll(below) - 1) * step;
+            hi = lo + step < hi ? lo + step : hi;
+        }
+        inst = lo;
+        share = b - first[inst];
+        shares = first[inst + 1] - first[inst];
+    }
     const int64_t b0 = offsets[inst], n = offsets[inst + 1] - b0;
     const uint8_t* xi = x + b0;
     const int64_t lead = (int64_t)((16 - ((uintptr_t)xi & 15)) & 15);
     const int64_t head = n < lead ? n : lead;
     const int64_t nbody = (n - head) / 16;
+    if (share && (int64_t)share * kLvBlock >= nbody) return;  // a smaller instance than the grid's largest
+    level_clear(tab);
     __syncthreads();
     char* t8 = reinterpret_cast<char*>(tab);
-    level_count(t8, reinterpret_cast<const uint4*>(xi + head), (int64_t)blockIdx.x * kLvBlock + tid, nbody,
-                (int64_t)gridDim.x * kLvBlock);
-    if (blockIdx.x == 0) level_ragged(t8, xi, n, head, nbody);
+    level_count(t8, reinterpret_cast<const uint4*>(xi + head), (int64_t)share * kLvBlock + tid, nbody,
+                (int64_t)shares * kLvBlock);
+    if (share == 0) level_ragged(t8, xi, n, head, nbody);
     __syncthreads();
     const uint32_t c = level_total(tab);
     if (tid >= 256) return;
-    uint32_t* ci = counts + (int64_t)inst * copies * 256;
-    if (gridDim.x == 1) {
-        ci[tid] = c;
+    if (!LIST && shares == 1)
         hist[(int64_t)inst * 256 + tid] = hist_norm(c, n);
-    } else if (c) {
-        atomicAdd(ci + (blockIdx.x % copies) * 256 + tid, c);
+    else if (c)
+        atomicAdd(counts + ((int64_t)inst * copies + share % copies) * 256 + tid, c);
+}
+
+// Small instances: one wave each, with a table of its own.  Clearing and
+// adding up 64 columns takes a block 2.4 us whatever it counts, and two blocks
+// fill a CU; for few voxels the adds that serialise on a busy level cost less
+// (65,536 instances of 64 voxels: 302 us a block each, 36 a wave each; 10,000
+// of 1,024, half of them on one level: 50 and 25; 4,096 of 4,096: 24 and 33).
+constexpr int64_t kHistWaveVoxels = 1024;
+
+__global__ __launch_bounds__(512) void hist_waves_kernel(const uint8_t* x, const int64_t* offsets, int count,
+                                                         float* hist) {
+    __shared__ uint32_t tabs[8][256];
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    const int64_t inst = (int64_t)blockIdx.x * 8 + wid;
+    if (inst >= count) return;  // waves share nothing: no barrier below
+    uint32_t* tab = tabs[wid];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) tab[64 * j + lane] = 0u;
+    const int64_t b0 = offsets[inst], n = offsets[inst + 1] - b0;
+    const uint8_t* xi = x + b0;
+    const int64_t lead = (int64_t)((16 - ((uintptr_t)xi & 15)) & 15);
+    const int64_t head = n < lead ? n : lead;
+    const int64_t nbody = (n - head) / 16, tail0 = head + 16 * nbody, nr = head + (n - tail0);
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    const uint4* body = reinterpret_cast<const uint4*>(xi + head);
+    for (int64_t c = lane; c < nbody; c += 64) {
+        const uint4 w = body[c];
+        const uint32_t words[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int b = 0; b < 4; ++b) atomicAdd(tab + ((words[q] >> (8 * b)) & 0xFFu), 1u);
+    }
+    if (lane < nr) atomicAdd(tab + xi[lane < head ? lane : tail0 + (lane - head)], 1u);  // nr < 32
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const uint32_t c = tab[64 * j + lane];
+        hist[inst * 256 + 64 * j + lane] = hist_norm(c, n);
     }
 }
 
-// totals of the copies -> copy 0 (integer counts) and count / n (FP64, stored FP32)
-__global__ __launch_bounds__(kBlock) void hist_norm_kernel(uint32_t* counts, const int64_t* offsets, float* hist,
+// totals of the copies, as count / n (FP64, stored FP32)
+__global__ __launch_bounds__(kBlock) void hist_norm_kernel(const uint32_t* counts, const int64_t* offsets, float* hist,
                                                            int copies) {
     const int inst = blockIdx.x;
-    uint32_t* ci = counts + (int64_t)inst * copies * 256;
+    const uint32_t* ci = counts + (int64_t)inst * copies * 256;
     uint32_t total = 0u;
     for (int c = 0; c < copies; ++c) total += ci[c * 256 + threadIdx.x];
-    ci[threadIdx.x] = total;
     hist[(int64_t)inst * 256 + threadIdx.x] = hist_norm(total, offsets[inst + 1] - offsets[inst]);
 }
 
 int histogram_copies(int count) { return count == 1 ? kHistCopies : 1; }
 
-// Blocks per instance: enough that the launch gives every CU two, with 16,384
-// (below that a block's clearing and totals outweigh its count) to 131,072
-// voxels each; a single instance takes at most one per CU (the reads of two
-// are no faster).
-static int hist_blocks(int count, int64_t max_n) {
-    constexpr int64_t kCus = 256, kMin = 16384, kMax = 131072;
-    int64_t share = max_n * count / (2 * kCus);
-    share = share < kMin ? kMin : (share > kMax && count > 1 ? kMax : share);
-    int64_t gx = (max_n + share - 1) / share;
-    if (count == 1 && gx > kCus) gx = kCus;
-    return (int)(gx < 1 ? 1 : (gx > 4096 ? 4096 : gx));
+// How the instances are dealt to blocks.  A block's share is between 16,384
+// (below that a block's clearing and totals outweigh its count) and 131,072
+// voxels, such that the launch gives every CU two blocks; a single instance
+// takes at most one per CU (the reads of two are no faster).  Equal numbers of
+// blocks for every instance (kHistRect) unless that would launch more than
+// twice the blocks that the instances need, most of them without a share
+// (one volume of 67M voxels and 512 slices of 256x256: the call took
+// 940 us, 92 as a list of blocks; with 5,000 slices of 64x64: 8,420 and 354):
+// then kHistList.  More small instances than fit at once: a wave each (kHistWaves).
+HistSplit histogram_split(const int64_t* offsets, int count, int32_t* first) {
+    static constexpr int64_t kCus = 256, kMin = 16384, kMax = 131072;
+    auto clamped = [](int64_t v) { return std::min(std::max(v, kMin), kMax); };
+    auto blocks = [](int64_t n, int64_t share) { return std::min<int64_t>((n + share - 1) / share, 4096); };
+    int64_t max_n = 0;
+    for (int i = 0; i < count; ++i) max_n = std::max(max_n, offsets[i + 1] - offsets[i]);
+    if (count >= 2 * kCus && max_n <= kHistWaveVoxels) return {kHistWaves, (count + 7) / 8};
+    if (count == 1) return {kHistRect, (int)std::min(blocks(max_n, std::max(kMin, max_n / (2 * kCus))), kCus)};
+    const int64_t gx = blocks(max_n, clamped(max_n * count / (2 * kCus)));
+    const int64_t share = clamped(offsets[count] / (2 * kCus));
+    int64_t need = 0;
+    for (int i = 0; i < count; ++i) need += blocks(offsets[i + 1] - offsets[i], share);
+    if (gx * count <= 2 * need) return {kHistRect, (int)gx};
+    first[0] = 0;
+    for (int i = 0; i < count; ++i) first[i + 1] = first[i] + (int32_t)blocks(offsets[i + 1] - offsets[i], share);
+    return {kHistList, (int)need};
 }
 
-bool histogram_needs_zero(int count, int64_t max_n) { return hist_blocks(count, max_n) > 1; }
+bool histogram_needs_counts(HistSplit sp) { return sp.form == kHistList || (sp.form == kHistRect && sp.blocks > 1); }
 
 // counting and normalisation on counters that are already zero (where that is needed)
-hipError_t launch_histogram_counts(const uint8_t* x, const int64_t* d_offsets, int count, int64_t max_n,
-                                   uint32_t* counts, float* hist, hipStream_t s) {
+hipError_t launch_histogram_counts(const uint8_t* x, const int64_t* d_offsets, const int32_t* d_first, HistSplit sp,
+                                   int count, uint32_t* counts, float* hist, hipStream_t s) {
     const int copies = histogram_copies(count);
     hipError_t e;
-    const int gx = hist_blocks(count, max_n);
-    constexpr int kMaxY = 65535;  // grid y limit: instances per launch
-    for (int c0 = 0; c0 < count; c0 += kMaxY) {
-        const int cnt = count - c0 < kMaxY ? count - c0 : kMaxY;
-        hipLaunchKernelGGL(hist_count_kernel, dim3(gx, cnt), dim3(kLvBlock), 0, s, x, d_offsets + c0,
-                           counts + (int64_t)c0 * copies * 256, hist + (int64_t)c0 * 256, copies);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
+    if (sp.form == kHistWaves) {
+        hipLaunchKernelGGL(hist_waves_kernel, dim3(sp.blocks), dim3(512), 0, s, x, d_offsets, count, hist);
+        return hipGetLastError();
     }
-    if (gx == 1) return hipSuccess;
+    if (sp.form == kHistList) {
+        hipLaunchKernelGGL(hist_count_kernel<true>, dim3(sp.blocks), dim3(kLvBlock), 0, s, x, d_offsets, d_first, count,
+                           counts, hist, copies);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+    } else {
+        constexpr int kMaxY = 65535;  // grid y limit: instances per launch
+        for (int c0 = 0; c0 < count; c0 += kMaxY) {
+            const int cnt = count - c0 < kMaxY ? count - c0 : kMaxY;
+            hipLaunchKernelGGL(hist_count_kernel<false>, dim3(sp.blocks, cnt), dim3(kLvBlock), 0, s, x, d_offsets + c0,
+                               static_cast<const int32_t*>(nullptr), cnt, counts + (int64_t)c0 * copies * 256,
+                               hist + (int64_t)c0 * 256, copies);
+            if ((e = hipGetLastError()) != hipSuccess) return e;
+        }
+        if (sp.blocks == 1) return hipSuccess;
+    }
     hipLaunchKernelGGL(hist_norm_kernel, dim3(count), dim3(256), 0, s, counts, d_offsets, hist, copies);
     return hipGetLastError();
 }
 
-hipError_t launch_histogram(const uint8_t* x, const int64_t* d_offsets, int count, int64_t max_n, uint32_t* counts,
-                            float* hist, hipStream_t s) {
-    if (histogram_needs_zero(count, max_n)) {
+hipError_t launch_histogram(const uint8_t* x, const int64_t* d_offsets, const int32_t* d_first, HistSplit sp, int count,
+                            uint32_t* counts, float* hist, hipStream_t s) {
+    if (histogram_needs_counts(sp)) {
         const int64_t words = 256 * (int64_t)count * histogram_copies(count);
         hipError_t e = hipMemsetAsync(counts, 0, sizeof(uint32_t) * (size_t)words, s);
         if (e != hipSuccess) return e;
     }
-    return launch_histogram_counts(x, d_offsets, count, max_n, counts, hist, s);
+    return launch_histogram_counts(x, d_offsets, d_first, sp, count, counts, hist, s);
 }
 
 // ---------------------------------------------------------------------------
@@ -673,11 +756,12 @@ hipError_t launch_mlp_starts(const void* w, const float* X, int count, int C, do
 // ---------------------------------------------------------------------------
 
 // The workspace of fcm_histogram in a fixed device array: the instance
-// offsets, then the counters ([count][copies][256]; one instance uses
+// offsets, the first blocks of a list, then the counters ([count][copies][256]; one instance uses
 // kHistCopies copies, more instances one copy each).  Each device holds its
 // own copy of the array for the life of the process.
 constexpr int kNoAllocMaxCount = 1024;
-constexpr size_t kNoAllocOffBytes = (sizeof(int64_t) * (kNoAllocMaxCount + 1) + 255) / 256 * 256;
+constexpr size_t kNoAllocOffBytes =
+    ((sizeof(int64_t) + sizeof(int32_t)) * (kNoAllocMaxCount + 1) + 255) / 256 * 256;
 constexpr size_t kNoAllocCountWords = 256 * (size_t)kNoAllocMaxCount;
 static_assert((size_t)kHistCopies <= (size_t)kNoAllocMaxCount, "one instance's copies fit");
 static __device__ __align__(256) unsigned char scratch[kNoAllocOffBytes + sizeof(uint32_t) * kNoAllocCountWords];
@@ -733,16 +817,21 @@ extern "C" int fcm_histogram_noalloc(const uint8_t* d_x, const int64_t* offsets,
     if (rc != FCM_OK) return rc;
     hipStream_t s = (hipStream_t)stream;
     int64_t* d_off = reinterpret_cast<int64_t*>(base);
+    int32_t* d_first = reinterpret_cast<int32_t*>(d_off + kNoAllocMaxCount + 1);
     uint32_t* d_counts = reinterpret_cast<uint32_t*>(static_cast<unsigned char*>(base) + kNoAllocOffBytes);
+    int32_t first[kNoAllocMaxCount + 1];
+    const HistSplit sp = histogram_split(offsets, count, first);
     FCM_HIP(hipMemcpyAsync(d_off, offsets, sizeof(int64_t) * ((size_t)count + 1), hipMemcpyHostToDevice, s));
-    if (histogram_needs_zero(count, max_n)) {
+    if (sp.form == kHistList)
+        FCM_HIP(hipMemcpyAsync(d_first, first, sizeof(int32_t) * ((size_t)count + 1), hipMemcpyHostToDevice, s));
+    if (histogram_needs_counts(sp)) {
         // the array keeps the previous call's counts: clear them (a kernel, no memset node)
         const int64_t words = 256 * (int64_t)count * histogram_copies(count);
         const int zgrid = (int)((words + kBlock - 1) / kBlock < 1024 ? (words + kBlock - 1) / kBlock : 1024);
         hipLaunchKernelGGL(zero_words_kernel, dim3(zgrid), dim3(kBlock), 0, s, d_counts, words);
         FCM_HIP(hipGetLastError());
     }
-    FCM_HIP(launch_histogram_counts(d_x, d_off, count, max_n, d_counts, d_hist, s));
+    FCM_HIP(launch_histogram_counts(d_x, d_off, d_first, sp, count, d_counts, d_hist, s));
     FCM_HIP(hipStreamSynchronize(s));
     return FCM_OK;
 }

@@ -13,6 +13,7 @@
 #include <cstdint>
 #include <cstdio>
 #include <cstring>
+#include <memory>
 #include <new>
 #include <string>
 #include <vector>
@@ -430,14 +431,22 @@ int fcm_histogram(const uint8_t* d_x, const int64_t* offsets, int32_t count, flo
     }
     if (max_n > (int64_t)UINT32_MAX) return FCM_EINVAL;
     hipStream_t s = (hipStream_t)stream;
-    // one temporary: the counters, then the offsets
-    const size_t b_counts = sizeof(uint32_t) * 256 * (size_t)count * histogram_copies(count);
+    const size_t cnt = (size_t)count;
+    std::unique_ptr<int32_t[]> first(new (std::nothrow) int32_t[cnt + 1]);
+    if (!first) return FCM_ENOMEM;
+    const HistSplit sp = histogram_split(offsets, count, first.get());
+    // one temporary: the counters, then the offsets and the first blocks
+    const size_t b_counts = histogram_needs_counts(sp) ? sizeof(uint32_t) * 256 * cnt * histogram_copies(count) : 0;
     uint32_t* d_counts = nullptr;
-    if (hipMalloc(&d_counts, b_counts + sizeof(int64_t) * ((size_t)count + 1)) != hipSuccess) return FCM_ENOMEM;
+    if (hipMalloc(&d_counts, b_counts + (sizeof(int64_t) + sizeof(int32_t)) * (cnt + 1)) != hipSuccess)
+        return FCM_ENOMEM;
     int64_t* d_off = reinterpret_cast<int64_t*>(reinterpret_cast<char*>(d_counts) + b_counts);
+    int32_t* d_first = reinterpret_cast<int32_t*>(d_off + cnt + 1);
     int rc = FCM_OK;
-    hipError_t e = hipMemcpyAsync(d_off, offsets, sizeof(int64_t) * ((size_t)count + 1), hipMemcpyHostToDevice, s);
-    if (e == hipSuccess) e = launch_histogram(d_x, d_off, count, max_n, d_counts, d_hist, s);
+    hipError_t e = hipMemcpyAsync(d_off, offsets, sizeof(int64_t) * (cnt + 1), hipMemcpyHostToDevice, s);
+    if (e == hipSuccess && sp.form == kHistList)
+        e = hipMemcpyAsync(d_first, first.get(), sizeof(int32_t) * (cnt + 1), hipMemcpyHostToDevice, s);
+    if (e == hipSuccess) e = launch_histogram(d_x, d_off, d_first, sp, count, d_counts, d_hist, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) rc = dev_err(e, "fcm_histogram");
     (void)hipFree(d_counts);

@@ -16,6 +16,7 @@
 #include <cstdint>
 #include <cstddef>
 #include <cstring>
+#include <memory>
 #include <new>
 #include <string>
 #include <vector>
@@ -136,7 +137,7 @@ struct fcm_handle {
 
     // warm start workspace (first fcm_solve_warm)
     int64_t* d_woff = nullptr;     // {0, n}
-    uint32_t* d_wcounts = nullptr; // [kHistCopies][256] histogram workspace (copy 0: totals)
+    uint32_t* d_wcounts = nullptr; // [kHistCopies][256] histogram workspace
     float* d_whist = nullptr;      // [256]
     double* d_wv0 = nullptr;       // [kMaxC] learned start
     uint32_t* d_ghist = nullptr;   // [2][kHistCopies][256] counters of the in-kernel histogram; a learned
@@ -914,7 +915,9 @@ int fcm_solve_warm(fcm_handle* h, fcm_mlp* net, int32_t check, fcm_result* out, 
         h->p.init = kInitLearnedFused;
     } else {
         if ((rc = ensure_level_ws(h)) != FCM_OK) return rc;
-        FCM_HIP(launch_histogram(h->d_x, h->d_woff, 1, h->n, h->d_wcounts, h->d_whist, h->stream));
+        const int64_t range[2] = {0, h->n};
+        FCM_HIP(launch_histogram(h->d_x, h->d_woff, nullptr, histogram_split(range, 1, nullptr), 1, h->d_wcounts,
+                                 h->d_whist, h->stream));
         if ((rc = mlp_warm(net, h->d_whist, 1, h->d_wv0, h->stream)) != FCM_OK) return rc;
         h->p.init = FCM_INIT_DEVICE;
         h->dv0 = h->d_wv0;
@@ -1058,7 +1061,8 @@ struct fcm_batch {
     uint32_t* d_ltickets = nullptr; // [count]
 
     // learned starts (first fcm_batch_set_start with a network)
-    int64_t* d_off = nullptr;      // offsets [count + 1]
+    int64_t* d_off = nullptr;      // offsets [count + 1], then the histogram's first blocks [count + 1]
+    HistSplit hsplit{};
     uint32_t* d_counts = nullptr;  // [count][256]
     float* d_whist = nullptr;      // [count][256]
     double* d_wv0 = nullptr;       // [count][kMaxC]
@@ -1382,16 +1386,25 @@ int fcm_batch_set_start(fcm_batch* b, fcm_mlp* net, const uint8_t* use_learned) 
                 return FCM_ENOMEM;
             if (hipMalloc(&b->d_whist, sizeof(float) * 256 * cnt) != hipSuccess) return FCM_ENOMEM;
             if (hipMalloc(&b->d_wv0, sizeof(double) * kMaxC * cnt) != hipSuccess) return FCM_ENOMEM;
+            std::unique_ptr<int32_t[]> first(new (std::nothrow) int32_t[cnt + 1]);
+            if (!first) return FCM_ENOMEM;
             int64_t* off = nullptr;
-            if (hipMalloc(&off, sizeof(int64_t) * (cnt + 1)) != hipSuccess) return FCM_ENOMEM;
-            FCM_HIP(hipMemcpyAsync(off, b->offsets.data(), sizeof(int64_t) * (cnt + 1), hipMemcpyHostToDevice,
-                                   b->stream));
-            FCM_HIP(hipStreamSynchronize(b->stream));
+            if (hipMalloc(&off, (sizeof(int64_t) + sizeof(int32_t)) * (cnt + 1)) != hipSuccess) return FCM_ENOMEM;
+            b->hsplit = histogram_split(b->offsets.data(), b->count, first.get());
+            hipError_t e = hipMemcpyAsync(off, b->offsets.data(), sizeof(int64_t) * (cnt + 1), hipMemcpyHostToDevice,
+                                          b->stream);
+            if (e == hipSuccess && b->hsplit.form == kHistList)
+                e = hipMemcpyAsync(off + cnt + 1, first.get(), sizeof(int32_t) * (cnt + 1), hipMemcpyHostToDevice,
+                                   b->stream);
+            if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
+            if (e != hipSuccess) {
+                (void)hipFree(off);
+                return dev_err(e, "hipMemcpyAsync");
+            }
             b->d_off = off;
         }
-        int64_t max_n = 1;
-        for (int32_t i = 0; i < b->count; ++i) max_n = std::max<int64_t>(max_n, b->h_inst[i].n);
-        FCM_HIP(launch_histogram(b->d_x, b->d_off, b->count, max_n, b->d_counts, b->d_whist, b->stream));
+        FCM_HIP(launch_histogram(b->d_x, b->d_off, reinterpret_cast<const int32_t*>(b->d_off + cnt + 1), b->hsplit,
+                                 b->count, b->d_counts, b->d_whist, b->stream));
         int rc = mlp_warm(net, b->d_whist, b->count, b->d_wv0, b->stream);
         if (rc != FCM_OK) return rc;
     }
