@@ -249,7 +249,9 @@ void fcm_destroy(fcm_handle* h);
 typedef struct fcm_batch fcm_batch;
 
 /* Validates everything before any HIP call (FCM_EINVAL), allocates the
- * workspace (tile table, per-instance state and history), enqueues nothing.
+ * workspace (tile table, per-instance state and history; that of the per-voxel
+ * passes by the first call that sets a block size or a tiling, which can return
+ * FCM_ENOMEM), enqueues nothing.
  * The solve is one ordinary launch: its blocks take tiles of whichever
  * instance has work ready and never wait for one another's work in
  * progress, so the grid need not be resident at once. */

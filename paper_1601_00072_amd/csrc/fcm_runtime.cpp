@@ -1037,28 +1037,31 @@ struct fcm_batch {
     int64_t hist_total = 0;
 
     BatchInst* d_inst = nullptr;
-    int32_t* d_ntiles = nullptr;
-    BatchTile* d_tiles = nullptr;
     BatchRec* d_recs = nullptr;
     double* d_hist = nullptr;
+    // per-voxel passes (batch_build_tiles)
+    int32_t* d_ntiles = nullptr;
+    BatchTile* d_tiles = nullptr;
     uint64_t* d_rows = nullptr;
     uint64_t* d_dec = nullptr;
     uint64_t* d_ctl = nullptr;
     BatchSync* d_sync = nullptr;
     int64_t tiles_cap = 0;     // capacity of d_tiles / d_rows
-    BatchRec* h_recs = nullptr;
+    BatchRec* h_recs = nullptr;    // pinned, and behind them h_sync
     BatchSync* h_sync = nullptr;
     uint64_t* h_ctl = nullptr;
 
     // solve over the grey levels (until the caller sets a block size or a tiling)
     bool tiled = false;            // the caller's tiles: per-voxel passes
     int32_t level_tiles = 0;
-    void* d_level = nullptr;       // one allocation: counters, m, tiles, tile counts, tickets
+    void* d_level = nullptr;       // one allocation: instances, m, tiles, tile counts, counters, tickets
     uint32_t* d_lcounts = nullptr; // [count][256]
     double* d_lm = nullptr;        // [count]
     BatchTile* d_ltiles = nullptr;
     int32_t* d_lntiles = nullptr;  // [count]
     uint32_t* d_ltickets = nullptr; // [count]
+    BatchTile* d_labtiles = nullptr; // what the label launch deals out
+    int32_t label_tiles = 0;
 
     // learned starts (first fcm_batch_set_start with a network)
     int64_t* d_off = nullptr;      // offsets [count + 1], then the histogram's first blocks [count + 1]
@@ -1081,14 +1084,31 @@ void batch_free_tiles(fcm_batch* b) {
 void batch_release(fcm_batch* b) {
     if (!b) return;
     batch_free_tiles(b);
-    for (void* p : {(void*)b->d_inst, (void*)b->d_ntiles, (void*)b->d_recs, (void*)b->d_hist, (void*)b->d_dec,
+    if (b->d_inst && !b->d_level) (void)hipFree(b->d_inst);  // else part of that allocation
+    for (void* p : {(void*)b->d_ntiles, (void*)b->d_recs, (void*)b->d_hist, (void*)b->d_dec,
                     (void*)b->d_ctl, (void*)b->d_sync, (void*)b->d_off, (void*)b->d_counts, (void*)b->d_whist,
                     (void*)b->d_wv0, b->d_level})
         if (p) (void)hipFree(p);
     if (b->h_recs) (void)hipHostFree(b->h_recs);
-    if (b->h_sync) (void)hipHostFree(b->h_sync);
     if (b->h_ctl) (void)hipHostFree(b->h_ctl);
     delete b;
+}
+
+// Tiles of `chunks` chunks that cover instance i, appended; returns their number.
+int32_t cut_instance(const BatchInst& in, int32_t i, int64_t chunks, std::vector<BatchTile>& tiles) {
+    int64_t c0 = 0;
+    int32_t count = 0;
+    do {
+        BatchTile t{};
+        t.c0 = c0;
+        t.c1 = std::min<int64_t>(in.nbody, c0 + chunks);
+        t.inst = i;
+        t.ragged = c0 == 0 ? 1 : 0;
+        tiles.push_back(t);
+        ++count;
+        c0 = t.c1;
+    } while (c0 < in.nbody);
+    return count;
 }
 
 // Cut every instance into two tile sets -- coarse tiles of 256 *
@@ -1097,7 +1117,7 @@ void batch_release(fcm_batch* b) {
 // instance would need more than kBatchMaxTiles tiles -- and upload the
 // instance and tile tables (the coarse tiles of every instance first).  The
 // tile-indexed buffers grow as needed and are cleared, so no stale tag can
-// match.
+// match.  A batch that only solves over the grey levels has none of this.
 int batch_build_tiles(fcm_batch* b) {
     b->h_tiles.clear();
     std::vector<int32_t> nt_of((size_t)b->count * 2);
@@ -1108,17 +1128,7 @@ int batch_build_tiles(fcm_batch* b) {
             const int64_t tile_chunks =
                 std::max<int64_t>((int64_t)b->block * cpt, (in.nbody + kBatchMaxTiles - 1) / kBatchMaxTiles);
             const int32_t first = (int32_t)b->h_tiles.size();
-            int64_t c0 = 0;
-            do {
-                BatchTile t{};
-                t.c0 = c0;
-                t.c1 = std::min<int64_t>(in.nbody, c0 + tile_chunks);
-                t.inst = i;
-                t.ragged = c0 == 0 ? 1 : 0;
-                b->h_tiles.push_back(t);
-                c0 = t.c1;
-            } while (c0 < in.nbody);
-            const int32_t count = (int32_t)b->h_tiles.size() - first;
+            const int32_t count = cut_instance(in, i, tile_chunks, b->h_tiles);
             (set ? in.tile0f : in.tile0) = first;
             (set ? in.ntilesf : in.ntiles) = count;
             nt_of[(size_t)i * 2 + set] = count;
@@ -1127,10 +1137,21 @@ int batch_build_tiles(fcm_batch* b) {
     }
     const int64_t nt = (int64_t)b->h_tiles.size();
     if (nt > (int64_t)INT32_MAX) return FCM_EINVAL;
+    const size_t cnt = (size_t)b->count;
+    if (!b->d_inst && hipMalloc(&b->d_inst, sizeof(BatchInst) * cnt) != hipSuccess) return FCM_ENOMEM;
+    if (!b->d_ntiles && hipMalloc(&b->d_ntiles, sizeof(int32_t) * 2 * cnt) != hipSuccess) return FCM_ENOMEM;
+    if (!b->d_dec && hipMalloc(&b->d_dec, sizeof(uint64_t) * kBatchDecWords * cnt) != hipSuccess) return FCM_ENOMEM;
+    if (!b->d_ctl && hipMalloc(&b->d_ctl, sizeof(uint64_t) * cnt) != hipSuccess) return FCM_ENOMEM;
+    if (!b->d_sync && hipMalloc(&b->d_sync, sizeof(BatchSync)) != hipSuccess) return FCM_ENOMEM;
+    if (!b->h_ctl && hipHostMalloc(&b->h_ctl, sizeof(uint64_t) * cnt, hipHostMallocDefault) != hipSuccess)
+        return FCM_ENOMEM;
     if (nt > b->tiles_cap) {
         batch_free_tiles(b);
-        if (hipMalloc(&b->d_tiles, sizeof(BatchTile) * nt) != hipSuccess) return FCM_ENOMEM;
-        if (hipMalloc(&b->d_rows, sizeof(uint64_t) * kBatchRowWords * nt) != hipSuccess) return FCM_ENOMEM;
+        if (hipMalloc(&b->d_tiles, sizeof(BatchTile) * nt) != hipSuccess ||
+            hipMalloc(&b->d_rows, sizeof(uint64_t) * kBatchRowWords * nt) != hipSuccess) {
+            batch_free_tiles(b);
+            return FCM_ENOMEM;
+        }
         b->tiles_cap = nt;
     }
     FCM_HIP(hipMemsetAsync(b->d_rows, 0, sizeof(uint64_t) * kBatchRowWords * b->tiles_cap, b->stream));
@@ -1149,6 +1170,15 @@ int batch_build_tiles(fcm_batch* b) {
     return FCM_OK;
 }
 
+// The caller's tiles from here on; without the memory for them a batch goes
+// on solving over the grey levels.
+int batch_retile(fcm_batch* b) {
+    b->solved = false;
+    const int rc = batch_build_tiles(b);
+    b->tiled = b->tiled || rc == FCM_OK;
+    return rc;
+}
+
 // Tiles and workspace of the level solve.  A tile is one block's share of an
 // instance: enough tiles to give every CU two, between 16,384 voxels (below
 // that a block's fixed cost, clearing and adding its counters, outweighs the
@@ -1165,51 +1195,50 @@ int batch_build_levels(fcm_batch* b) {
         }
     const int64_t share = b->offsets.back() / (2 * (int64_t)b->ncu);
     const int64_t chunks = std::min(kLevelTileMax, std::max(kLevelTileMin, share)) / 16;
-    std::vector<int32_t> order(cnt), nt(cnt);
+    std::vector<int32_t> order(cnt);
     for (size_t i = 0; i < cnt; ++i) order[i] = (int32_t)i;
-    std::stable_sort(order.begin(), order.end(), [&](int32_t p, int32_t q) {
+    auto before = [&](int32_t p, int32_t q) {
         const BatchInst &x = b->h_inst[(size_t)p], &y = b->h_inst[(size_t)q];
         return x.C != y.C ? x.C > y.C : x.n > y.n;
-    });
-    std::vector<BatchTile> tiles;
-    for (int32_t i : order) {
-        const BatchInst& in = b->h_inst[(size_t)i];
-        int64_t c0 = 0;
-        do {
-            BatchTile t{};
-            t.c0 = c0;
-            t.c1 = std::min<int64_t>(in.nbody, c0 + chunks);
-            t.inst = i;
-            t.ragged = c0 == 0 ? 1 : 0;
-            tiles.push_back(t);
-            ++nt[(size_t)i];
-            c0 = t.c1;
-        } while (c0 < in.nbody);
-    }
+    };
+    if (!std::is_sorted(order.begin(), order.end(), before)) std::stable_sort(order.begin(), order.end(), before);
+    std::vector<BatchTile> tiles;  // of the solve, then (where they differ) of the labels
+    std::vector<int32_t> nt(cnt);
+    for (int32_t i : order) nt[(size_t)i] = cut_instance(b->h_inst[(size_t)i], i, chunks, tiles);
     if (tiles.size() > (size_t)INT32_MAX) {
         b->tiled = true;
         return FCM_OK;
     }
-    std::vector<double> m(cnt);
-    for (size_t i = 0; i < cnt; ++i) m[i] = b->p[i].m;
+    const size_t nsolve = tiles.size();
+    // labels have no count to clear and add: tiles of at most 32,768 voxels
+    constexpr int64_t kLabelChunks = (int64_t)kBatchBlock * kBatchChunks;
+    if (chunks > kLabelChunks)
+        for (int32_t i = 0; i < b->count; ++i) cut_instance(b->h_inst[(size_t)i], i, kLabelChunks, tiles);
+    // one upload (each waits for a copy of its own) and one clear: the
+    // instances, m, the tiles and their numbers, then the counters and tickets
     auto up = [](size_t v) { return (v + 255) / 256 * 256; };
-    const size_t o_m = up(sizeof(uint32_t) * 256 * cnt), o_tiles = o_m + up(sizeof(double) * cnt);
-    const size_t o_nt = o_tiles + up(sizeof(BatchTile) * tiles.size()), o_tk = o_nt + up(sizeof(int32_t) * cnt);
-    if (hipMalloc(&b->d_level, o_tk + sizeof(uint32_t) * cnt) != hipSuccess) return FCM_ENOMEM;
+    const size_t o_m = up(sizeof(BatchInst) * cnt), o_tiles = o_m + up(sizeof(double) * cnt);
+    const size_t o_nt = o_tiles + up(sizeof(BatchTile) * tiles.size()), o_cnt = o_nt + up(sizeof(int32_t) * cnt);
+    const size_t o_tk = o_cnt + sizeof(uint32_t) * 256 * cnt, end = o_tk + sizeof(uint32_t) * cnt;
+    std::vector<char> table(o_nt + sizeof(int32_t) * cnt);
+    std::memcpy(table.data(), b->h_inst.data(), sizeof(BatchInst) * cnt);
+    for (size_t i = 0; i < cnt; ++i) std::memcpy(table.data() + o_m + sizeof(double) * i, &b->p[i].m, sizeof(double));
+    std::memcpy(table.data() + o_tiles, tiles.data(), sizeof(BatchTile) * tiles.size());
+    std::memcpy(table.data() + o_nt, nt.data(), sizeof(int32_t) * cnt);
+    if (hipMalloc(&b->d_level, end) != hipSuccess) return FCM_ENOMEM;
     char* at = static_cast<char*>(b->d_level);
-    b->d_lcounts = reinterpret_cast<uint32_t*>(at);
+    b->d_inst = reinterpret_cast<BatchInst*>(at);
     b->d_lm = reinterpret_cast<double*>(at + o_m);
     b->d_ltiles = reinterpret_cast<BatchTile*>(at + o_tiles);
     b->d_lntiles = reinterpret_cast<int32_t*>(at + o_nt);
+    b->d_lcounts = reinterpret_cast<uint32_t*>(at + o_cnt);
     b->d_ltickets = reinterpret_cast<uint32_t*>(at + o_tk);
-    b->level_tiles = (int32_t)tiles.size();
-    FCM_HIP(hipMemsetAsync(b->d_lcounts, 0, sizeof(uint32_t) * 256 * cnt, b->stream));
-    FCM_HIP(hipMemsetAsync(b->d_ltickets, 0, sizeof(uint32_t) * cnt, b->stream));
-    FCM_HIP(hipMemcpyAsync(b->d_lm, m.data(), sizeof(double) * cnt, hipMemcpyHostToDevice, b->stream));
-    FCM_HIP(hipMemcpyAsync(b->d_ltiles, tiles.data(), sizeof(BatchTile) * tiles.size(), hipMemcpyHostToDevice,
-                           b->stream));
-    FCM_HIP(hipMemcpyAsync(b->d_lntiles, nt.data(), sizeof(int32_t) * cnt, hipMemcpyHostToDevice, b->stream));
-    FCM_HIP(hipStreamSynchronize(b->stream));  // the host tables end here
+    b->level_tiles = (int32_t)nsolve;
+    b->d_labtiles = b->d_ltiles + (tiles.size() > nsolve ? nsolve : 0);
+    b->label_tiles = (int32_t)(tiles.size() > nsolve ? tiles.size() - nsolve : nsolve);
+    FCM_HIP(hipMemsetAsync(b->d_lcounts, 0, end - o_cnt, b->stream));
+    FCM_HIP(hipMemcpyAsync(at, table.data(), table.size(), hipMemcpyHostToDevice, b->stream));
+    FCM_HIP(hipStreamSynchronize(b->stream));  // the host table ends here
     return FCM_OK;
 }
 
@@ -1324,22 +1353,16 @@ int fcm_batch_init(fcm_batch** out, const uint8_t* d_x, const int64_t* offsets, 
     if ((e = batch_max_grid(b->block, b->ncu, &b->max_grid)) != hipSuccess) return fail(dev_err(e, "occupancy"));
     b->max_grid = std::max(1, std::min(b->max_grid, kMaxPersistGrid));
 
-    if (hipMalloc(&b->d_inst, sizeof(BatchInst) * count) != hipSuccess) return fail(FCM_ENOMEM);
-    if (hipMalloc(&b->d_ntiles, sizeof(int32_t) * 2 * count) != hipSuccess) return fail(FCM_ENOMEM);
     if (hipMalloc(&b->d_recs, sizeof(BatchRec) * count) != hipSuccess) return fail(FCM_ENOMEM);
     if (hipMalloc(&b->d_hist, sizeof(double) * hist) != hipSuccess) return fail(FCM_ENOMEM);
-    if (hipMalloc(&b->d_dec, sizeof(uint64_t) * kBatchDecWords * count) != hipSuccess) return fail(FCM_ENOMEM);
-    if (hipMalloc(&b->d_ctl, sizeof(uint64_t) * count) != hipSuccess) return fail(FCM_ENOMEM);
-    if (hipMalloc(&b->d_sync, sizeof(BatchSync)) != hipSuccess) return fail(FCM_ENOMEM);
-    if (hipHostMalloc(&b->h_recs, sizeof(BatchRec) * count, hipHostMallocDefault) != hipSuccess)
+    static_assert(sizeof(BatchRec) % alignof(BatchSync) == 0, "the sync record follows the records");
+    if (hipHostMalloc(&b->h_recs, sizeof(BatchRec) * count + sizeof(BatchSync), hipHostMallocDefault) != hipSuccess)
         return fail(FCM_ENOMEM);
-    if (hipHostMalloc(&b->h_sync, sizeof(BatchSync), hipHostMallocDefault) != hipSuccess) return fail(FCM_ENOMEM);
-    if (hipHostMalloc(&b->h_ctl, sizeof(uint64_t) * count, hipHostMallocDefault) != hipSuccess)
-        return fail(FCM_ENOMEM);
+    b->h_sync = reinterpret_cast<BatchSync*>(b->h_recs + count);
     if ((e = hipMemsetAsync(b->d_recs, 0, sizeof(BatchRec) * count, b->stream)) != hipSuccess)
         return fail(dev_err(e, "hipMemsetAsync"));
-    int rc = batch_build_tiles(b);
-    if (rc == FCM_OK) rc = batch_build_levels(b);
+    int rc = batch_build_levels(b);
+    if (rc == FCM_OK && b->tiled) rc = batch_build_tiles(b);
     if (rc != FCM_OK) return fail(rc);
     *out = b;
     return FCM_OK;
@@ -1348,11 +1371,9 @@ int fcm_batch_init(fcm_batch** out, const uint8_t* d_x, const int64_t* offsets, 
 int fcm_batch_set_tiling(fcm_batch* b, int32_t chunks_per_thread, int32_t grid) {
     if (!b || chunks_per_thread < 1 || chunks_per_thread > 64 || grid < 0 || grid > kMaxPersistGrid)
         return FCM_EINVAL;
-    b->tiled = true;
     b->chunks_per_thread = chunks_per_thread;
     b->grid_req = grid;
-    b->solved = false;
-    return batch_build_tiles(b);
+    return batch_retile(b);
 }
 
 int fcm_batch_set_block(fcm_batch* b, int32_t threads) {
@@ -1360,20 +1381,16 @@ int fcm_batch_set_block(fcm_batch* b, int32_t threads) {
     int max_grid = 0;
     hipError_t e = batch_max_grid(threads, b->ncu, &max_grid);
     if (e != hipSuccess) return dev_err(e, "occupancy");
-    b->tiled = true;
     b->block = threads;
     b->max_grid = std::max(1, std::min(max_grid, kMaxPersistGrid));
-    b->solved = false;
-    return batch_build_tiles(b);
+    return batch_retile(b);
 }
 
 int fcm_batch_set_tail_tiling(fcm_batch* b, int32_t from_pass, int32_t chunks_per_thread) {
     if (!b || from_pass < 0 || chunks_per_thread < 1 || chunks_per_thread > 64) return FCM_EINVAL;
-    b->tiled = true;
     b->fine_from = from_pass;
     b->fine_chunks = chunks_per_thread;
-    b->solved = false;
-    return batch_build_tiles(b);
+    return batch_retile(b);
 }
 
 int fcm_batch_set_start(fcm_batch* b, fcm_mlp* net, const uint8_t* use_learned) {
@@ -1427,6 +1444,7 @@ int fcm_batch_set_start(fcm_batch* b, fcm_mlp* net, const uint8_t* use_learned) 
 int fcm_batch_solve(fcm_batch* b, fcm_result* out) {
     if (!b || !out) return FCM_EINVAL;
     if (!b->tiled) return batch_solve_levels(b, out);
+    if (!b->d_rows) return FCM_ENOMEM;  // a tiling that did not fit
     int max_iter = 1;
     for (const fcm_params& q : b->p) max_iter = std::max(max_iter, q.max_iter);
     // tags of this launch: round0 + 1 + phase, phases 0 .. max_iter + 1, and
@@ -1546,10 +1564,11 @@ int fcm_batch_labels(fcm_batch* b, uint8_t* d_labels) {
     a.x = b->d_x;
     a.labels = d_labels;
     a.inst = b->d_inst;
-    a.tiles = b->d_tiles;
+    // the coarse set covers every voxel once
+    a.tiles = b->d_tiles ? b->d_tiles : b->d_labtiles;
     a.recs = b->d_recs;
     a.hist = b->d_hist;
-    a.ntiles = (int32_t)b->coarse_tiles;  // the coarse set covers every voxel once
+    a.ntiles = b->d_tiles ? (int32_t)b->coarse_tiles : b->label_tiles;
     a.bytewise = (((uintptr_t)b->d_x ^ (uintptr_t)d_labels) & 15) ? 1 : 0;
     const int grid = (int)std::max<int64_t>(1, std::min<int64_t>(a.ntiles, 4LL * b->ncu));
     hipError_t e = launch_batch_labels(a, grid, b->stream);
