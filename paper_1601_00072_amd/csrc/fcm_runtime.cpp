@@ -87,6 +87,9 @@ int validate_tuning(const fcm_tuning* t) {
 
 }  // namespace
 
+// tagged partial rows of the persistent driver's exchange, both round parities
+static constexpr size_t kRowsBytes = sizeof(uint64_t) * 2 * kMaxPersistGrid * kTaggedStrideMax;
+
 struct fcm_handle {
     const uint8_t* d_x = nullptr;
     int64_t n = 0, head = 0, nbody = 0;
@@ -105,14 +108,14 @@ struct fcm_handle {
     int mclass = kM2;
     float alpha = 1.f, mexp = 2.f;
 
-    void* d_arena = nullptr;       // one allocation: d_state, d_lcounts, d_minmax, d_hist
+    void* d_arena = nullptr;       // one allocation: d_state, d_lcounts, d_mmrows, d_minmax, d_hist
     DevState* d_state = nullptr;
     uint32_t* d_lcounts = nullptr; // [kLvCopies][256] grey-level counters of the level solve, zero between launches
+    uint32_t* d_minmax = nullptr;  // [2][grid]
+    uint64_t* d_mmrows = nullptr;  // [2][kMaxPersistGrid][2] tagged grey-level ranges (cooperative driver)
     // per-voxel drivers and the random start (ensure_voxel_ws)
     float* d_partials = nullptr;   // [rows][grid] partial rows of the per-pass launches
-    uint32_t* d_minmax = nullptr;  // [2][grid]
     uint64_t* d_rows = nullptr;    // [2][kMaxPersistGrid][rows] tagged partial rows (cooperative driver)
-    uint64_t* d_mmrows = nullptr;  // [2][kMaxPersistGrid][2] tagged grey-level ranges (cooperative driver)
     bool aborted = false;          // a cooperative wait timed out; the next reset clears everything
     double* d_hist = nullptr;      // v: (max_iter + 2) * C, then delta, then J: (max_iter + 2) each
     DevState* h_state = nullptr;   // pinned: [0] the host's view, [1] written by the level solve itself
@@ -535,23 +538,21 @@ int run_batch(fcm_handle* h, int batch) {
     return FCM_OK;
 }
 
-// Workspace of the per-voxel drivers and of the random start: partial rows
-// and the exchange's tagged words (cleared: no stale tag may match).
+// Workspace of the per-voxel drivers and of the random start that is not part
+// of the arena: partial rows and the exchange's tagged rows (cleared: no stale
+// tag may match).
 int ensure_voxel_ws(fcm_handle* h) {
-    if (h->d_mmrows) return FCM_OK;
+    if (h->d_rows) return FCM_OK;
     if (!h->d_partials && hipMalloc(&h->d_partials, sizeof(float) * partial_rows(kMaxC) * kMaxGrid) != hipSuccess)
         return FCM_ENOMEM;
-    if (!h->d_rows && hipMalloc(&h->d_rows, sizeof(uint64_t) * 2 * kMaxPersistGrid * kTaggedStrideMax) != hipSuccess)
-        return FCM_ENOMEM;
-    uint64_t* mm = nullptr;
-    if (hipMalloc(&mm, sizeof(uint64_t) * 4 * kMaxPersistGrid) != hipSuccess) return FCM_ENOMEM;
-    hipError_t e = hipMemsetAsync(h->d_rows, 0, sizeof(uint64_t) * 2 * kMaxPersistGrid * kTaggedStrideMax, h->stream);
-    if (e == hipSuccess) e = hipMemsetAsync(mm, 0, sizeof(uint64_t) * 4 * kMaxPersistGrid, h->stream);
+    uint64_t* rows = nullptr;
+    if (hipMalloc(&rows, kRowsBytes) != hipSuccess) return FCM_ENOMEM;
+    hipError_t e = hipMemsetAsync(rows, 0, kRowsBytes, h->stream);
     if (e != hipSuccess) {
-        (void)hipFree(mm);
+        (void)hipFree(rows);
         return dev_err(e, "hipMemsetAsync");
     }
-    h->d_mmrows = mm;
+    h->d_rows = rows;
     return FCM_OK;
 }
 
@@ -581,13 +582,9 @@ int ensure_level_ws(fcm_handle* h) {
 // wait was aborted, which clears it together with the tagged row buffers.
 int enqueue_start(fcm_handle* h) {
     if (h->aborted) {
-        // the state and the level counters lie next to each other in the arena
+        // state, level counters and tagged ranges lie next to each other in the arena
         FCM_HIP(hipMemsetAsync(h->d_state, 0, (size_t)((char*)h->d_minmax - (char*)h->d_state), h->stream));
-        if (h->d_mmrows) {
-            FCM_HIP(hipMemsetAsync(h->d_rows, 0, sizeof(uint64_t) * 2 * kMaxPersistGrid * kTaggedStrideMax,
-                                   h->stream));
-            FCM_HIP(hipMemsetAsync(h->d_mmrows, 0, sizeof(uint64_t) * 4 * kMaxPersistGrid, h->stream));
-        }
+        if (h->d_rows) FCM_HIP(hipMemsetAsync(h->d_rows, 0, kRowsBytes, h->stream));
         if (h->d_ghist) FCM_HIP(hipMemsetAsync(h->d_ghist, 0, sizeof(uint32_t) * 2 * 256 * kHistCopies, h->stream));
         h->aborted = false;
         h->mirrored = false;
@@ -618,7 +615,6 @@ void release(fcm_handle* h) {
     if (h->d_arena) (void)hipFree(h->d_arena);
     if (h->d_partials) (void)hipFree(h->d_partials);
     if (h->d_rows) (void)hipFree(h->d_rows);
-    if (h->d_mmrows) (void)hipFree(h->d_mmrows);
     for (void* p : {(void*)h->d_woff, (void*)h->d_wcounts, (void*)h->d_whist, (void*)h->d_wv0,
                     (void*)h->d_ghist})
         if (p) (void)hipFree(p);
@@ -698,20 +694,21 @@ int fcm_init(fcm_handle** out, const uint8_t* d_x, int64_t n, const fcm_params* 
     // one allocation for what every solve uses
     auto up = [](size_t b) { return (b + 255) / 256 * 256; };
     const size_t b_state = up(sizeof(DevState)), b_cnt = up(sizeof(uint32_t) * 256 * kLvCopies);
-    const size_t b_mm = up(sizeof(uint32_t) * 2 * kMaxGrid);
+    const size_t b_mmrows = up(sizeof(uint64_t) * 4 * kMaxPersistGrid), b_mm = up(sizeof(uint32_t) * 2 * kMaxGrid);
     const size_t hist_doubles = (size_t)(p->max_iter + 2) * (C + 2);
-    if (hipMalloc(&h->d_arena, b_state + b_cnt + b_mm + sizeof(double) * hist_doubles) != hipSuccess)
+    if (hipMalloc(&h->d_arena, b_state + b_cnt + b_mmrows + b_mm + sizeof(double) * hist_doubles) != hipSuccess)
         return fail(FCM_ENOMEM);
     char* at = static_cast<char*>(h->d_arena);
     h->d_state = reinterpret_cast<DevState*>(at);
     h->d_lcounts = reinterpret_cast<uint32_t*>(at + b_state);
-    h->d_minmax = reinterpret_cast<uint32_t*>(at + b_state + b_cnt);
-    h->d_hist = reinterpret_cast<double*>(at + b_state + b_cnt + b_mm);
+    h->d_mmrows = reinterpret_cast<uint64_t*>(at + b_state + b_cnt);
+    h->d_minmax = reinterpret_cast<uint32_t*>(at + b_state + b_cnt + b_mmrows);
+    h->d_hist = reinterpret_cast<double*>(at + b_state + b_cnt + b_mmrows + b_mm);
     if (hipHostMalloc(&h->h_state, 2 * sizeof(DevState), hipHostMallocDefault) != hipSuccess) return fail(FCM_ENOMEM);
     std::memset(h->h_state, 0, 2 * sizeof(DevState));
-    if ((!use_levels(h) || p->init == FCM_INIT_RANDOM_U) && (rc = ensure_voxel_ws(h)) != FCM_OK) return fail(rc);
     h->aborted = true;  // first start clears the handshake and the flags too
     rc = enqueue_start(h);
+    if (rc == FCM_OK && (!use_levels(h) || p->init == FCM_INIT_RANDOM_U)) rc = ensure_voxel_ws(h);
     if (rc != FCM_OK) return fail(rc);
     *out = h;
     return FCM_OK;
