@@ -335,8 +335,11 @@ def roofline_entry(shape, n, C, m, passes_per_launch, launch_s, tuning, kernel):
 
 def per_voxel(f, **kw):
     """The persistent solve over the voxels in its default shape: by default
-    the driver iterates over the grey levels, a named grid asks for voxels."""
-    f.set_tuning(grid=f.tuning["grid"], **kw)
+    the driver iterates over the grey levels, a named grid asks for voxels
+    (the loop driver's resolved grid is the library's choice for them)."""
+    driver = f.tuning["driver"]
+    f.set_tuning(driver=0)
+    f.set_tuning(driver=driver, grid=f.tuning["grid"], **kw)
 
 
 def solve_steps(dev, x, C, m, eps, steps, warmup, launch, autotune, tune_cache):
@@ -376,7 +379,7 @@ def small_workloads(dev, steps, launch, tune_cache):
     for name, shape, seed, ctx in cases:
         x = torch.from_numpy(phantom(PhantomParams(shape=shape, seed=seed)).ravel()).to(dev)
         n = x.numel()
-        # no recorded choice for the slice: the autotuner would take the level solve
+        # the slice has no recorded choice: the library's default per-voxel shape
         st = solve_steps(dev, x, 4, 2.0, 1e-5, steps, 5, launch, len(shape) == 3, tune_cache)
         r = st["r"]
         pps = st["passes"] / steps
@@ -515,6 +518,7 @@ def batched(dev, tune_cache):
     flat = torch.from_numpy(np.concatenate(xs)).to(dev)
     n = flat.numel()
     with FCMBatch(flat, [a.size for a in xs], [dict(n_clusters=c, m=2.0, eps=1e-5) for c in Cs]) as b:
+        b.set_tiling()  # per-voxel passes, as the recorded choices; by default a batch solves over the grey levels
         bs, cpt, bgrid, _ = b.autotune(cache=tune_cache, reps=1)
         b.solve()
         torch.cuda.synchronize()

@@ -134,8 +134,10 @@ typedef struct fcm_tuning {
                            (persistent driver: see FCM_DRIVER_PERSISTENT).  The
                            persistent driver caps it at the number of blocks that
                            fit on the device at once.  fcm_get_tuning reports the
-                           grid that a per-voxel pass would take. */
-    int32_t unroll;     /* 16-voxel chunks in flight per thread: 1 or 2 */
+                           resolved grid, or 0 where the persistent driver solves
+                           over the grey levels, so that the record, set again,
+                           changes nothing. */
+    int32_t unroll;     /* per-voxel passes: 16-voxel chunks in flight per thread, 1 or 2 */
     int32_t driver;     /* FCM_DRIVER_* */
     int32_t graph_k;    /* loop/graph drivers: passes per host synchronisation
                            (and per graph), 1..64 */
@@ -322,18 +324,23 @@ void fcm_batch_destroy(fcm_batch* b);
  * per-voxel pass (ordinary launch) over grids from half
  * the CU count up to one 16-voxel chunk per thread, leader, all-gather and two-level
  * exchange, unroll 1 and 2; graph driver with 4 and 16 passes per graph.
- * Key: C, the m class (2, 1.5, other), the precision flag and floor(log2 n).
+ * Key: C, the m class (2, 1.5, other), the precision flag, floor(log2 n) and
+ * whether the handle solves over the grey levels at entry (that is then the
+ * first candidate; choices of per-voxel handles are not applied to it).
  * The handle is left reset with the chosen tuning (chosen may be NULL; ms:
  * the chosen configuration's median solve time, may be NULL). */
 int fcm_autotune(fcm_handle* h, const char* cache_path, int32_t reps, fcm_tuning* chosen, double* ms);
 
 /* Batch: blocks of 512, 256 and 128 threads x tiles of 1, 2, 3, 4, 5, 6, 8, 12
  * or 16 chunks per thread, on the largest grid the device holds and on half
- * of it (the tail tiling stays as set).  Key: instance count, largest C and
- * floor(log2 of the total voxels).  The chosen block size and tiling are
+ * of it (the tail tiling stays as set).  Key: instance count, largest C,
+ * floor(log2 of the total voxels) and whether the batch solves over the grey
+ * levels at entry.  The chosen block size and tiling are
  * applied (fcm_batch_set_block, fcm_batch_set_tiling) unless the batch solved
- * over the grey levels at entry and that was faster (it then goes on doing so);
- * outputs may be NULL. */
+ * over the grey levels at entry and that was faster: it then goes on doing so,
+ * ms is the time of that, and the block size and tiling reported are only those
+ * that per-voxel passes would have (setting them would ask for such passes;
+ * a recorded choice has 0 chunks).  Outputs may be NULL. */
 int fcm_batch_autotune(fcm_batch* b, const char* cache_path, int32_t reps, int32_t* block,
                        int32_t* chunks_per_thread, int32_t* grid, double* ms);
 

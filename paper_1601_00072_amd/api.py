@@ -121,7 +121,8 @@ class FCM:
     def autotune(self, cache: str | None = None, reps: int = 3):
         """Time candidate launch configurations on this input and keep the
         fastest that agrees with the current one (see fcm_autotune).
-        Returns (tuning dict, median ms per solve)."""
+        Returns (tuning dict, median ms per solve); set_tuning(**dict) gives
+        another handle the same (grid 0: the solve over the grey levels)."""
         t, ms = L.FcmTuning(), ctypes.c_double()
         self._check(self._lib.fcm_autotune(self._h, None if cache is None else str(cache).encode(), int(reps),
                                            ctypes.byref(t), ctypes.byref(ms)), "fcm_autotune")
@@ -317,7 +318,9 @@ class FCMBatch:
 
     def autotune(self, cache: str | None = None, reps: int = 2):
         """Pick the block size, tile size and grid (see fcm_batch_autotune);
-        returns (block, chunks_per_thread, grid, median ms per batched solve)."""
+        returns (block, chunks_per_thread, grid, median ms per batched solve).
+        A batch that solves over the grey levels goes on so where that is the
+        fastest: ms is then its time, and the rest what per-voxel passes would have."""
         bs, cpt, grid, ms = ctypes.c_int32(), ctypes.c_int32(), ctypes.c_int32(), ctypes.c_double()
         rc = self._lib.fcm_batch_autotune(self._h, None if cache is None else str(cache).encode(), int(reps),
                                           ctypes.byref(bs), ctypes.byref(cpt), ctypes.byref(grid), ctypes.byref(ms))

@@ -17,6 +17,7 @@ struct HandleShape {
     int64_t n, nbody;   // voxels, aligned 16-voxel chunks
     int C, mclass, kahan, device, ncu, coop;
     int grid_asked;     // the grid as set by the caller (0: the library's choice)
+    int levels;         // it solves over the grey levels
 };
 struct BatchShape {
     int64_t voxels;     // all instances

@@ -743,7 +743,10 @@ int fcm_set_tuning(fcm_handle* h, const fcm_tuning* t) {
 int fcm_get_tuning(const fcm_handle* h, fcm_tuning* t) {
     if (!h || !t) return FCM_EINVAL;
     *t = h->tun;
-    t->grid = h->grid;
+    // as resolved; but a grid named on the persistent driver asks for the
+    // per-voxel pass, so where the launch is left to the library it stays 0
+    // and the record, set again, changes nothing
+    if (!(t->driver == FCM_DRIVER_PERSISTENT && use_levels(h))) t->grid = h->grid;
     return FCM_OK;
 }
 
@@ -1615,6 +1618,7 @@ int handle_shape(const fcm_handle* h, HandleShape* s) {
     s->ncu = h->ncu;
     s->coop = h->coop;
     s->grid_asked = h->tun.grid;
+    s->levels = use_levels(h) ? 1 : 0;
     return FCM_OK;
 }
 

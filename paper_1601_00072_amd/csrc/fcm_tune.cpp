@@ -8,7 +8,11 @@
 // counts differ by one).  Choices are cached per process and, if a path is
 // given, in a text file (one line per choice, the last matching line wins),
 // keyed by device, HIP runtime version, C, the m class, the precision
-// variant and the size bucket (floor(log2 n)).
+// variant and the size bucket (floor(log2 n)), and by the route at entry: an
+// object that solves over the grey levels is 20 to 30 times faster than any
+// per-voxel choice, so choices made for, or by, per-voxel objects (the only
+// ones that files of earlier builds hold) do not apply to it, nor its own to
+// them.
 
 #include <hip/hip_runtime.h>
 
@@ -164,14 +168,13 @@ int fcm_autotune(fcm_handle* h, const char* cache_path, int32_t reps, fcm_tuning
     HandleShape s{};
     int rc = handle_shape(h, &s);
     if (rc != FCM_OK) return rc;
+    fcm_tuning entry{};
+    if ((rc = fcm_get_tuning(h, &entry)) != FCM_OK) return rc;
     std::ostringstream key;
     key << "single " << device_tag(s.device) << " C=" << s.C << " mclass=" << s.mclass << " kahan=" << s.kahan
         << " nlog2=" << log2_floor(s.n);
-    fcm_tuning entry{};
-    if ((rc = fcm_get_tuning(h, &entry)) != FCM_OK) return rc;
-    // as set, not as resolved: with grid 0 and the automatic exchange the
-    // library solves over the grey levels, and that stays a candidate
-    entry.grid = s.grid_asked;
+    if (s.levels) key << (entry.driver == FCM_DRIVER_HISTOGRAM ? " route=histogram" : " route=levels");
+    entry.grid = s.grid_asked;  // as set, not as resolved
     Choice c{};
     if (load_choice(cache_path, key.str(), 6, &c)) {
         fcm_tuning t = entry;
@@ -271,7 +274,7 @@ int fcm_batch_autotune(fcm_batch* b, const char* cache_path, int32_t reps, int32
     if (rc != FCM_OK) return rc;
     std::ostringstream key;
     key << "batch2 " << device_tag(s.device) << " count=" << s.count << " maxC=" << s.max_C
-        << " vlog2=" << log2_floor(s.voxels);
+        << " vlog2=" << log2_floor(s.voxels) << (s.tiled ? "" : " route=levels");
     // block size, then tiling; s follows the batch's state whatever fails
     auto apply = [&](int bs, int cpt, int g) {
         int r = bs == s.block ? FCM_OK : fcm_batch_set_block(b, bs);
