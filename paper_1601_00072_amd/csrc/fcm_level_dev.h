@@ -322,27 +322,13 @@ __device__ __noinline__ double level_u_any(double x, const double* v, double m, 
 // S = sum w, and u_k^m = w_k u2_k / S^m because alpha (m - 1) = 1 -- so only
 // the generic m needs logarithms, one log2 and one exp2 per cluster.  Returns
 // the level's term of Eq.1, sum_k u_k^m q_k = u2_0 q_0 S^(1-m) (u2_k q_k is the
-// same for every k).  Products out of range (centroids far beyond the grey
-// levels) give non-finite values: the caller sees them in the sums and repeats
-// that pass with the ratio form (`safe`).  `twins`: some centroids are equal.
-// They have equal memberships, and so must keep them to the last bit: the
-// products of two equal centroids round differently, and Algorithm 1 moves
-// away from coinciding centroids exponentially once they differ.
-template <int C, int MK>
-__device__ __forceinline__ double level_u(double x, const double (&v)[C], double m, double alpha, bool safe,
-                                          bool twins, const LevelScratch& sh, double (&u)[C], double (&a)[C]) {
-    if (safe) {
-        double cv[C], cu[C], ca[C];  // copies: only they live in memory
-#pragma unroll
-        for (int k = 0; k < C; ++k) cv[k] = v[k];
-        const double j = level_u_any<C>(x, cv, m, cu, ca);
-#pragma unroll
-        for (int k = 0; k < C; ++k) {
-            u[k] = cu[k];
-            a[k] = ca[k];
-        }
-        return j;
-    }
+// same for every k).  EQUAL: some centroids may be equal.  They have equal
+// memberships, and so must keep them to the last bit: the products of two equal
+// centroids round differently, and Algorithm 1 moves away from coinciding
+// centroids exponentially once they differ.
+template <int C, int MK, bool EQUAL>
+__device__ __forceinline__ double level_products(double x, const double (&v)[C], double m, double alpha,
+                                                 const LevelScratch& sh, double (&u)[C], double (&a)[C]) {
     double q[C], P[C], pre[C], suf[C];
 #pragma unroll
     for (int k = 0; k < C; ++k) {
@@ -359,7 +345,7 @@ __device__ __forceinline__ double level_u(double x, const double (&v)[C], double
     P[C - 1] = pre[C - 1];
 #pragma unroll
     for (int k = 1; k < C - 1; ++k) P[k] = pre[k] * suf[k + 1];
-    if (twins)
+    if constexpr (EQUAL)
 #pragma unroll
         for (int k = 1; k < C; ++k)
 #pragma unroll
@@ -368,9 +354,9 @@ __device__ __forceinline__ double level_u(double x, const double (&v)[C], double
     double S = P[0];
 #pragma unroll
     for (int j = 1; j < C; ++j) S += P[j];
-    if (__any(S == 0.0)) {
-        // two or more centroids on a level of this wave: every product is 0,
-        // and the zero-distance rule splits equally over them
+    if constexpr (EQUAL) {
+        // equal centroids on this level: every product is 0, and the
+        // zero-distance rule splits equally over them
         const bool zero = S == 0.0;
         double nz = 0.0;
 #pragma unroll
@@ -430,6 +416,48 @@ __device__ __forceinline__ double level_u(double x, const double (&v)[C], double
         }
         return j2 * (s * t);
     }
+}
+
+
+// The same for centroids that may be equal, or so far beyond the grey levels
+// that the products leave the range (non-finite values: the ratio form then).
+// Out of line: the tests for either inside level_products cost every pass
+// 0.06-0.08 us of 0.65, and neither happens in most solves.
+template <int C, int MK>
+__device__ __noinline__ double level_u_special(double x, const double* v, double m, double alpha,
+                                               const LevelScratch& sh, double* u, double* a) {
+    double cv[C], cu[C], ca[C];
+#pragma unroll
+    for (int k = 0; k < C; ++k) cv[k] = v[k];
+    const double j = level_products<C, MK, true>(x, cv, m, alpha, sh, cu, ca);
+    bool fin = true;
+#pragma unroll
+    for (int k = 0; k < C; ++k) fin = fin && isfinite(cu[k]) && isfinite(ca[k]);
+    if (!fin) return level_u_any<C>(x, v, m, u, a);
+#pragma unroll
+    for (int k = 0; k < C; ++k) {
+        u[k] = cu[k];
+        a[k] = ca[k];
+    }
+    return j;
+}
+
+template <int C, int MK>
+__device__ __forceinline__ double level_u(double x, const double (&v)[C], double m, double alpha, bool special,
+                                          const LevelScratch& sh, double (&u)[C], double (&a)[C]) {
+    if (special) {
+        double cv[C], cu[C], ca[C];  // copies: only they live in memory
+#pragma unroll
+        for (int k = 0; k < C; ++k) cv[k] = v[k];
+        const double j = level_u_special<C, MK>(x, cv, m, alpha, sh, cu, ca);
+#pragma unroll
+        for (int k = 0; k < C; ++k) {
+            u[k] = cu[k];
+            a[k] = ca[k];
+        }
+        return j;
+    }
+    return level_products<C, MK, false>(x, v, m, alpha, sh, u, a);
 }
 
 // Whether any two of the centroids (the same in every lane) are equal.
@@ -513,7 +541,7 @@ __device__ __forceinline__ void level_iterate(const LevelProblem& pb, uint32_t c
         __syncthreads();
 #pragma unroll
         for (int k = 0; k < C; ++k) v[k] = readfirst_d(sh.v[k]);
-        twins = any_equal<C>(v);
+        twins = LEARNED || pb.given ? any_equal<C>(v) : lo == hi;  // evenly spaced
         if (wid == 4) {
             if (lane < C) pb.hist_v[lane] = sh.v[lane];
             if (pb.times && lane == 0) pb.times[0] = wall_clock64();
@@ -527,11 +555,11 @@ __device__ __forceinline__ void level_iterate(const LevelProblem& pb, uint32_t c
             double vp[C], t[C];
 #pragma unroll
             for (int k = 0; k < C; ++k) vp[k] = pb.hist_v[(int64_t)(p - 1) * C + k];
-            level_u<C, MK>(x, vp, pb.m, pb.alpha, false, twins, sh, uo, t);
+            level_u<C, MK>(x, vp, pb.m, pb.alpha, twins, sh, uo, t);
             bool fin = true;
 #pragma unroll
             for (int k = 0; k < C; ++k) fin = fin && isfinite(uo[k]);
-            if (!fin) level_u<C, MK>(x, vp, pb.m, pb.alpha, true, twins, sh, uo, t);
+            if (!fin) level_u<C, MK>(x, vp, pb.m, pb.alpha, true, sh, uo, t);
         }
     }
     // also where v^0 was committed before this launch (a query or labels first)
@@ -557,10 +585,10 @@ __device__ __forceinline__ void level_iterate(const LevelProblem& pb, uint32_t c
         const int64_t stop_at = (int64_t)p + pb.max_passes - 1;
         const int calm = huge ? -1 : (int)(stop_at < pb.max_iter ? stop_at : pb.max_iter);
         int par = 0, slot = 0;
-        bool safe = false;
+        bool special = twins;
         while (true) {
             double u[C], a[C];
-            const double jt = level_u<C, MK>(x, v, pb.m, pb.alpha, safe, twins, sh, u, a);
+            const double jt = level_u<C, MK>(x, v, pb.m, pb.alpha, special, sh, u, a);
 #pragma unroll
             for (int k = 0; k < C; ++k) a[k] *= c;
             double num[SETS], den[SETS];
@@ -614,7 +642,7 @@ __device__ __forceinline__ void level_iterate(const LevelProblem& pb, uint32_t c
             int dec = (FCM_RUNNING + kLvStatus0) << kLvStatusShift;
             bool run = true;
             if (!(go && p < calm)) {
-                const bool retry = !ok && !safe;  // again, with the form that holds for any centroids
+                const bool retry = !ok && !special;  // again, with the form that holds for any centroids
                 const int status = !ok || huge ? FCM_ENUMERIC
                                                : (p >= 1 && !go ? FCM_OK : (p >= pb.max_iter ? FCM_NOT_CONVERGED
                                                                                              : FCM_RUNNING));
@@ -636,10 +664,10 @@ __device__ __forceinline__ void level_iterate(const LevelProblem& pb, uint32_t c
                 for (int k = 0; k < C; ++k) uo[k] = u[k];
 #pragma unroll
                 for (int s = 0; s < SETS; ++s) vk[s] = vn[s];
-                safe = false;
+                special = twins;
                 ++p;
             } else if (dec & kLvRetry) {
-                safe = true;
+                special = true;
             } else {
 #pragma unroll
                 for (int s = 0; s < SETS; ++s) {
@@ -672,8 +700,7 @@ __device__ __forceinline__ void level_iterate(const LevelProblem& pb, uint32_t c
                 const double j = (jr[lane] + jr[lane + 64]) + (jr[lane + 128] + jr[lane + 192]);
                 double d = fmax(fmax(dr[lane], dr[lane + 64]), fmax(dr[lane + 128], dr[lane + 192]));
                 const double vn = sh.vnext[slot][lane & 7];
-                double J = quad_sum_f64(j, 0.0, 0.0, 0.0);
-                if (huge) J = __builtin_nan("");  // as its FP32 terms would make it
+                const double J = quad_sum_f64(j, 0.0, 0.0, 0.0);
                 d = wave_max_pos_f64(d);
                 const double delta = p > 0 ? readlane_d(d, 63) : __builtin_nan("");
                 if (lane == 0) {
@@ -693,6 +720,10 @@ __device__ __forceinline__ void level_iterate(const LevelProblem& pb, uint32_t c
                 if (dec & kLvEnd) break;
             }
             slot = slot == 2 ? 0 : slot + 1;
+        }
+        if (huge) {  // ended with pass 0: its objective as FP32 terms would make it
+            out.J = __builtin_nan("");
+            if (lane == 0) pb.hist_J[0] = out.J;
         }
         out.pass = p;
         out.passes = passes;

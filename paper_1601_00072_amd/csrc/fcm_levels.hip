@@ -135,7 +135,6 @@ __global__ __launch_bounds__(kLvBlock, LEARNED ? 2 : 4) void fcm_level_kernel(Le
             level_commit<C>(a.host, a, o, sh, total);
             a.host->lo = o.lo;
             a.host->hi = o.hi;
-            a.host->sync.abort = st->sync.abort;  // of a per-voxel solve still pending before this one
             // the host may see this before the runtime reports the launch done
             __hip_atomic_store(&a.host->ticket, a.seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
         }

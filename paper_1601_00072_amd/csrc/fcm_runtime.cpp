@@ -120,7 +120,8 @@ struct fcm_handle {
     double* d_hist = nullptr;      // v: (max_iter + 2) * C, then delta, then J: (max_iter + 2) each
     DevState* h_state = nullptr;   // pinned: [0] the host's view, [1] written by the level solve itself
     bool mirrored = false;         // h_state[1] holds the state that the last launch left
-    bool graphed = false;          // a captured per-voxel solve may run after it without the host's knowledge
+    bool voxel_pending = false;    // an asynchronous per-voxel solve was enqueued since d_state was last read
+    bool graphed = false;          // one was captured: it may run at any time without the host's knowledge
     uint32_t seq = 0;              // its number: h_state[1].ticket once that launch has written its result
 
     fcm_tuning tun{};
@@ -298,7 +299,9 @@ int wait_own_launch(fcm_handle* h) {
 // State as of the work enqueued so far; waits for the stream, or (own_launch)
 // for the level launch just enqueued.
 int read_state(fcm_handle* h, bool own_launch = false) {
-    if (h->mirrored && (own_launch || !h->graphed)) {  // the launch itself left its result in host memory
+    // the launch itself left its result in host memory; it does not say whether
+    // a per-voxel solve before it hit its wait limit, nor what a graph runs
+    if (h->mirrored && !h->voxel_pending && !h->graphed) {
         if (own_launch) {
             int rc = wait_own_launch(h);
             if (rc != FCM_OK) return rc;
@@ -308,11 +311,11 @@ int read_state(fcm_handle* h, bool own_launch = false) {
         const DevState& m = h->h_state[1];
         std::memcpy(h->h_state, &m, offsetof(DevState, sync));
         h->h_state->sync.passes_total = m.sync.passes_total;
-        h->h_state->sync.abort = m.sync.abort;
-    } else {
-        FCM_HIP(hipMemcpyAsync(h->h_state, h->d_state, sizeof(DevState), hipMemcpyDeviceToHost, h->stream));
-        FCM_HIP(hipStreamSynchronize(h->stream));
+        return FCM_OK;
     }
+    FCM_HIP(hipMemcpyAsync(h->h_state, h->d_state, sizeof(DevState), hipMemcpyDeviceToHost, h->stream));
+    FCM_HIP(hipStreamSynchronize(h->stream));
+    h->voxel_pending = false;
     if (h->h_state->sync.abort) {
         h->aborted = true;
         last_error() = "a cross-block wait exceeded its time limit; the solve was aborted (reset the handle)";
@@ -863,6 +866,7 @@ int fcm_solve_async(fcm_handle* h, uint8_t* d_labels) {
             if (hipStreamIsCapturing(h->stream, &cs) != hipSuccess) (void)hipGetLastError();
             h->graphed = cs != hipStreamCaptureStatusNone;
         }
+        h->voxel_pending = true;
         hipError_t e = launch_persist(a, h->p.n_clusters, h->mclass, h->tun.unroll, h->grid,
                                       h->tun.launch == FCM_LAUNCH_COOPERATIVE, h->stream);
         if (e != hipSuccess) return dev_err(e, "persistent launch");
