@@ -21,16 +21,17 @@ const uint16_t* mlp_bf16_weights(fcm_mlp* net, hipStream_t s, int* rc);
 
 // Histograms of `count` instances: counts is a workspace of
 // count * histogram_copies(count) * 256 words, unused (may be null) unless
-// histogram_needs_counts; hist[count][256] receives the normalised histograms.  The split follows from the host's copy of the
-// offsets (count + 1); a kHistList also needs `first` (host, count + 1 values,
-// written then; unused for one instance) on the device.
+// histogram_needs_counts; hist[count][256] receives the normalised
+// histograms.  The split follows from the host's copy of the offsets
+// (count + 1) and the largest instance; a kHistList also needs `first` (host,
+// count + 1 values, written then; unused for one instance) on the device.
 int histogram_copies(int count);
 enum HistForm : int { kHistRect = 0, kHistList = 1, kHistWaves = 2 };
 struct HistSplit {
     int form;
     int blocks;  // kHistRect: of each instance, else in all
 };
-HistSplit histogram_split(const int64_t* offsets, int count, int32_t* first);
+HistSplit histogram_split(const int64_t* offsets, int count, int64_t max_n, int32_t* first);
 hipError_t launch_histogram(const uint8_t* x, const int64_t* d_offsets, const int32_t* d_first, HistSplit sp, int count,
                             uint32_t* counts, float* hist, hipStream_t s);
 bool histogram_needs_counts(HistSplit sp);

@@ -142,15 +142,14 @@ int histogram_copies(int count) { return count == 1 ? kHistCopies : 1; }
 // (one volume of 67M voxels and 512 slices of 256x256: the call took
 // 940 us, 92 as a list of blocks; with 5,000 slices of 64x64: 8,420 and 354):
 // then kHistList.  More small instances than fit at once: a wave each (kHistWaves).
-HistSplit histogram_split(const int64_t* offsets, int count, int32_t* first) {
+HistSplit histogram_split(const int64_t* offsets, int count, int64_t max_n, int32_t* first) {
     static constexpr int64_t kCus = 256, kMin = 16384, kMax = 131072;
     auto clamped = [](int64_t v) { return std::min(std::max(v, kMin), kMax); };
     auto blocks = [](int64_t n, int64_t share) { return std::min<int64_t>((n + share - 1) / share, 4096); };
-    int64_t max_n = 0;
-    for (int i = 0; i < count; ++i) max_n = std::max(max_n, offsets[i + 1] - offsets[i]);
     if (count >= 2 * kCus && max_n <= kHistWaveVoxels) return {kHistWaves, (count + 7) / 8};
     if (count == 1) return {kHistRect, (int)std::min(blocks(max_n, std::max(kMin, max_n / (2 * kCus))), kCus)};
     const int64_t gx = blocks(max_n, clamped(max_n * count / (2 * kCus)));
+    if (gx <= 2) return {kHistRect, (int)gx};
     const int64_t share = clamped(offsets[count] / (2 * kCus));
     int64_t need = 0;
     for (int i = 0; i < count; ++i) need += blocks(offsets[i + 1] - offsets[i], share);
@@ -820,7 +819,7 @@ extern "C" int fcm_histogram_noalloc(const uint8_t* d_x, const int64_t* offsets,
     int32_t* d_first = reinterpret_cast<int32_t*>(d_off + kNoAllocMaxCount + 1);
     uint32_t* d_counts = reinterpret_cast<uint32_t*>(static_cast<unsigned char*>(base) + kNoAllocOffBytes);
     int32_t first[kNoAllocMaxCount + 1];
-    const HistSplit sp = histogram_split(offsets, count, first);
+    const HistSplit sp = histogram_split(offsets, count, max_n, first);
     FCM_HIP(hipMemcpyAsync(d_off, offsets, sizeof(int64_t) * ((size_t)count + 1), hipMemcpyHostToDevice, s));
     if (sp.form == kHistList)
         FCM_HIP(hipMemcpyAsync(d_first, first, sizeof(int32_t) * ((size_t)count + 1), hipMemcpyHostToDevice, s));

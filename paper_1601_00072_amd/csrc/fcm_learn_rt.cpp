@@ -434,7 +434,7 @@ int fcm_histogram(const uint8_t* d_x, const int64_t* offsets, int32_t count, flo
     const size_t cnt = (size_t)count;
     std::unique_ptr<int32_t[]> first(new (std::nothrow) int32_t[cnt + 1]);
     if (!first) return FCM_ENOMEM;
-    const HistSplit sp = histogram_split(offsets, count, first.get());
+    const HistSplit sp = histogram_split(offsets, count, max_n, first.get());
     // one temporary: the counters, then the offsets and the first blocks
     const size_t b_counts = histogram_needs_counts(sp) ? sizeof(uint32_t) * 256 * cnt * histogram_copies(count) : 0;
     uint32_t* d_counts = nullptr;

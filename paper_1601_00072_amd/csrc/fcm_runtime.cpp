@@ -920,7 +920,7 @@ int fcm_solve_warm(fcm_handle* h, fcm_mlp* net, int32_t check, fcm_result* out, 
     } else {
         if ((rc = ensure_level_ws(h)) != FCM_OK) return rc;
         const int64_t range[2] = {0, h->n};
-        FCM_HIP(launch_histogram(h->d_x, h->d_woff, nullptr, histogram_split(range, 1, nullptr), 1, h->d_wcounts,
+        FCM_HIP(launch_histogram(h->d_x, h->d_woff, nullptr, histogram_split(range, 1, h->n, nullptr), 1, h->d_wcounts,
                                  h->d_whist, h->stream));
         if ((rc = mlp_warm(net, h->d_whist, 1, h->d_wv0, h->stream)) != FCM_OK) return rc;
         h->p.init = FCM_INIT_DEVICE;
@@ -1411,7 +1411,9 @@ int fcm_batch_set_start(fcm_batch* b, fcm_mlp* net, const uint8_t* use_learned) 
             if (!first) return FCM_ENOMEM;
             int64_t* off = nullptr;
             if (hipMalloc(&off, (sizeof(int64_t) + sizeof(int32_t)) * (cnt + 1)) != hipSuccess) return FCM_ENOMEM;
-            b->hsplit = histogram_split(b->offsets.data(), b->count, first.get());
+            int64_t max_n = 1;
+            for (const BatchInst& in : b->h_inst) max_n = std::max(max_n, in.n);
+            b->hsplit = histogram_split(b->offsets.data(), b->count, max_n, first.get());
             hipError_t e = hipMemcpyAsync(off, b->offsets.data(), sizeof(int64_t) * (cnt + 1), hipMemcpyHostToDevice,
                                           b->stream);
             if (e == hipSuccess && b->hsplit.form == kHistList)
