@@ -56,13 +56,13 @@ __global__ __launch_bounds__(kLvBlock) void hist_count_kernel(const uint8_t* x, 
         share = b - first[inst];
         shares = first[inst + 1] - first[inst];
     }
+    level_clear(tab);  // while the offsets are on their way
     const int64_t b0 = offsets[inst], n = offsets[inst + 1] - b0;
     const uint8_t* xi = x + b0;
     const int64_t lead = (int64_t)((16 - ((uintptr_t)xi & 15)) & 15);
     const int64_t head = n < lead ? n : lead;
     const int64_t nbody = (n - head) / 16;
     if (share && (int64_t)share * kLvBlock >= nbody) return;  // a smaller instance than the grid's largest
-    level_clear(tab);
     __syncthreads();
     char* t8 = reinterpret_cast<char*>(tab);
     level_count(t8, reinterpret_cast<const uint4*>(xi + head), (int64_t)share * kLvBlock + tid, nbody,
