@@ -750,6 +750,8 @@ def main():
             "n_voxels": n, "C": C, "m": m, "eps": eps, "iterations": r.iters, "status": r.status,
             "passes_per_solve": passes_per_solve,
             "time_to_converge_ms": ms_per_step,
+            "route": "over the voxels in every pass (the grid is named); with the grid left to the library a solve "
+                     "counts the grey levels once and iterates over them, see extra.histogram_domain",
             "step": "data-range pass + fused passes to convergence + labels, one persistent launch per step "
                     "(fcm_solve_async), steps enqueued back to back, one host wait for the timed run; "
                     "passes counted on the device",

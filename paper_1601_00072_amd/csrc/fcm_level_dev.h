@@ -282,7 +282,8 @@ __device__ __forceinline__ double exp2_tab(double y, const LevelScratch& sh) {
 
 // Eq.4 and u^m by distance ratios, u_k = w_k / sum_j w_j with
 // w_k = (d_min / d_k)^(2/(m-1)) <= 1, and the zero-distance rule (equal split
-// over the clusters at distance 0): the form that holds for any centroids.
+// over the clusters at distance 0): the form that holds for any centroids, and
+// gives equal ones equal memberships to the last bit.
 template <int C>
 __device__ __noinline__ double level_u_any(double x, const double* v, double m, double* u, double* a) {
     double d[C];
@@ -294,15 +295,20 @@ __device__ __noinline__ double level_u_any(double x, const double* v, double m, 
         dmin = fmin(dmin, d[k]);
         nz += d[k] == 0.0;
     }
+    if (nz) {
+        const double un = 1.0 / nz, an = m == 2.0 ? un * un : pow(un, m);
+#pragma unroll
+        for (int k = 0; k < C; ++k) {
+            u[k] = d[k] == 0.0 ? un : 0.0;
+            a[k] = d[k] == 0.0 ? an : 0.0;
+        }
+        return 0.0;
+    }
     double s = 0.0;
 #pragma unroll
     for (int k = 0; k < C; ++k) {
-        if (nz) {
-            u[k] = d[k] == 0.0 ? 1.0 : 0.0;
-        } else {
-            const double r = dmin / d[k];
-            u[k] = m == 2.0 ? r * r : pow(r, 2.0 / (m - 1.0));
-        }
+        const double r = dmin / d[k];
+        u[k] = m == 2.0 ? r * r : pow(r, 2.0 / (m - 1.0));
         s += u[k];
     }
 #pragma unroll
@@ -322,13 +328,29 @@ __device__ __noinline__ double level_u_any(double x, const double* v, double m, 
 // S = sum w, and u_k^m = w_k u2_k / S^m because alpha (m - 1) = 1 -- so only
 // the generic m needs logarithms, one log2 and one exp2 per cluster.  Returns
 // the level's term of Eq.1, sum_k u_k^m q_k = u2_0 q_0 S^(1-m) (u2_k q_k is the
-// same for every k).  EQUAL: some centroids may be equal.  They have equal
-// memberships, and so must keep them to the last bit: the products of two equal
-// centroids round differently, and Algorithm 1 moves away from coinciding
-// centroids exponentially once they differ.
-template <int C, int MK, bool EQUAL>
-__device__ __forceinline__ double level_products(double x, const double (&v)[C], double m, double alpha,
-                                                 const LevelScratch& sh, double (&u)[C], double (&a)[C]) {
+// same for every k).  `safe`: by the ratio form.  The caller asks for it in
+// every pass where two centroids are equal -- their products round differently,
+// and Algorithm 1 moves away from coinciding centroids exponentially once they
+// differ -- and from the pass on in which products out of range (centroids far
+// beyond the grey levels) gave non-finite sums.  (Equal products and the
+// zero-distance rule inside the product form, or anything else that touches
+// this branch in a pass, costs every other solve 1 to 10 % of a pass.)
+template <int C, int MK>
+__device__ __forceinline__ double level_u(double x, const double (&v)[C], double m, double alpha, bool safe, bool on,
+                                          const LevelScratch& sh, double (&u)[C], double (&a)[C]) {
+    if (safe) {
+        double cv[C], cu[C], ca[C];  // copies: only they live in memory
+#pragma unroll
+        for (int k = 0; k < C; ++k) cv[k] = v[k];
+        // a level that no voxel has takes the cheap way out of the rule
+        const double j = level_u_any<C>(on ? x : v[0], cv, m, cu, ca);
+#pragma unroll
+        for (int k = 0; k < C; ++k) {
+            u[k] = cu[k];
+            a[k] = ca[k];
+        }
+        return j;
+    }
     double q[C], P[C], pre[C], suf[C];
 #pragma unroll
     for (int k = 0; k < C; ++k) {
@@ -345,28 +367,9 @@ __device__ __forceinline__ double level_products(double x, const double (&v)[C],
     P[C - 1] = pre[C - 1];
 #pragma unroll
     for (int k = 1; k < C - 1; ++k) P[k] = pre[k] * suf[k + 1];
-    if constexpr (EQUAL)
-#pragma unroll
-        for (int k = 1; k < C; ++k)
-#pragma unroll
-            for (int j = k - 1; j >= 0; --j)
-                if (v[j] == v[k]) P[k] = P[j];  // the lowest such j is the last one written
     double S = P[0];
 #pragma unroll
     for (int j = 1; j < C; ++j) S += P[j];
-    if constexpr (EQUAL) {
-        // equal centroids on this level: every product is 0, and the
-        // zero-distance rule splits equally over them
-        const bool zero = S == 0.0;
-        double nz = 0.0;
-#pragma unroll
-        for (int k = 0; k < C; ++k) {
-            const double on = q[k] == 0.0 ? 1.0 : 0.0;
-            P[k] = zero ? on : P[k];
-            nz += on;
-        }
-        S = zero ? nz : S;
-    }
     const double r = recip_f64(S);
 #pragma unroll
     for (int k = 0; k < C; ++k) P[k] *= r;  // u2
@@ -416,48 +419,6 @@ __device__ __forceinline__ double level_products(double x, const double (&v)[C],
         }
         return j2 * (s * t);
     }
-}
-
-
-// The same for centroids that may be equal, or so far beyond the grey levels
-// that the products leave the range (non-finite values: the ratio form then).
-// Out of line: the tests for either inside level_products cost every pass
-// 0.06-0.08 us of 0.65, and neither happens in most solves.
-template <int C, int MK>
-__device__ __noinline__ double level_u_special(double x, const double* v, double m, double alpha,
-                                               const LevelScratch& sh, double* u, double* a) {
-    double cv[C], cu[C], ca[C];
-#pragma unroll
-    for (int k = 0; k < C; ++k) cv[k] = v[k];
-    const double j = level_products<C, MK, true>(x, cv, m, alpha, sh, cu, ca);
-    bool fin = true;
-#pragma unroll
-    for (int k = 0; k < C; ++k) fin = fin && isfinite(cu[k]) && isfinite(ca[k]);
-    if (!fin) return level_u_any<C>(x, v, m, u, a);
-#pragma unroll
-    for (int k = 0; k < C; ++k) {
-        u[k] = cu[k];
-        a[k] = ca[k];
-    }
-    return j;
-}
-
-template <int C, int MK>
-__device__ __forceinline__ double level_u(double x, const double (&v)[C], double m, double alpha, bool special,
-                                          const LevelScratch& sh, double (&u)[C], double (&a)[C]) {
-    if (special) {
-        double cv[C], cu[C], ca[C];  // copies: only they live in memory
-#pragma unroll
-        for (int k = 0; k < C; ++k) cv[k] = v[k];
-        const double j = level_u_special<C, MK>(x, cv, m, alpha, sh, cu, ca);
-#pragma unroll
-        for (int k = 0; k < C; ++k) {
-            u[k] = cu[k];
-            a[k] = ca[k];
-        }
-        return j;
-    }
-    return level_products<C, MK, false>(x, v, m, alpha, sh, u, a);
 }
 
 // Whether any two of the centroids (the same in every lane) are equal.
@@ -555,11 +516,11 @@ __device__ __forceinline__ void level_iterate(const LevelProblem& pb, uint32_t c
             double vp[C], t[C];
 #pragma unroll
             for (int k = 0; k < C; ++k) vp[k] = pb.hist_v[(int64_t)(p - 1) * C + k];
-            level_u<C, MK>(x, vp, pb.m, pb.alpha, twins, sh, uo, t);
+            level_u<C, MK>(x, vp, pb.m, pb.alpha, twins, cnt != 0u, sh, uo, t);
             bool fin = true;
 #pragma unroll
             for (int k = 0; k < C; ++k) fin = fin && isfinite(uo[k]);
-            if (!fin) level_u<C, MK>(x, vp, pb.m, pb.alpha, true, sh, uo, t);
+            if (!fin) level_u<C, MK>(x, vp, pb.m, pb.alpha, true, cnt != 0u, sh, uo, t);
         }
     }
     // also where v^0 was committed before this launch (a query or labels first)
@@ -585,10 +546,10 @@ __device__ __forceinline__ void level_iterate(const LevelProblem& pb, uint32_t c
         const int64_t stop_at = (int64_t)p + pb.max_passes - 1;
         const int calm = huge ? -1 : (int)(stop_at < pb.max_iter ? stop_at : pb.max_iter);
         int par = 0, slot = 0;
-        bool special = twins;
+        bool safe = twins;
         while (true) {
             double u[C], a[C];
-            const double jt = level_u<C, MK>(x, v, pb.m, pb.alpha, special, sh, u, a);
+            const double jt = level_u<C, MK>(x, v, pb.m, pb.alpha, safe, cnt != 0u, sh, u, a);
 #pragma unroll
             for (int k = 0; k < C; ++k) a[k] *= c;
             double num[SETS], den[SETS];
@@ -642,7 +603,7 @@ __device__ __forceinline__ void level_iterate(const LevelProblem& pb, uint32_t c
             int dec = (FCM_RUNNING + kLvStatus0) << kLvStatusShift;
             bool run = true;
             if (!(go && p < calm)) {
-                const bool retry = !ok && !special;  // again, with the form that holds for any centroids
+                const bool retry = !ok && !safe;  // again, with the form that holds for any centroids
                 const int status = !ok || huge ? FCM_ENUMERIC
                                                : (p >= 1 && !go ? FCM_OK : (p >= pb.max_iter ? FCM_NOT_CONVERGED
                                                                                              : FCM_RUNNING));
@@ -664,10 +625,9 @@ __device__ __forceinline__ void level_iterate(const LevelProblem& pb, uint32_t c
                 for (int k = 0; k < C; ++k) uo[k] = u[k];
 #pragma unroll
                 for (int s = 0; s < SETS; ++s) vk[s] = vn[s];
-                special = twins;
                 ++p;
             } else if (dec & kLvRetry) {
-                special = true;
+                safe = true;
             } else {
 #pragma unroll
                 for (int s = 0; s < SETS; ++s) {
